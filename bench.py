@@ -61,7 +61,7 @@ PREC_BYTES = {"dslash_f64": 16, "dslash_f32": 8, "dslash_f16": 4, "dslash_step":
 # smoother step reads r and writes r', and reads and writes x
 SPINOR_VOLUMES = {"dslash_f64": 2, "dslash_f32": 2, "dslash_f16": 2, "dslash_step": 4}
 KERNEL_NAMES = {"dslash_f16": "k_dslash<F16, DOT> (fused MR-smoother dslash)",
-                "dslash_f32": "k_dslash_rb<F32> (two rhs per thread)", "dslash_f64": "k_dslash<F64>",
+                "dslash_f32": "k_dslash<F32> (two rhs per thread)", "dslash_f64": "k_dslash<F64>",
                 "dslash_step": "k_dslash_march<F16, DOT, MR> (fused FP16 smoother step: dslash, dots, "
                                "r and x updates)"}
 N_SITE_VARIANTS_DOT = 2  # site-parallel launch variants of the reducing dslash; plane-marching ones follow

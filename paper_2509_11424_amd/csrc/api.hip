@@ -45,24 +45,24 @@ void Context::prof_end(int kclass, double bytes, hipEvent_t a) {
   if (prof.pending.size() > 4096) prof_flush();
 }
 
-int Context::choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt) {
+int Context::choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt, int more) {
   auto it = tune.table.find(key);
   if (it != tune.table.end()) {
-    MGM_CHECK(it->second.variant < nvar, MGM_ERR_INVALID_ARG,
+    MGM_CHECK(it->second.variant < nvar + more, MGM_ERR_INVALID_ARG,
               "pinned launch variant " + std::to_string(it->second.variant) + " out of range for " + key);
     run(it->second.variant);
     return it->second.variant;
   }
-  if (!tune.enabled || capturing || nvar <= 1) {
+  if (!tune.enabled || capturing || nvar + more <= 1) {
     run(dflt);
     return dflt;
   }
   const bool prof_was_on = prof.on;
   prof.on = false;  // tuning launches stay out of the kernel-class statistics
   Tuner::Entry e;
-  e.ms.assign(nvar, 0.0f);
+  e.ms.assign(nvar + more, 0.0f);
   hipEvent_t a = take_event(), b = take_event();
-  for (int v = 0; v < nvar; v++) {
+  for (int v = 0; v < nvar + more; v++) {
     run(v);  // warm-up
     float best = 3.0e38f;
     for (int rep = 0; rep < 3; rep++) {
@@ -77,9 +77,10 @@ int Context::choose(const std::string& key, int nvar, const std::function<void(i
     e.ms[v] = best;
   }
   int bv = 0;
-  for (int v = 1; v < nvar; v++)
+  for (int v = 1; v < nvar + more; v++)
     if (e.ms[v] < e.ms[bv]) bv = v;
   e.variant = bv;
+  e.ms.resize(nvar);  // the report lists the first nvar
   tune.table[key] = e;
   prof.pool.push_back(a);
   prof.pool.push_back(b);

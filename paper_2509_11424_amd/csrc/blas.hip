@@ -659,8 +659,46 @@ __global__ __launch_bounds__(256) void k_segment_sum(const double2* data, int64_
   if (threadIdx.x == 0) seg[(int64_t)g * nout + o] = make_double2(sa[0], sb[0]);
 }
 
+// the same sums in one pass (grid = 2 * nrhs): thread j of 256 sums entries
+// j, j + 256, ..., then a fixed tree
+__global__ __launch_bounds__(256) void k_sum_dn(const double2* part, int64_t nblk, int nrhs, double2* qr, double* qq) {
+  const int o = blockIdx.x, t = threadIdx.x;
+  double a = 0, b = 0;
+#pragma unroll 4
+  for (int64_t j = t; j < nblk; j += 256) {
+    const double2 v = part[(int64_t)o * nblk + j];
+    a += v.x;
+    b += v.y;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    a += __shfl_down(a, off, 64);
+    b += __shfl_down(b, off, 64);
+  }
+  __shared__ double2 sw[4];
+  if ((t & 63) == 0) sw[t >> 6] = make_double2(a, b);
+  __syncthreads();
+  if (t != 0) return;
+  for (int w = 1; w < 4; w++) {
+    a += sw[w].x;
+    b += sw[w].y;
+  }
+  if (o < nrhs)
+    qr[o] = make_double2(a, b);
+  else
+    qq[o - nrhs] = a;
+}
+
+// One launch up to 4096 partials a column (16 dependent-free loads a thread;
+// the two launches it replaces cost 10 us of a 50 us step on 16^4), two beyond,
+// where one block a column would be the bottleneck.
 void b_finalize_dot_norm(Context* c, Scratch& s, const double2* part, int64_t nblk, int nrhs, double2* qr,
                          double* qq) {
+  if (nblk <= 4096) {
+    hipLaunchKernelGGL(k_sum_dn, dim3(2 * nrhs), dim3(256), 0, c->stream, part, nblk, nrhs, qr, qq);
+    MGM_LAUNCH_CHECK();
+    return;
+  }
   const int G = (int)std::min<int64_t>(64, std::max<int64_t>(1, nblk / 256));
   need(s, (size_t)G * 2 * nrhs);
   hipLaunchKernelGGL(k_segment_sum, dim3(G, 2 * nrhs), dim3(256), 0, c->stream, part, nblk, 2 * nrhs,

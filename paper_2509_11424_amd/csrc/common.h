@@ -300,8 +300,11 @@ struct Context {
   void prof_flush();
   void sync() { MGM_HIP(hipStreamSynchronize(stream)); }
   // variant of `key` among nvar; run(v) launches variant v on the stream;
-  // `dflt` is the variant used while the autotuner is off
-  int choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt = 0);
+  // `dflt` is the variant used while the autotuner is off.  `more` variants
+  // follow the nvar listed ones: they are tuned and pinned like them, but the
+  // times of the report are those of the listed ones, whose numbers saved
+  // tables hold
+  int choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt = 0, int more = 0);
 };
 
 // RAII timer around one launch of kernel class kc (no-op when profiling is off).

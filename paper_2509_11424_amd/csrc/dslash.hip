@@ -9,9 +9,9 @@
 // A_z = -i s3, A_t = 1, so (1 -/+ g_mu) psi is fixed by the half spinor
 // h = u -/+ A_mu l (u, l: upper / lower spin pairs):
 //   (1 - g) psi = (h, -A^H h),   (1 + g) psi = (h, A^H h).
-// The dslash is HBM-bound: one thread per (site, rhs), every field stored
-// component-major so each wave's loads are contiguous; the rhs index is the
-// fastest so lanes of one site share (broadcast) its links and clover.
+// Every field is stored component-major so each wave's loads are contiguous;
+// the rhs index is the fastest so lanes of one site share (broadcast) its links
+// and clover.
 #include "fine.h"
 #include "fine_dev.h"
 #include "devonce.h"
@@ -217,13 +217,16 @@ __global__ void k_cvt_r64_r16(__half* o, const double* in, int64_t n) {
 // ---------------------------------------------------------------- dslash
 
 // Per-rhs block sums of the fused reductions, written to dpart[2][nrhs][block]
-// (q^H in, then |q|^2).  When nq = nrhs / RB divides 64 (and nrhs <= 64),
-// lane % nq fixes a thread's rhs columns: a fixed xor-shuffle tree sums each
+// (q^H in, then |q|^2).  Thread u of the block holds the columns
+// RB ((base + u) % nq) .. + RB - 1 with nq = nrhs / RB.  When nq divides 64 (and
+// nrhs <= 64), lane % nq fixes a thread's columns: a fixed xor-shuffle tree sums each
 // wave and the four wave rows are added in order.  Otherwise every thread's
-// entries go through LDS and thread t < nrhs sums those of rhs t in thread
-// order.  Both orders are fixed, so results are deterministic.
+// entries go through LDS: G threads per column each sum every G-th of its
+// entries, and one adds the G sums in order (one thread per column took 30 us
+// of a 44 us step at 25 rhs on 8^4).  Both orders are fixed, so results are
+// deterministic.
 template <int RB>
-__device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&dqq)[RB], bool active, int r0,
+__device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&dqq)[RB], bool active, int base,
                                                 int nrhs, int64_t nblocks, double2* __restrict__ dpart) {
   const int nq = nrhs / RB;
   if (!active) {
@@ -233,6 +236,7 @@ __device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&
       dqq[j] = 0;
     }
   }
+  const int t = threadIdx.x;
   if (nrhs <= 64 && 64 % nq == 0) {
     __shared__ double2 sw_qr[4][64];
     __shared__ double sw_qq[4][64];
@@ -244,7 +248,7 @@ __device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&
         dqq[j] += __shfl_xor(dqq[j], off, 64);
       }
     }
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = t >> 6, lane = t & 63;
     if (lane < nq) {
 #pragma unroll
       for (int j = 0; j < RB; j++) {
@@ -253,8 +257,7 @@ __device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&
       }
     }
     __syncthreads();
-    if ((int)threadIdx.x < nrhs) {
-      const int t = threadIdx.x;
+    if (t < nrhs) {
       double a = 0, b = 0, n2 = 0;
       for (int ww = 0; ww < (int)(blockDim.x >> 6); ww++) {
         a += sw_qr[ww][t].x;
@@ -266,217 +269,120 @@ __device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&
     }
     return;
   }
-  __shared__ double2 sh_qr[256 * RB];
+  __shared__ double2 sh_qr[256 * RB];  // [column of the thread][thread]
   __shared__ double sh_qq[256 * RB];
-  __shared__ int sh_r[256 * RB];
 #pragma unroll
   for (int j = 0; j < RB; j++) {
-    sh_qr[threadIdx.x * RB + j] = make_double2(dqr[j].re, dqr[j].im);
-    sh_qq[threadIdx.x * RB + j] = dqq[j];
-    sh_r[threadIdx.x * RB + j] = active ? r0 + j : -1;
+    sh_qr[j * 256 + t] = make_double2(dqr[j].re, dqr[j].im);
+    sh_qq[j * 256 + t] = dqq[j];
   }
   __syncthreads();
-  if ((int)threadIdx.x < nrhs) {
-    double a = 0, b = 0, n2 = 0;
-    for (int u = 0; u < (int)blockDim.x * RB; u++)
-      if (sh_r[u] == (int)threadIdx.x) {
-        a += sh_qr[u].x;
-        b += sh_qr[u].y;
-        n2 += sh_qq[u];
-      }
-    dpart[(int64_t)threadIdx.x * nblocks + blockIdx.x] = make_double2(a, b);
-    dpart[(int64_t)(nrhs + threadIdx.x) * nblocks + blockIdx.x] = make_double2(n2, 0.0);
+  int G = 1;
+  while (2 * G * nrhs <= 256) G *= 2;
+  double a = 0, b = 0, n2 = 0;
+  const int r = t % nrhs, g = t / nrhs;
+  if (g < G) {
+    const int q = r / RB, j = r - q * RB;
+    int u = q - base;
+    if (u < 0) u += nq;
+    for (u += g * nq; u < 256; u += G * nq) {
+      a += sh_qr[j * 256 + u].x;
+      b += sh_qr[j * 256 + u].y;
+      n2 += sh_qq[j * 256 + u];
+    }
+  }
+  __syncthreads();
+  sh_qr[t] = make_double2(a, b);
+  sh_qq[t] = n2;
+  __syncthreads();
+  if (t < nrhs) {
+    for (int k = 1; k < G; k++) {
+      a += sh_qr[t + k * nrhs].x;
+      b += sh_qr[t + k * nrhs].y;
+      n2 += sh_qq[t + k * nrhs];
+    }
+    dpart[(int64_t)t * nblocks + blockIdx.x] = make_double2(a, b);
+    dpart[(int64_t)(nrhs + t) * nblocks + blockIdx.x] = make_double2(n2, 0.0);
   }
 }
 
-constexpr int kSlab = 4;  // time slices (one wave each) per 256-thread block
+// Order in which the site-parallel kernel walks the lattice: bands of bt time
+// slices, inside a band bands of bz planes, inside those bands of by rows;
+// within a tile x is fastest, then y, z, t.  by = bz = bt = 0: lexicographic.
+struct SiteOrder {
+  int by, bz, bt;
+};
 
+// coordinates of the p-th site of the order
+__device__ __forceinline__ void ordered_site(const Geom& g, const SiteOrder& o, uint32_t p, int c[4]) {
+  const uint32_t X = (uint32_t)g.X, Y = (uint32_t)g.Y, Z = (uint32_t)g.Z, T = (uint32_t)g.T;
+  uint32_t ny = Y, nz = Z, t0 = 0, z0 = 0, y0 = 0;
+  if (o.bt > 0) {
+    uint32_t q = p / ((uint32_t)o.bt * X * Y * Z);
+    t0 = q * (uint32_t)o.bt;
+    const uint32_t nt = T - t0 < (uint32_t)o.bt ? T - t0 : (uint32_t)o.bt;
+    p -= t0 * X * Y * Z;
+    q = p / ((uint32_t)o.bz * X * Y * nt);
+    z0 = q * (uint32_t)o.bz;
+    nz = Z - z0 < (uint32_t)o.bz ? Z - z0 : (uint32_t)o.bz;
+    p -= z0 * X * Y * nt;
+    q = p / ((uint32_t)o.by * X * nz * nt);
+    y0 = q * (uint32_t)o.by;
+    ny = Y - y0 < (uint32_t)o.by ? Y - y0 : (uint32_t)o.by;
+    p -= y0 * X * nz * nt;
+  }
+  uint32_t q = p / X;
+  c[0] = (int)(p - q * X);
+  p = q;
+  q = p / ny;
+  c[1] = (int)(y0 + p - q * ny);
+  p = q;
+  q = p / nz;
+  c[2] = (int)(z0 + p - q * nz);
+  c[3] = (int)(t0 + q);
+}
+
+// Site-parallel dslash: one thread computes RB consecutive right-hand sides
+// of one site, so the links, clover entries and index arithmetic are shared by
+// the columns (16-byte FP32, 8-byte FP16 spinor loads at RB = 2).  Bound by the
+// L1 misses a CU keeps in flight: all nine spinor reads of a site miss L1
+// (about 60 outstanding 128-byte lines at 560 cycles, FP64 at 20 rhs on
+// 16^3 x 32), 230 ps a site and rhs in FP64, 105 in FP32, 78 in FP16 whatever the
+// lattice.
 // DOT: also reduce q^H in and |q|^2 per rhs for the minimal-residual smoother
 // (q = D in), written per block to dpart[2][nrhs][block] (q^H in, then |q|^2).
-template <class P, bool DOT>
+// MR (with DOT): the smoother step of k_dslash_march (see there): q is not
+// stored, out = in - omega q, xio += omega in, dots of the unrounded q.
+template <class P, bool DOT, bool MR, int RB>
 __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
                                                 const typename P::S* __restrict__ in,
                                                 const typename P::S* __restrict__ U,
-                                                const typename P::RS* __restrict__ C, Geom g,
-                                                int nrhs, int64_t nblocks, int slab,
-                                                double2* __restrict__ dpart) {
+                                                const typename P::RS* __restrict__ C, Geom g, int nrhs,
+                                                int64_t nblocks, SiteOrder ord, double2* __restrict__ dpart,
+                                                typename P::S* __restrict__ xio, const double2* __restrict__ wqr,
+                                                const double* __restrict__ wqq) {
   using R = typename P::R;
+  static_assert(!MR || DOT, "the smoother step also produces the next dots");
   const int64_t blk = xcd_block(blockIdx.x, nblocks);
   const int64_t V = g.V;
-  const int64_t N = V * nrhs;
-  int64_t tid;
-  if (slab) {
-    // Block = kSlab waves on kSlab consecutive time slices of one 64-element
-    // chunk of a slice: the t-neighbours of the inner waves are loaded by
-    // sibling waves of the same block at about the same time.
-    const int64_t per_slice = (V / g.T) * nrhs;
-    const int64_t chunks = per_slice / 64;
-    const int64_t chunk = blk % chunks, tg = blk / chunks;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    tid = (tg * kSlab + w) * per_slice + chunk * 64 + lane;
-  } else {
-    tid = blk * blockDim.x + threadIdx.x;
-  }
+  const int64_t N = V * nrhs;  // elements per dof plane
+  const int nq = nrhs / RB;    // threads per site
+  // the block's first element is split once, in 32 bits where it can be;
+  // V < 2^31 (the FP64 links alone take 576 bytes a site)
+  const int64_t p0 = nblocks < (1 << 23) ? (int64_t)((uint32_t)blk * 256u / (uint32_t)nq) : blk * 256 / nq;
+  const int base = (int)(blk * 256 - p0 * nq);
+  const uint32_t q0 = (uint32_t)base + threadIdx.x;
+  const int64_t p = p0 + q0 / (uint32_t)nq;
+  const int r0 = (int)(q0 % (uint32_t)nq) * RB;
   // the reducing variant keeps every thread until the block reduction;
   // threads past the end compute site 0 and contribute nothing
-  const bool active = tid < N;
+  const bool active = p < V;
   if (!DOT && !active) return;
-  if (!active) tid = 0;
-  const int64_t s = tid / nrhs;
-  const int r = (int)(tid - s * nrhs);
   int c[4];
-  {
-    int64_t q = s;
-    c[0] = (int)(q % g.X); q /= g.X;
-    c[1] = (int)(q % g.Y); q /= g.Y;
-    c[2] = (int)(q % g.Z); q /= g.Z;
-    c[3] = (int)q;
-  }
+  ordered_site(g, ord, active ? (uint32_t)p : 0u, c);
   const int64_t sy = g.X, sz = (int64_t)g.X * g.Y, st = sz * g.Z;
-
-  cx<R> acc[12];
-#pragma unroll
-  for (int k = 0; k < 12; k++) acc[k] = {0, 0};
-  // The eight hops run as a loop that is not unrolled, so only one
-  // neighbour's spinor and link are live at a time (registers stay low and
-  // occupancy high enough to cover HBM latency).
-#pragma unroll 1
-  for (int hop = 0; hop < 8; hop++) {
-    const int mu = hop >> 1;
-    const bool fwd = (hop & 1) == 0;
-    const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
-    const int ex = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
-    const int64_t sd = mu == 0 ? 1 : mu == 1 ? sy : mu == 2 ? sz : st;
-    const bool wrap = fwd ? (cm == ex - 1) : (cm == 0);
-    const int64_t span = (int64_t)(ex - 1) * sd;
-    const int64_t sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
-    // -1/2 (1 -/+ g_mu), times -1 on hops across the time boundary
-    const R f = (mu == 3 && wrap && g.antiperiodic) ? (R)0.5 : (R)-0.5;
-    const R sg = fwd ? (R)-1 : (R)1;  // half spinor h = u + sg * A_mu l
-    const int64_t e = sn * nrhs + r;
-    cx<R> h[2][3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-      cx<R> u0 = P::ld(in, (int64_t)(0 * 3 + a) * N + e), u1 = P::ld(in, (int64_t)(1 * 3 + a) * N + e);
-      cx<R> l0 = P::ld(in, (int64_t)(2 * 3 + a) * N + e), l1 = P::ld(in, (int64_t)(3 * 3 + a) * N + e);
-      cx<R> a0, a1;
-      A_times(mu, l0, l1, a0, a1);
-      h[0][a] = u0 + sg * a0;
-      h[1][a] = u1 + sg * a1;
-    }
-    // forward: U_mu(x) h ; backward: U_mu(x - mu)^H h
-    const typename P::S* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
-    cx<R> Um[3][3];
-#pragma unroll
-    for (int k = 0; k < 9; k++) Um[k / 3][k % 3] = P::ld(Ub, (int64_t)k * V);
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-      cx<R> g0 = {0, 0}, g1 = {0, 0};
-      if (fwd) {
-#pragma unroll
-        for (int b = 0; b < 3; b++) {
-          fma_(g0, Um[a][b], h[0][b]);
-          fma_(g1, Um[a][b], h[1][b]);
-        }
-      } else {
-#pragma unroll
-        for (int b = 0; b < 3; b++) {  // (U^H)_{ab} = conj(U_{ba})
-          fmac_(g0, Um[b][a], h[0][b]);
-          fmac_(g1, Um[b][a], h[1][b]);
-        }
-      }
-      cx<R> d0, d1;
-      Ad_times(mu, g0, g1, d0, d1);  // lower spins: -A^H g (forward), +A^H g (backward)
-      const R fs = f * sg;
-      axpy_(acc[0 * 3 + a], f, g0);
-      axpy_(acc[1 * 3 + a], f, g1);
-      axpy_(acc[2 * 3 + a], fs, d0);
-      axpy_(acc[3 * 3 + a], fs, d1);
-    }
-  }
-  // site-local term: clover blocks with the mass folded into the diagonal
-  cx<double> dqr = {0, 0};
-  double dqq = 0;
-#pragma unroll 1
-  for (int chi = 0; chi < 2; chi++) {
-    cx<R> p[6], q[6];
-#pragma unroll
-    for (int k = 0; k < 6; k++) p[k] = P::ld(in, (int64_t)(6 * chi + k) * N + tid);
-    clover_block<P>(C, V, s, chi, p, q);
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-      cx<R> o;
-      if (chi == 0) o = acc[k] = acc[k] + q[k];
-      else o = acc[6 + k] = acc[6 + k] + q[k];
-      if (DOT) {
-        // the rounded stored value enters the dots
-        typename P::S st_;
-        P::st(&st_, 0, o);
-        const cx<R> os = P::ld(&st_, 0);
-        fmac_(dqr, cx<double>{(double)os.re, (double)os.im}, cx<double>{(double)p[k].re, (double)p[k].im});
-        dqq += (double)os.re * os.re + (double)os.im * os.im;
-      }
-    }
-  }
-  if (active) {
-#pragma unroll
-    for (int k = 0; k < 12; k++) P::st(out, (int64_t)k * N + tid, acc[k]);
-  }
-  if (DOT) {
-    cx<double> qr1[1] = {dqr};
-    double qq1[1] = {dqq};
-    dot_block_store<1>(qr1, qq1, active, r, nrhs, nblocks, dpart);
-  }
-}
-
-// Variant for FP32/FP16 with an even rhs count: one thread computes RB = 2
-// consecutive right-hand sides of one site, so the links, clover entries and
-// index arithmetic are shared by the two columns and the spinor loads become
-// 16-byte (FP32) or 8-byte (FP16) vector loads.  Same block order, DOT
-// reduction and output as k_dslash.
-template <class P, bool DOT, int RB>
-__global__ __launch_bounds__(256) void k_dslash_rb(typename P::S* __restrict__ out,
-                                                const typename P::S* __restrict__ in,
-                                                const typename P::S* __restrict__ U,
-                                                const typename P::RS* __restrict__ C, Geom g,
-                                                int nrhs, int64_t nblocks, int slab,
-                                                double2* __restrict__ dpart) {
-  using R = typename P::R;
-  const int64_t blk = xcd_block(blockIdx.x, nblocks);
-  const int64_t V = g.V;
-  const int64_t N = V * nrhs;       // elements per dof plane
-  const int nq = nrhs / RB;         // threads per site
-  const int64_t NT = V * nq;        // threads in the grid that carry work
-  int64_t tid;
-  if (slab) {
-    // Block = kSlab waves on kSlab consecutive time slices of one 64-thread
-    // chunk of a slice: the t-neighbours of the inner waves are loaded by
-    // sibling waves of the same block at about the same time.
-    const int64_t per_slice = (V / g.T) * nq;
-    const int64_t chunks = per_slice / 64;
-    const int64_t chunk = blk % chunks, tg = blk / chunks;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    tid = (tg * kSlab + w) * per_slice + chunk * 64 + lane;
-  } else {
-    tid = blk * blockDim.x + threadIdx.x;
-  }
-  // the reducing variant keeps every thread until the block reduction;
-  // threads past the end compute site 0 and contribute nothing
-  const bool active = tid < NT;
-  if (!DOT && !active) return;
-  if (!active) tid = 0;
-  const int64_t s = tid / nq;
-  const int r0 = (int)(tid - s * nq) * RB;
+  const int64_t s = c[0] + sy * c[1] + sz * c[2] + st * c[3];
   const int64_t es = s * nrhs + r0;  // this thread's first element in a plane
-  int c[4];
-  {
-    int64_t q = s;
-    c[0] = (int)(q % g.X); q /= g.X;
-    c[1] = (int)(q % g.Y); q /= g.Y;
-    c[2] = (int)(q % g.Z); q /= g.Z;
-    c[3] = (int)q;
-  }
-  const int64_t sy = g.X, sz = (int64_t)g.X * g.Y, st = sz * g.Z;
 
   cx<R> acc[12][RB];
 #pragma unroll
@@ -551,16 +457,29 @@ __global__ __launch_bounds__(256) void k_dslash_rb(typename P::S* __restrict__ o
   // site-local term: clover blocks with the mass folded into the diagonal
   cx<double> dqr[RB];
   double dqq[RB];
+  cx<R> om[RB], sqr[RB];  // smoother step: omega, this site's dots
+  R sqq[RB];
 #pragma unroll
   for (int j = 0; j < RB; j++) {
     dqr[j] = {0, 0};
     dqq[j] = 0;
+    om[j] = sqr[j] = {0, 0};
+    sqq[j] = 0;
+    if (MR) {
+      const double d = wqq[r0 + j];
+      if (d > 0.0) om[j] = {(R)(wqr[r0 + j].x / d), (R)(wqr[r0 + j].y / d)};
+    }
   }
 #pragma unroll 1
   for (int chi = 0; chi < 2; chi++) {
     cx<R> pv[6][RB];
 #pragma unroll
     for (int k = 0; k < 6; k++) P::template ldv<RB>(in, (int64_t)(6 * chi + k) * N + es, pv[k]);
+    cx<R> xv[6][RB];
+    if (MR) {
+#pragma unroll
+      for (int k = 0; k < 6; k++) P::template ldv<RB>(xio, (int64_t)(6 * chi + k) * N + es, xv[k]);
+    }
 #pragma unroll
     for (int j = 0; j < RB; j++) {
       cx<R> x6[6], q6[6];
@@ -572,7 +491,18 @@ __global__ __launch_bounds__(256) void k_dslash_rb(typename P::S* __restrict__ o
         cx<R> o;
         if (chi == 0) o = acc[k][j] = acc[k][j] + q6[k];
         else o = acc[6 + k][j] = acc[6 + k][j] + q6[k];
-        if (DOT) {
+        if (MR) {
+          fmac_(sqr[j], o, x6[k]);
+          sqq[j] += o.re * o.re + o.im * o.im;
+          // r - omega q (in place of r), and x + omega r
+          fma_(xv[k][j], om[j], x6[k]);
+          cx<R> rn = x6[k];
+          rn.re = fmar(-om[j].re, o.re, rn.re);
+          rn.re = fmar(om[j].im, o.im, rn.re);
+          rn.im = fmar(-om[j].re, o.im, rn.im);
+          rn.im = fmar(-om[j].im, o.re, rn.im);
+          pv[k][j] = rn;
+        } else if (DOT) {
           // the rounded stored value enters the dots
           typename P::S st_;
           P::st(&st_, 0, o);
@@ -582,12 +512,25 @@ __global__ __launch_bounds__(256) void k_dslash_rb(typename P::S* __restrict__ o
         }
       }
     }
+    if (MR && active) {
+#pragma unroll
+      for (int k = 0; k < 6; k++) {
+        P::template stv<RB>(out, (int64_t)(6 * chi + k) * N + es, pv[k]);
+        P::template stv<RB>(xio, (int64_t)(6 * chi + k) * N + es, xv[k]);
+      }
+    }
   }
-  if (active) {
+  if (MR) {
+#pragma unroll
+    for (int j = 0; j < RB; j++) {
+      dqr[j] = {(double)sqr[j].re, (double)sqr[j].im};
+      dqq[j] = (double)sqq[j];
+    }
+  } else if (active) {
 #pragma unroll
     for (int k = 0; k < 12; k++) P::template stv<RB>(out, (int64_t)k * N + es, acc[k]);
   }
-  if (DOT) dot_block_store<RB>(dqr, dqq, active, r0, nrhs, nblocks, dpart);
+  if (DOT) dot_block_store<RB>(dqr, dqq, active, base, nrhs, nblocks, dpart);
 }
 
 // ------------------------------------------------- plane-marching dslash
@@ -1252,43 +1195,48 @@ int64_t FineOp::nblocks(mgm_prec p, int nrhs, bool dot) const {
   return (g.V * (nrhs / rb_of(p, nrhs, dot)) + 255) / 256;
 }
 
+// Rows of 8 planes (4 in FP64, whose sites are twice as long) of 4 time slices, so that neighbours in z and t are read
+// while their lines are still in the XCD's L2 (FP32, 20 rhs on 32^4: 2.13 ms against
+// 2.38 lexicographic, 12 rhs on 24^3 x 48: 0.84 against 0.90; FP64, 4 rhs on 32^4:
+// 1.09 against 1.17).  Vectors that fit the eight L2s (32 MB) are walked
+// lexicographically: their index arithmetic is shorter, which shows in launches
+// of 20 us.
+static SiteOrder site_order(const Geom& g, mgm_prec p, int nrhs) {
+  if (12.0 * g.V * nrhs * (double)prec_bytes(p) <= 32e6) return SiteOrder{0, 0, 0};
+  return SiteOrder{1, std::min(g.Z, p == MGM_PREC_F64 ? 4 : 8), std::min(g.T, 4)};
+}
+
+// Extra arrays of the smoother-step mode (all null otherwise).
+struct MrArgs {
+  void* x = nullptr;
+  const double2* qr = nullptr;
+  const double* qq = nullptr;
+};
+
+template <class P, bool DOT, bool MR, int RB>
+static int64_t launch_site_p(const FineOp& op, const typename P::S* U, const typename P::RS* C, const void* x, void* y,
+                          int nrhs, double2* dpart, SiteOrder ord, const MrArgs& mr) {
+  using S = typename P::S;
+  const int64_t nb = (op.g.V * (nrhs / RB) + 255) / 256;
+  hipLaunchKernelGGL((k_dslash<P, DOT, MR, RB>), dim3((unsigned)nb), dim3(256), 0, op.ctx->stream, (S*)y,
+                     (const S*)x, U, C, op.g, nrhs, nb, ord, dpart, (S*)mr.x, mr.qr, mr.qq);
+  MGM_LAUNCH_CHECK();
+  return nb;
+}
+
 template <bool DOT, int RB>
-static void launch_rb(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart,
-                      bool allow_slab) {
-  const Geom& g = op.g;
-  const int threads = 256;
-  const int64_t nb = (g.V * (nrhs / RB) + 255) / 256;
-  // slab mapping needs whole 64-thread chunks per slice and kSlab | T; it
-  // then covers exactly nb * 256 = V * nrhs / RB threads
-  const int64_t per_slice = (g.V / g.T) * (nrhs / RB);
-  const int slab = (allow_slab && per_slice % 64 == 0 && g.T % kSlab == 0 && threads == 64 * kSlab) ? 1 : 0;
-  hipStream_t st = op.ctx->stream;
+static int64_t launch_rb(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart,
+                      SiteOrder ord) {
   switch (p) {
     case MGM_PREC_F64:
-      MGM_CHECK(RB == 1, MGM_ERR_INVALID_ARG, "FP64 dslash takes one rhs per thread");
-      hipLaunchKernelGGL((k_dslash<F64, DOT>), dim3((unsigned)nb), dim3(threads), 0, st, (double2*)y,
-                         (const double2*)x, op.U64, op.C64, g, nrhs, nb, slab, dpart);
-      break;
+      return launch_site_p<F64, DOT, false, RB>(op, op.U64, op.C64, x, y, nrhs, dpart, ord, MrArgs());
     case MGM_PREC_F32:
-      if (RB == 2)
-        hipLaunchKernelGGL((k_dslash_rb<F32, DOT, 2>), dim3((unsigned)nb), dim3(threads), 0, st, (float2*)y,
-                           (const float2*)x, op.U32, op.C32, g, nrhs, nb, slab, dpart);
-      else
-        hipLaunchKernelGGL((k_dslash<F32, DOT>), dim3((unsigned)nb), dim3(threads), 0, st, (float2*)y,
-                           (const float2*)x, op.U32, op.C32, g, nrhs, nb, slab, dpart);
-      break;
+      return launch_site_p<F32, DOT, false, RB>(op, op.U32, op.C32, x, y, nrhs, dpart, ord, MrArgs());
     case MGM_PREC_F16:
-      if (RB == 2)
-        hipLaunchKernelGGL((k_dslash_rb<F16, DOT, 2>), dim3((unsigned)nb), dim3(threads), 0, st, (__half2*)y,
-                           (const __half2*)x, op.U16, op.C16, g, nrhs, nb, slab, dpart);
-      else
-        hipLaunchKernelGGL((k_dslash<F16, DOT>), dim3((unsigned)nb), dim3(threads), 0, st, (__half2*)y,
-                           (const __half2*)x, op.U16, op.C16, g, nrhs, nb, slab, dpart);
-      break;
+      return launch_site_p<F16, DOT, false, RB>(op, op.U16, op.C16, x, y, nrhs, dpart, ord, MrArgs());
     default:
       throw Error(MGM_ERR_INVALID_ARG, "dslash precision must be F64, F32 or F16");
   }
-  MGM_LAUNCH_CHECK();
 }
 
 // Plane-marching shapes (rows per tile, z-planes per block, rhs per block),
@@ -1323,12 +1271,60 @@ static bool march_ok(const FineOp& op, mgm_prec p, int nrhs, const MarchShape& m
   return march_lds(g, p, m, dot) <= op.ctx->max_lds;
 }
 
-// Extra arrays of the smoother-step mode (all null otherwise).
-struct MrArgs {
-  void* x = nullptr;
-  const double2* qr = nullptr;
-  const double* qq = nullptr;
-};
+// Estimated microseconds of the FP16 forms, by which the untuned default is
+// chosen and the smoother forms its column groups.  Marching: a CU holds 1024
+// threads of these kernels (128 VGPRs) or as many blocks as its LDS; a plane of
+// a resident set of th threads takes 7 us of latency plus 12.7 ns a thread
+// (20 us for a full CU at 8 rhs per block on 32^3 x 64), a block zs + 1 planes.
+// Rows of fewer than 4 rhs, and blocks that hold a small part of a site's rhs,
+// waste part of each cache line: measured 1.15x at 2 and 1.4x at 1 rhs per block,
+// 1.06x to 2.4x when a block holds one half to one tenth of them.
+static double march_us(const FineOp& op, mgm_prec p, int nrhs, const MarchShape& m, bool dot) {
+  const Geom& g = op.g;
+  const int64_t blocks = (int64_t)(nrhs / m.nbr) * g.T * (g.Y / m.ty) * (g.Z / m.zs);
+  const int th = g.X * m.ty * m.nbr;
+  const int64_t cus = op.ctx->cu_count;
+  const int64_t res = std::max<int64_t>(
+      1, std::min<int64_t>(1024 / th, (int64_t)(op.ctx->max_lds / march_lds(g, p, m, dot))));
+  auto plane = [&](int64_t blocks_per_cu) { return blocks_per_cu == 0 ? 0.0 : 7.0 + 12.7e-3 * (double)(blocks_per_cu * th); };
+  const int64_t full = blocks / (cus * res), tail = (blocks - full * cus * res + cus - 1) / cus;
+  const double ratio = (double)nrhs / m.nbr;
+  const double line = (m.nbr == 1 ? 1.4 : m.nbr == 2 ? 1.15 : 1.0) * (1.0 + 0.015 * ratio * ratio);
+  return ((double)full * plane(res) + plane(tail)) * (m.zs + 1) * line;
+}
+// Site-parallel: measured 135 ps per site and rhs for the step and 115 ps for
+// the dslash (2 rhs per thread, 4 to 8 rhs, 16^4 to 32^3 x 64), and 12 us where a
+// launch does not fill the chip.
+static double site_us(const FineOp& op, int nrhs, bool step) {
+  return 12.0 + (step ? 135e-6 : 115e-6) * (double)op.g.V * nrhs;
+}
+// index of the fastest estimated shape, or -1 for the site-parallel kernel
+static int best_shape(const FineOp& op, mgm_prec p, int nrhs, const std::vector<MarchShape>& shapes, bool dot,
+                      bool step, double* us = nullptr) {
+  int best = -1;
+  double t = site_us(op, nrhs, step);
+  for (size_t i = 0; i < shapes.size(); i++) {
+    const double ti = march_us(op, p, nrhs, shapes[i], dot);
+    if (ti < t) {
+      t = ti;
+      best = (int)i;
+    }
+  }
+  if (us) *us = t;
+  return best;
+}
+static std::vector<MarchShape> march_shapes(const FineOp& op, mgm_prec p, int nrhs, bool dot) {
+  std::vector<MarchShape> shapes;
+  for (const MarchShape& m : kMarchShapes)
+    if (march_ok(op, p, nrhs, m, dot)) shapes.push_back(m);
+  return shapes;
+}
+
+double FineOp::step_us(int nrhs) const {
+  double us = 0;
+  best_shape(*this, MGM_PREC_F16, nrhs, march_shapes(*this, MGM_PREC_F16, nrhs, true), true, true, &us);
+  return us;
+}
 
 template <class P, bool DOT, bool MR, int TY, bool PK = false>
 static void launch_march_p(const FineOp& op, const typename P::S* U, const typename P::RS* C, const void* x,
@@ -1377,25 +1373,27 @@ static int64_t launch_march(const FineOp& op, mgm_prec p, const void* x, void* y
   return nb;
 }
 
-// Tuned launch shapes.  Site-parallel variants first: 0 (rb_of, slab
-// order), 1 the plain block order, and the non-reducing FP32/FP16 kernels
+// Tuned launch shapes.  Site-parallel variants first: 0 (rb_of, banded walk),
+// 1 the lexicographic walk, and the non-reducing FP32/FP16 kernels
 // with an even rhs count also try the other rhs-per-thread count (2, 3);
-// then every plane-marching shape that applies.  Untuned, FP16 takes the
-// first plane-marching shape that applies (measured fastest for the fused
-// smoother's 8 and 4 rhs on 32^3 x 64), FP32 and FP64 variant 0.  Returns the
-// block count of the variant that ran.
+// then every plane-marching shape that applies.  Untuned, FP16 takes the form
+// with the smallest estimated time (the first marching shape that applies left
+// 224 of 256 CUs idle on 16^4: 166 us against 31 at 4 rhs), FP32 and FP64
+// variant 0.  Returns the block count of the variant that ran.
 template <bool DOT>
 static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart) {
   const int rb0 = rb_of(p, nrhs, DOT);
   const bool alt = !DOT && p != MGM_PREC_F64 && nrhs % 2 == 0;
   const int nsite = alt ? 4 : 2;
-  std::vector<MarchShape> shapes;
-  for (const MarchShape& m : kMarchShapes)
-    if (march_ok(op, p, nrhs, m, DOT)) shapes.push_back(m);
+  const std::vector<MarchShape> shapes = march_shapes(op, p, nrhs, DOT);
   const std::string key = std::string(DOT ? "dslash_dot/" : "dslash/") + std::to_string((int)p) + "/" +
                           std::to_string(op.g.V) + "/" + std::to_string(nrhs);
   int64_t nb = 0;
-  const int dflt = (p == MGM_PREC_F16 && !shapes.empty()) ? nsite : 0;
+  int dflt = 0;
+  if (p == MGM_PREC_F16) {
+    const int i = best_shape(op, p, nrhs, shapes, DOT, false);
+    if (i >= 0) dflt = nsite + i;
+  }
   op.ctx->choose(
       key, nsite + (int)shapes.size(),
       [&](int v) {
@@ -1406,12 +1404,11 @@ static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* 
       return;
     }
     const int rb = v < 2 ? rb0 : 3 - rb0;
-    const bool slab = (v & 1) == 0;
+    const SiteOrder ord = (v & 1) == 0 ? site_order(op.g, p, nrhs) : SiteOrder{};
     if (rb == 2)
-      launch_rb<DOT, 2>(op, p, x, y, nrhs, dpart, slab);
+      nb = launch_rb<DOT, 2>(op, p, x, y, nrhs, dpart, ord);
     else
-      launch_rb<DOT, 1>(op, p, x, y, nrhs, dpart, slab);
-    nb = (op.g.V * (nrhs / rb) + 255) / 256;
+      nb = launch_rb<DOT, 1>(op, p, x, y, nrhs, dpart, ord);
       },
       dflt);
   return nb;
@@ -1449,9 +1446,7 @@ int64_t FineOp::apply_step(mgm_prec p, const void* r, void* r_next, void* x, con
                            int nrhs, double2* dpart) const {
   MGM_CHECK(step_fusable(p, nrhs), MGM_ERR_SHAPE, "no plane-marching tile for the fused smoother step");
   MGM_CHECK(r != r_next && r != x && r_next != x, MGM_ERR_INVALID_ARG, "fused smoother step needs distinct arrays");
-  std::vector<MarchShape> shapes;
-  for (const MarchShape& m : kMarchShapes)
-    if (march_ok(*this, p, nrhs, m, true)) shapes.push_back(m);
+  const std::vector<MarchShape> shapes = march_shapes(*this, p, nrhs, true);
   MrArgs mr;
   mr.x = x;
   mr.qr = qr;
@@ -1462,10 +1457,23 @@ int64_t FineOp::apply_step(mgm_prec p, const void* r, void* r_next, void* x, con
   // variants: every shape with FP32 arithmetic on converted values, then
   // every shape with packed FP16 arithmetic
   const int ns = (int)shapes.size();
-  ctx->choose(key, 2 * ns, [&](int v) {
-    MGM_CHECK(v >= 0 && v < 2 * ns, MGM_ERR_INVALID_ARG, "fused smoother launch variant out of range");
-    nb = launch_march<true, true>(*this, p, r, r_next, nrhs, dpart, shapes[v % ns], mr, v >= ns);
-  });
+  // then the site-parallel form, with FP32 arithmetic: one rhs per thread, and
+  // two (the default of the two where the count is even)
+  const int nsite = nrhs % 2 ? 1 : 2;
+  int dflt = best_shape(*this, p, nrhs, shapes, true, true);
+  if (dflt < 0) dflt = 2 * ns + nsite - 1;
+  ctx->choose(
+      key, 2 * ns,
+      [&](int v) {
+        MGM_CHECK(v >= 0 && v < 2 * ns + nsite, MGM_ERR_INVALID_ARG, "fused smoother launch variant out of range");
+        if (v == 2 * ns)
+          nb = launch_site_p<F16, true, true, 1>(*this, U16, C16, r, r_next, nrhs, dpart, site_order(g, p, nrhs), mr);
+        else if (v == 2 * ns + 1)
+          nb = launch_site_p<F16, true, true, 2>(*this, U16, C16, r, r_next, nrhs, dpart, site_order(g, p, nrhs), mr);
+        else
+          nb = launch_march<true, true>(*this, p, r, r_next, nrhs, dpart, shapes[v % ns], mr, v >= ns);
+      },
+      dflt, nsite);
   return nb;
 }
 

@@ -39,7 +39,7 @@ struct FineOp {
   // algorithmic bytes of one application (fields once, spinors in and out)
   double bytes(mgm_prec p, int nrhs) const;
   // One fused minimal-residual smoother step with the previous step's
-  // length (FP16 storage, plane-marching shapes only): with omega = qr / qq
+  // length (FP16 storage, lattices with a plane-marching shape): with omega = qr / qq
   // per rhs (0 where qq is 0) and q = D r (not stored), writes
   // r_next = r - omega q, updates x += omega r in place and writes the block
   // partials of q^H r and |q|^2 to dpart; returns their block count.
@@ -47,6 +47,8 @@ struct FineOp {
   int64_t apply_step(mgm_prec p, const void* r, void* r_next, void* x, const double2* qr, const double* qq,
                      int nrhs, double2* dpart) const;
   double step_bytes(mgm_prec p, int nrhs) const;
+  // estimated microseconds of one FP16 smoother step in its default form
+  double step_us(int nrhs) const;
 };
 
 }  // namespace mgm

@@ -99,21 +99,40 @@ static bool smooth_f16(Hier& H, int l, mgm_prec p, const SolveCfg& cfg) {
 }
 
 // Column groups of the FP16 smoother: with more than 8 rhs and the fused
-// step, its vectors are stored group-major ([nrhs / gs][dof][site][gs], gs
-// = 8 when 8 divides nrhs, else 4 when 4 does) and smoothed one group at a
-// time, so that a block of the step kernel holds all rhs of a site's run and
-// reads whole 128-byte lines (8 FP16 rhs of a dof are 32 bytes; with 16 rhs
+// step, its vectors may be stored group-major ([nrhs / gs][dof][site][gs], gs
+// = 8 or 4 where it divides nrhs) and smoothed one group at a
+// time, so that a block of the marching step kernel holds all rhs of a site's
+// run and reads whole lines (8 FP16 rhs of a dof are 32 bytes; with 16 rhs
 // stored together each block read half of every line, and 20 rhs have no
-// marching shape with more than 4 rhs per block).  Returns the group size
-// (nrhs: no groups).
+// marching shape with more than 4 rhs per block).  A group costs its own
+// launches (a step and the sum of its dots, about 8 us of gaps and small
+// kernels): the split with the smallest estimated time is taken, which is
+// groups on 32^3 x 64 (20 rhs: 5 steps of 0.68 ms against 4.5 ms) and none on
+// 16^4 (12 rhs: 0.10 ms against 3 of 0.035 ms).  The estimates are those of the
+// untuned forms: while the autotuner is on, groups are formed wherever they
+// can be, as it then measures the marching shapes of each.  Returns the group
+// size (nrhs: no groups).
 static bool smooth_fusable(Hier& H, int nrhs, const SolveCfg& cfg) {
   return cfg.smooth >= 2 && H.ws16[0].qr2 != nullptr && H.fine->step_fusable(MGM_PREC_F16, nrhs);
 }
 static int smooth_group(Hier& H, int nrhs, const SolveCfg& cfg) {
   if (nrhs <= 8) return nrhs;
-  for (int gs : {8, 4})
-    if (nrhs % gs == 0 && smooth_fusable(H, gs, cfg)) return gs;
-  return nrhs;
+  if (H.ctx->tune.enabled) {
+    for (int gs : {8, 4})
+      if (nrhs % gs == 0 && smooth_fusable(H, gs, cfg)) return gs;
+    return nrhs;
+  }
+  int best = nrhs;
+  double t = smooth_fusable(H, nrhs, cfg) ? H.fine->step_us(nrhs) + 8.0 : 1e30;
+  for (int gs : {8, 4}) {
+    if (nrhs % gs != 0 || !smooth_fusable(H, gs, cfg)) continue;
+    const double tg = (nrhs / gs) * (H.fine->step_us(gs) + 8.0);
+    if (tg < t) {
+      t = tg;
+      best = gs;
+    }
+  }
+  return best;
 }
 
 // Smoothing e = S r on level l.  On the fine level of the mixed V-cycle the
