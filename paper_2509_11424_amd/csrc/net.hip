@@ -4,9 +4,7 @@
 // Adam, and the training-pair generation from multigrid solves.
 //
 // Layout: channel-major like the fine spinors, element
-// ((channel * 3 + colour) * V + site) * nrhs + rhs, FP32 complex.  A thread
-// handles one (site, rhs) and all output channels of a layer; the weights are
-// uniform across the wave and come through the scalar cache.
+// ((channel * 3 + colour) * V + site) * nrhs + rhs, FP32 complex.
 #include "net.h"
 
 #include <chrono>
@@ -16,55 +14,10 @@
 namespace mgm {
 
 // ------------------------------------------------------------ transports
-
-// (T_p in_b)(s) for the three colours of channel b.  p = 0 identity,
-// 1 + mu: U_mu(s) in(s + mu); 5 + mu: U_mu(s - mu)^H in(s - mu); the hop
-// across the time boundary carries the antiperiodic sign.
-__device__ __forceinline__ void ptc_transport(const float2* __restrict__ in, const float2* __restrict__ U,
-                                              const Geom& g, int64_t s, const int c[4], int p, int b,
-                                              int nrhs, int r, cx<float> t[3]) {
-  const int64_t V = g.V;
-  if (p == 0) {
-#pragma unroll
-    for (int cc = 0; cc < 3; cc++) {
-      float2 v = in[((int64_t)(b * 3 + cc) * V + s) * nrhs + r];
-      t[cc] = {v.x, v.y};
-    }
-    return;
-  }
-  const int mu = (p - 1) & 3;
-  const bool fwd = p <= 4;
-  const int cm = c[mu];
-  const int ex = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
-  const int64_t sd = mu == 0 ? 1 : mu == 1 ? (int64_t)g.X : mu == 2 ? (int64_t)g.X * g.Y
-                                                                     : (int64_t)g.X * g.Y * g.Z;
-  const bool wrap = fwd ? (cm == ex - 1) : (cm == 0);
-  const int64_t span = (int64_t)(ex - 1) * sd;
-  const int64_t sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
-  const float ph = (mu == 3 && wrap && g.antiperiodic) ? -1.f : 1.f;
-  cx<float> v[3];
-#pragma unroll
-  for (int cc = 0; cc < 3; cc++) {
-    float2 w = in[((int64_t)(b * 3 + cc) * V + sn) * nrhs + r];
-    v[cc] = {ph * w.x, ph * w.y};
-  }
-  const float2* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
-#pragma unroll
-  for (int a = 0; a < 3; a++) {
-    cx<float> acc = {0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 3; k++) {
-      if (fwd) {
-        float2 u = Ub[(int64_t)(3 * a + k) * V];
-        fma_(acc, cx<float>{u.x, u.y}, v[k]);
-      } else {
-        float2 u = Ub[(int64_t)(3 * k + a) * V];  // (U^H)_{ak} = conj(U_{ka})
-        fmac_(acc, cx<float>{u.x, u.y}, v[k]);
-      }
-    }
-    t[a] = acc;
-  }
-}
+//
+// T_p in_b at site s: p = 0 identity, 1 + mu: U_mu(s) in(s + mu); 5 + mu:
+// U_mu(s - mu)^H in(s - mu); the hop across the time boundary carries the
+// antiperiodic sign.
 
 __device__ __forceinline__ void site_coords(const Geom& g, int64_t s, int c[4]) {
   int64_t q = s;
@@ -76,98 +29,335 @@ __device__ __forceinline__ void site_coords(const Geom& g, int64_t s, int c[4]) 
   c[3] = (int)(q / g.Z);
 }
 
-// out = sum_p W_p T_p in ; W [9][CO][ci]
-template <int CO>
+// ------------------------------------------------------- matrix-core forms
+//
+// The channel mixes run on the FP32 matrix cores.  v_mfma_f32_4x4x1_16b computes
+// D[i][n] = A[i] B[n] + D[i][n] for sixteen independent 4 x 4 blocks with one fused
+// multiply-add per entry (checked on the device against fmaf, subnormals and
+// NaN included), so a chain of them gives bit for bit the sums of the same chain of
+// scalar FMAs, at twice their rate.  Lane l holds A row l % 4 and B column
+// l % 4 of block l / 4, and the four rows of its own column of D.
+typedef float f4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4_t mfma4(float a, float b, f4_t c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+
+// out = sum_p W_p T_p in ; W [9][co][ci].  A lane is one element (site, rhs): it
+// forms the transport of its own element (the links of a path loaded once for
+// all input channels) and supplies it as the B column; the weights of output
+// channels a0 + 4 g + l % 4 are the A rows, from an LDS copy in that order.  A
+// workgroup computes the 4 NG output channels from a0 = 4 NG blockIdx.y.
+// Bound by the lines of the nine neighbour reads (all miss L1) and the matrix
+// cores: layers 4-16-16-16-4 on 16^3 x 32 at 4 rhs 1.17 ms (74 TFLOP/s), 3.19 ms
+// with scalar FMAs and the links re-read per input channel.  Twelve loads in
+// flight per wave; prefetching the next twelve spills or halves the occupancy
+// (1.71 ms), and so does one colour per wave (2.2 ms).
+template <int NG>
 __global__ __launch_bounds__(256) void k_ptc_layer(float2* __restrict__ out, const float2* __restrict__ in,
                                                    const float2* __restrict__ U, const float2* __restrict__ W,
-                                                   Geom g, int ci, int nrhs) {
+                                                   Geom g, int co, int ci, int nrhs) {
+  extern __shared__ __align__(16) float2 sW[];  // [path][input channel][l % 4][g]
+  const int a0 = 4 * NG * (int)blockIdx.y;
+  for (int i = threadIdx.x; i < kNetPaths * ci * 4 * NG; i += 256) {
+    const int gg = i % NG, l4 = (i / NG) % 4, pb = i / (4 * NG), p = pb / ci, b = pb - p * ci;
+    sW[i] = W[(p * co + a0 + 4 * gg + l4) * ci + b];
+  }
+  __syncthreads();
   const int64_t V = g.V, N = V * nrhs;
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= N) return;
+  const int64_t e = xcd_block(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  // every lane of a wave supplies weight rows: lanes past the end work on the
+  // last element and store nothing
+  const int64_t tid = e < N ? e : N - 1;
   const int64_t s = tid / nrhs;
   const int r = (int)(tid - s * nrhs);
   int c[4];
   site_coords(g, s, c);
-  cx<float> acc[CO][3];
+  f4_t ar[3][NG], ai[3][NG];
 #pragma unroll
-  for (int a = 0; a < CO; a++)
+  for (int cc = 0; cc < 3; cc++)
 #pragma unroll
-    for (int cc = 0; cc < 3; cc++) acc[a][cc] = {0.f, 0.f};
+    for (int q = 0; q < NG; q++) ar[cc][q] = ai[cc][q] = (f4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
   for (int p = 0; p < kNetPaths; p++) {
-    const float2* Wp = W + (int64_t)p * CO * ci;
+    int64_t sn = s;
+    const bool fwd = p <= 4;
+    float ph = 1.f;
+    cx<float> u[3][3];  // the transport matrix
+    if (p > 0) {
+      const int mu = (p - 1) & 3;
+      const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
+      const int ex = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
+      const int64_t sd = mu == 0 ? 1 : mu == 1 ? (int64_t)g.X : mu == 2 ? (int64_t)g.X * g.Y : (int64_t)g.X * g.Y * g.Z;
+      const bool wrap = fwd ? (cm == ex - 1) : (cm == 0);
+      const int64_t span = (int64_t)(ex - 1) * sd;
+      sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
+      ph = (mu == 3 && wrap && g.antiperiodic) ? -1.f : 1.f;
+      const float2* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
+#pragma unroll
+      for (int cc = 0; cc < 3; cc++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+          const float2 w = Ub[(int64_t)(fwd ? 3 * cc + k : 3 * k + cc) * V];
+          u[cc][k] = {w.x, fwd ? w.y : -w.y};  // (U^H)_{ak} = conj(U_{ka})
+        }
+    }
+    const float2* src = in + sn * nrhs + r;
+    const float2* wp = sW + (p * ci * 4 + (threadIdx.x & 3)) * NG;
+    // four input channels at a time (c_in is a multiple of 4): twelve loads in
+    // flight
 #pragma unroll 1
-    for (int b = 0; b < ci; b++) {
-      cx<float> t[3];
-      ptc_transport(in, U, g, s, c, p, b, nrhs, r, t);
+    for (int b0 = 0; b0 < ci; b0 += 4) {
+      float2 raw[4][3];
 #pragma unroll
-      for (int a = 0; a < CO; a++) {
-        const float2 wv = Wp[a * ci + b];
-        const cx<float> w = {wv.x, wv.y};
+      for (int j = 0; j < 4; j++)
 #pragma unroll
-        for (int cc = 0; cc < 3; cc++) fma_(acc[a][cc], w, t[cc]);
+        for (int k = 0; k < 3; k++) raw[j][k] = src[(int64_t)((b0 + j) * 3 + k) * N];
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        cx<float> t[3];
+        if (p == 0) {
+#pragma unroll
+          for (int cc = 0; cc < 3; cc++) t[cc] = {raw[j][cc].x, raw[j][cc].y};
+        } else {
+          cx<float> v[3];
+#pragma unroll
+          for (int k = 0; k < 3; k++) v[k] = {ph * raw[j][k].x, ph * raw[j][k].y};
+#pragma unroll
+          for (int cc = 0; cc < 3; cc++) {
+            t[cc] = {0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 3; k++) fma_(t[cc], u[cc][k], v[k]);
+          }
+        }
+        float2 w[NG];
+#pragma unroll
+        for (int q = 0; q < NG; q++) w[q] = wp[(b0 + j) * 4 * NG + q];
+        // acc.re += w.re t.re - w.im t.im, acc.im += w.re t.im + w.im t.re, each
+        // as two chained products in this order
+#pragma unroll
+        for (int cc = 0; cc < 3; cc++)
+#pragma unroll
+          for (int q = 0; q < NG; q++) {
+            ar[cc][q] = mfma4(w[q].x, t[cc].re, ar[cc][q]);
+            ai[cc][q] = mfma4(w[q].x, t[cc].im, ai[cc][q]);
+          }
+#pragma unroll
+        for (int cc = 0; cc < 3; cc++)
+#pragma unroll
+          for (int q = 0; q < NG; q++) {
+            ar[cc][q] = mfma4(w[q].y, -t[cc].im, ar[cc][q]);
+            ai[cc][q] = mfma4(w[q].y, t[cc].re, ai[cc][q]);
+          }
       }
     }
   }
+  if (e >= N) return;
 #pragma unroll
-  for (int a = 0; a < CO; a++)
+  for (int q = 0; q < NG; q++)
 #pragma unroll
-    for (int cc = 0; cc < 3; cc++)
-      out[((int64_t)(a * 3 + cc) * V + s) * nrhs + r] = make_float2(acc[a][cc].re, acc[a][cc].im);
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int cc = 0; cc < 3; cc++)
+        out[(int64_t)((a0 + 4 * q + i) * 3 + cc) * N + tid] = make_float2(ar[cc][q][i], ai[cc][q][i]);
 }
 
 // Weight gradient of one layer: part[blk][p][a][b] = sum over the block's
 // elements of gout_a conj(T_p in_b), summed over colours (grid nblk x 9).
-constexpr int kWE = 32;  // elements staged per tile
+// Elements are summed in tiles of kWE = 32 consecutive ones: within a tile in
+// FP32 (element by element, colour by colour, each product pair
+// fma(g.re, x.re, g.im x.im) added to the sum), over tiles in FP64.
+// A block of four waves stages the gradients and transports of NTB tiles, ES
+// elements of each at a time, in LDS; a wave owns output channels 4 ag .. + 3 and
+// one set of NTL tiles, and an MFMA covers 4 x 4 pairs of (NTL tiles) x (input
+// channel groups).  The loads of a step are in flight during the products of
+// the one before.  A 16 x 16 layer of 32768 elements takes 81 us (111 without the
+// loads ahead; 566 with two LDS reads for every pair and product); bound by the
+// additions of the product pairs, as many vector as matrix cycles.
+constexpr int kWE = 32;  // elements per tile
+template <int CO, int CI>
+struct WgradShape {
+  static constexpr int NA = CO / 4, NB = CI / 4;
+  static constexpr int NBp = NB <= 2 ? NB : 4;             // input groups per MFMA
+  static constexpr int NTL = 16 / NBp;                     // tiles per MFMA
+  static constexpr int WPS = NA <= 2 ? NA : 4;             // waves per tile set
+  static constexpr int SETS = 4 / WPS, NTB = NTL * SETS;   // tiles per block
+  static constexpr int per = (CO + CI) * 3 * NTB * 8;      // LDS bytes per staged element
+  static constexpr int ES = per * 18 <= 57344 ? 16 : per * 10 <= 57344 ? 8 : per * 6 <= 57344 ? 4 : 2;
+  static constexpr int ESP = ES + 2;  // rows 36 words (20, 12, 8) apart
+  static constexpr size_t lds = (size_t)(CO + CI) * 3 * NTB * ESP * 8;
+};
+template <int CO, int CI>
 __global__ __launch_bounds__(256) void k_ptc_wgrad(const float2* __restrict__ gout, const float2* __restrict__ in,
-                                                   const float2* __restrict__ U, Geom g, int co, int ci, int nrhs,
+                                                   const float2* __restrict__ U, Geom g, int nrhs,
                                                    int64_t per_block, double2* __restrict__ part) {
+  using S = WgradShape<CO, CI>;
+  constexpr int ES = S::ES, ESP = S::ESP, NTB = S::NTB, NEL = NTB * ES;
+  extern __shared__ __align__(16) float2 smem[];
+  float2* sG = smem;                           // [CO * 3][NTB][ESP]
+  float2* sX = smem + CO * 3 * NTB * ESP;      // [CI * 3][NTB][ESP]
   const int p = blockIdx.y;
   const int64_t V = g.V, N = V * nrhs;
   const int64_t e0 = (int64_t)blockIdx.x * per_block;
   const int64_t e1 = e0 + per_block < N ? e0 + per_block : N;
-  __shared__ float2 sG[kNetMaxWidth * 3][kWE];
-  __shared__ float2 sX[kNetMaxWidth * 3][kWE];
-  const int t = threadIdx.x;
-  const bool pair = t < co * ci;
-  const int a = pair ? t / ci : 0, b = pair ? t % ci : 0;
-  double ar = 0, ai = 0;
-  for (int64_t eb = e0; eb < e1; eb += kWE) {
-    for (int j = t; j < co * 3 * kWE; j += blockDim.x) {
-      const int ac = j / kWE, e = j % kWE;
-      const int64_t el = eb + e;
-      sG[ac][e] = el < e1 ? gout[(int64_t)ac * N + el] : make_float2(0.f, 0.f);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int ag = wave % S::WPS, set = wave / S::WPS;  // output group, tile set of this wave
+  const int l4 = lane & 3, blk = lane >> 2, bg = blk % S::NBp, tl = blk / S::NBp;
+  const bool work = ag < S::NA;  // three output groups: the fourth wave only stages
+  const float2* pg = sG + (((work ? 4 * ag : 0) + l4) * 3 * NTB + set * S::NTL + tl) * ESP;
+  const float2* px = sX + (((bg < S::NB ? 4 * bg : 0) + l4) * 3 * NTB + set * S::NTL + tl) * ESP;
+  const int mu = (p - 1) & 3;
+  const bool fwd = p <= 4;
+  const int ex = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
+  const int64_t sd = mu == 0 ? 1 : mu == 1 ? (int64_t)g.X : mu == 2 ? (int64_t)g.X * g.Y : (int64_t)g.X * g.Y * g.Z;
+  // staging: GI gradient entries and XI elements (a quarter of their input
+  // channels each, sharing the links) per thread
+  constexpr int GI = CO * 3 * NEL / 256, XI = 4 * NEL / 256;
+  float2 gr[GI], vr[XI][S::NB][3], ur[XI][9];
+  float ph[XI];
+  auto elem = [&](int64_t k, int q) {  // element of staged slot q in step k
+    return e0 + (k / (kWE / ES)) * (NTB * kWE) + (q / ES) * kWE + (k % (kWE / ES)) * ES + q % ES;
+  };
+  auto load = [&](int64_t k) {
+#pragma unroll
+    for (int i = 0; i < GI; i++) {
+      const int j = t + 256 * i, row = j / NEL;
+      const int64_t el = elem(k, j % NEL);
+      gr[i] = el < e1 ? gout[(int64_t)row * N + el] : make_float2(0.f, 0.f);
     }
-    for (int j = t; j < ci * kWE; j += blockDim.x) {
-      const int bb = j / kWE, e = j % kWE;
-      const int64_t el = eb + e;
-      cx<float> tt[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
-      if (el < e1) {
+#pragma unroll
+    for (int i = 0; i < XI; i++) {
+      const int j = t + 256 * i, b0 = j / NEL;
+      const int64_t el = elem(k, j % NEL);
+      ph[i] = 1.f;
+      if (el >= e1) {
+#pragma unroll
+        for (int b = 0; b < S::NB; b++)
+#pragma unroll
+          for (int cc = 0; cc < 3; cc++) vr[i][b][cc] = make_float2(0.f, 0.f);
+        continue;  // the links of an earlier step times zero
+      }
+      const float2* src = in + el;
+      if (p > 0) {
         const int64_t s = el / nrhs;
         const int r = (int)(el - s * nrhs);
         int c[4];
         site_coords(g, s, c);
-        ptc_transport(in, U, g, s, c, p, bb, nrhs, r, tt);
+        const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
+        const bool wrap = fwd ? (cm == ex - 1) : (cm == 0);
+        const int64_t span = (int64_t)(ex - 1) * sd;
+        const int64_t sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
+        if (mu == 3 && wrap && g.antiperiodic) ph[i] = -1.f;
+        const float2* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
+#pragma unroll
+        for (int k9 = 0; k9 < 9; k9++) ur[i][k9] = Ub[(int64_t)k9 * V];
+        src = in + sn * nrhs + r;
       }
 #pragma unroll
-      for (int cc = 0; cc < 3; cc++) sX[bb * 3 + cc][e] = make_float2(tt[cc].re, tt[cc].im);
+      for (int b = 0; b < S::NB; b++)
+#pragma unroll
+        for (int cc = 0; cc < 3; cc++) vr[i][b][cc] = src[(int64_t)((b0 + 4 * b) * 3 + cc) * N];
     }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int i = 0; i < GI; i++) {
+      const int j = t + 256 * i, row = j / NEL, q = j % NEL;
+      sG[(row * NTB + q / ES) * ESP + q % ES] = gr[i];
+    }
+#pragma unroll
+    for (int i = 0; i < XI; i++) {
+      const int j = t + 256 * i, b0 = j / NEL, q = j % NEL;
+      float2* dst = sX + (q / ES) * ESP + q % ES;
+#pragma unroll
+      for (int b = 0; b < S::NB; b++) {
+        cx<float> v[3];
+#pragma unroll
+        for (int k = 0; k < 3; k++) v[k] = {ph[i] * vr[i][b][k].x, ph[i] * vr[i][b][k].y};
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+          cx<float> x = {0.f, 0.f};
+          if (p == 0) {
+            x = v[a];
+          } else {
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+              const float2 w = ur[i][fwd ? 3 * a + k : 3 * k + a];
+              fma_(x, cx<float>{w.x, fwd ? w.y : -w.y}, v[k]);  // (U^H)_{ak} = conj(U_{ka})
+            }
+          }
+          dst[((b0 + 4 * b) * 3 + a) * NTB * ESP] = make_float2(x.re, x.im);
+        }
+      }
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < XI; i++)
+#pragma unroll
+    for (int k = 0; k < 9; k++) ur[i][k] = make_float2(0.f, 0.f);
+  double dr[4] = {0, 0, 0, 0}, di[4] = {0, 0, 0, 0};
+  f4_t fr = {0.f, 0.f, 0.f, 0.f}, fi = {0.f, 0.f, 0.f, 0.f};
+  const f4_t zero = {0.f, 0.f, 0.f, 0.f};
+  const int64_t nstep = (e1 - e0 + NTB * kWE - 1) / (NTB * kWE) * (kWE / ES);
+  load(0);
+#pragma unroll 1
+  for (int64_t k = 0; k < nstep; k++) {
+    __syncthreads();  // the previous step's tiles consumed
+    store();
     __syncthreads();
-    if (pair) {
-      float fr = 0.f, fi = 0.f;
-      for (int e = 0; e < kWE; e++)
+    if (k + 1 < nstep) load(k + 1);  // in flight during the products
+    if (!work) continue;
+#pragma unroll 2
+    for (int ee = 0; ee < ES; ee += 2) {
+      float4 gv[3], xv[3];  // two elements
+#pragma unroll
+      for (int cc = 0; cc < 3; cc++) {
+        gv[cc] = *reinterpret_cast<const float4*>(pg + cc * NTB * ESP + ee);
+        xv[cc] = *reinterpret_cast<const float4*>(px + cc * NTB * ESP + ee);
+      }
+#pragma unroll
+      for (int o = 0; o < 2; o++)
 #pragma unroll
         for (int cc = 0; cc < 3; cc++) {
-          const float2 gv = sG[a * 3 + cc][e], xv = sX[b * 3 + cc][e];
-          fr += gv.x * xv.x + gv.y * xv.y;  // g conj(x)
-          fi += gv.y * xv.x - gv.x * xv.y;
+          const float gx = o ? gv[cc].z : gv[cc].x, gy = o ? gv[cc].w : gv[cc].y;
+          const float xx = o ? xv[cc].z : xv[cc].x, xy = o ? xv[cc].w : xv[cc].y;
+          // g conj(x)
+          fr += mfma4(gx, xx, mfma4(gy, xy, zero));
+          fi += mfma4(gy, xx, mfma4(-gx, xy, zero));
         }
-      ar += fr;
-      ai += fi;
     }
-    __syncthreads();
+    if ((k + 1) % (kWE / ES) == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        dr[i] += (double)fr[i];
+        di[i] += (double)fi[i];
+      }
+      fr = fi = zero;
+    }
   }
-  if (pair) part[((int64_t)blockIdx.x * kNetPaths + p) * co * ci + t] = make_double2(ar, ai);
+  // tiles of the wave by a fixed shuffle tree, then the sets in order
+#pragma unroll
+  for (int off = 4 * S::NBp; off < 64; off <<= 1)
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      dr[i] += __shfl_xor(dr[i], off, 64);
+      di[i] += __shfl_xor(di[i], off, 64);
+    }
+  __syncthreads();
+  double2* sD = reinterpret_cast<double2*>(smem);  // [SETS][CO][CI]
+  if (work && tl == 0 && bg < S::NB) {
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      sD[(set * CO + 4 * ag + i) * CI + 4 * bg + l4] = make_double2(dr[i], di[i]);
+  }
+  __syncthreads();
+  for (int k = t; k < CO * CI; k += 256) {
+    double2 a = sD[k];
+    for (int q = 1; q < S::SETS; q++) {
+      a.x += sD[q * CO * CI + k].x;
+      a.y += sD[q * CO * CI + k].y;
+    }
+    part[((int64_t)blockIdx.x * kNetPaths + p) * CO * CI + k] = a;
+  }
 }
 
 // out[i] = sum_blk part[blk][i], one 64-lane wave per entry, fixed order
@@ -250,21 +440,59 @@ __global__ void k_ptc_loss(const double* n2, const double* e2, int nrhs, double*
 static void launch_layer(Context* c, const FineOp* op, float2* out, const float2* in, const float2* W, int co,
                          int ci, int nrhs) {
   const int64_t N = op->g.V * nrhs;
-  const dim3 nb(nblocks_for(N, 256)), tb(256);
   ProfScope ps(c, KC_NET, (double)op->g.V * (36.0 * 8 + (co + 9.0 * ci) * 3 * 8 * nrhs));
-  switch (co) {
-    case 4: hipLaunchKernelGGL(k_ptc_layer<4>, nb, tb, 0, c->stream, out, in, op->U32, W, op->g, ci, nrhs); break;
-    case 8: hipLaunchKernelGGL(k_ptc_layer<8>, nb, tb, 0, c->stream, out, in, op->U32, W, op->g, ci, nrhs); break;
-    case 12: hipLaunchKernelGGL(k_ptc_layer<12>, nb, tb, 0, c->stream, out, in, op->U32, W, op->g, ci, nrhs); break;
-    case 16: hipLaunchKernelGGL(k_ptc_layer<16>, nb, tb, 0, c->stream, out, in, op->U32, W, op->g, ci, nrhs); break;
+  const unsigned nb = nblocks_for(N, 256);
+  // One workgroup computes all output channels, unless the lattice leaves CUs
+  // idle: then the channels are split over workgroups (each repeats the
+  // transports) as long as every CU gets at most one.  Network 4-16-16-16-4: 4096
+  // elements 170 us whole, 141 in two and 129 in four parts; 32768 184, 154,
+  // 160; 262144 571, 731, 1172.
+  int ng = co / 4;
+  if (ng == 3 && 3u * nb <= (unsigned)c->cu_count) ng = 1;
+  while (ng % 2 == 0 && (unsigned)(co / (4 * ng)) * 2u * nb <= (unsigned)c->cu_count) ng /= 2;
+  const dim3 grid(nb, co / (4 * ng)), tb(256);
+  const size_t lds = (size_t)kNetPaths * ci * 4 * ng * sizeof(float2);
+  switch (ng) {
+    case 1: hipLaunchKernelGGL(k_ptc_layer<1>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
+    case 2: hipLaunchKernelGGL(k_ptc_layer<2>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
+    case 3: hipLaunchKernelGGL(k_ptc_layer<3>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
+    case 4: hipLaunchKernelGGL(k_ptc_layer<4>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
     default: throw Error(MGM_ERR_INVALID_ARG, "network widths must be 4, 8, 12 or 16");
   }
   MGM_LAUNCH_CHECK();
 }
 
+// blocks per path of the weight gradient: 256 elements each fill the chip
+// from 32768 elements on (nine paths)
 static int64_t wgrad_blocks(int64_t N) {
-  int64_t nb = (N + 2047) / 2048;
+  int64_t nb = (N + 255) / 256;
   return nb < 1 ? 1 : (nb > 512 ? 512 : nb);
+}
+
+template <int CO, int CI>
+static int64_t launch_wgrad_p(Context* c, const FineOp* op, const float2* gout, const float2* in, int nrhs,
+                              double2* part) {
+  using S = WgradShape<CO, CI>;
+  const int64_t N = op->g.V * nrhs, nblk = wgrad_blocks(N), chunk = (int64_t)S::NTB * kWE;
+  const int64_t per = ((N + nblk - 1) / nblk + chunk - 1) / chunk * chunk, nb = (N + per - 1) / per;
+  const size_t lds = std::max(S::lds, (size_t)S::SETS * CO * CI * sizeof(double2));
+  static_assert(S::lds <= 65536, "staged tiles exceed the default LDS of a workgroup");
+  hipLaunchKernelGGL((k_ptc_wgrad<CO, CI>), dim3((unsigned)nb, kNetPaths), dim3(256), lds, c->stream, gout, in,
+                     op->U32, op->g, nrhs, per, part);
+  MGM_LAUNCH_CHECK();
+  return nb;
+}
+// returns the number of block partials written to part[blk][path][co][ci]
+static int64_t launch_wgrad(Context* c, const FineOp* op, const float2* gout, const float2* in, int co, int ci,
+                            int nrhs, double2* part) {
+#define MGM_WGRAD(A, B) \
+  if (co == A && ci == B) return launch_wgrad_p<A, B>(c, op, gout, in, nrhs, part);
+  MGM_WGRAD(4, 4) MGM_WGRAD(4, 8) MGM_WGRAD(4, 12) MGM_WGRAD(4, 16)
+  MGM_WGRAD(8, 4) MGM_WGRAD(8, 8) MGM_WGRAD(8, 12) MGM_WGRAD(8, 16)
+  MGM_WGRAD(12, 4) MGM_WGRAD(12, 8) MGM_WGRAD(12, 12) MGM_WGRAD(12, 16)
+  MGM_WGRAD(16, 4) MGM_WGRAD(16, 8) MGM_WGRAD(16, 12) MGM_WGRAD(16, 16)
+#undef MGM_WGRAD
+  throw Error(MGM_ERR_INVALID_ARG, "network widths must be 4, 8, 12 or 16");
 }
 
 void Net::layout(Arena& a) {
@@ -340,7 +568,7 @@ double Net::loss_grad(const float2* r, const float2* e, int nrhs) {
   MGM_CHECK(desc.train_nrhs > 0 && nrhs >= 1 && nrhs <= desc.train_nrhs, MGM_ERR_INVALID_ARG,
             "nrhs exceeds the network's train_nrhs");
   Context* c = ctx;
-  const int64_t V = op->g.V, N = V * nrhs;
+  const int64_t V = op->g.V;
   auto in_of = [&](int l) { return l == 0 ? r : (const float2*)act[l]; };
   for (int l = 0; l < L; l++) launch_layer(c, op, act[l + 1], in_of(l), w32 + woff[l], width[l + 1], width[l], nrhs);
   // output gradient 2 (N(r) - e) / (n |e|^2), in place of the output
@@ -358,13 +586,9 @@ double Net::loss_grad(const float2* r, const float2* e, int nrhs) {
   MGM_LAUNCH_CHECK();
   b_scale_rhs(c, od, scale);
   const float2* G = act[L];
-  const int64_t nblk = wgrad_blocks(N);
-  const int64_t per = ((N + nblk - 1) / nblk + kWE - 1) / kWE * kWE;
   for (int l = L - 1; l >= 0; l--) {
     const int co = width[l + 1], ci = width[l];
-    const int64_t nb = (N + per - 1) / per;
-    hipLaunchKernelGGL(k_ptc_wgrad, dim3((unsigned)nb, kNetPaths), dim3(256), 0, c->stream, G, in_of(l), op->U32,
-                       op->g, co, ci, nrhs, per, wpart);
+    const int64_t nb = launch_wgrad(c, op, G, in_of(l), co, ci, nrhs, wpart);
     const int cnt = kNetPaths * co * ci;
     hipLaunchKernelGGL(k_ptc_wsum, dim3(cnt), dim3(64), 0, c->stream, wpart, nb, cnt, g64 + woff[l]);
     MGM_LAUNCH_CHECK();

@@ -105,6 +105,39 @@ def test_loss_and_weight_gradients_match_oracle(lat):
         assert rel(g, o) < 1e-4
 
 
+@pytest.mark.parametrize("nrhs", [1, 3, 40])
+@pytest.mark.parametrize("co", [4, 8, 12, 16])
+@pytest.mark.parametrize("ci", [4, 8, 12, 16])
+def test_layer_shapes_on_a_ragged_lattice(ci, co, nrhs):
+    """Every pair of layer widths (a template of the weight gradient each) at
+    element counts that fill no whole wave, tile or block: outputs within 2e-6
+    and gradients within 1e-4 of the oracle, as above."""
+    import paper_2509_11424_amd as m
+    from oracle.ptc import PTC, random_weights
+    dims = (3, 5, 2, 3)
+    U = gauge_field(dims, 0.6, 64)
+    op = m.Operator(m.Context(0), U, 0.05, 1.0)
+    widths = (4, ci, co, 4)
+    W = random_weights(widths, 65)
+    net = m.Net(op, widths=widths, max_nrhs=nrhs, train_nrhs=nrhs)
+    net.set_weights(W)
+    r = _to_f32_gpu(_rand(op.V, nrhs, 5))
+    e = _to_f32_gpu(_rand(op.V, nrhs, 6))
+    W32 = [w.astype(np.complex64).astype(np.complex128) for w in W]
+    ptc = PTC(U)
+
+    def field(t):
+        x = from_gpu(t)
+        return x.reshape(nrhs, dims[3], dims[2], dims[1], dims[0], 4, 3)
+
+    assert rel(from_gpu(net.apply(r)), ptc.apply(W32, field(r)).reshape(nrhs, op.V, 12)) < 2e-6
+    loss, grads = net.loss_grad(r, e)
+    ol, og = ptc.loss_grad(W32, field(r), field(e))
+    assert abs(loss - ol) < 1e-5 * ol
+    for g, o in zip(grads, og):
+        assert rel(g, o) < 1e-4
+
+
 @pytest.fixture(scope="module")
 def trained(lat):
     import paper_2509_11424_amd as m
