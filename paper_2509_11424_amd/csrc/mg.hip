@@ -87,82 +87,50 @@ void mg_agg_map(Context* c, const TGeom& t, int64_t* out) {
 }
 
 // ------------------------------------------------------------ transfers
+//
+// Both transfers are products with the aggregate's (rows x N_tv) block of P and
+// run on the matrix cores: v_mfma 16x16x4 in FP32 or FP64, whose entries are
+// chains of fused multiply-adds like the scalar ones (A[i][k]: lane i + 16 k,
+// B[k][n]: lane n + 16 k; D[i][n]: lane n + 16 q, register j, row 4 q + j in
+// FP32 and 4 j + q in FP64).  An aggregate and chirality is worked on by wpa
+// waves of a 256-thread workgroup: four, or one where the aggregate has too few
+// rows for four.  P streams from memory straight into the A operand, each entry
+// read once per launch and tile of right-hand sides; workgroups go to the XCDs
+// in contiguous ranges, so that aggregates that share lines of the fine
+// vector share an L2.  Aggregates 4^4, 24 test vectors, 20 rhs on 16^3 x 32, start
+// (scalar FMAs on LDS tiles) -> now: restriction FP64 329 -> 264 us, FP32 177 ->
+// 150, FP16 200 -> 51 (277 MB: at the rate of a copy); prolongation FP64 394 -> 269,
+// FP32 203 -> 153, FP16 added 289 -> 160 (530 MB, 104 us at that rate).
 
-// Transfers run one workgroup per (aggregate, chirality, rhs tile): the
-// aggregate's P block (rows x N_tv) is streamed once through LDS in chunks of
-// rows, so every P entry is read from HBM once per launch and reused by all
-// right-hand sides of the tile.  Each thread owns a 4 x 4 register tile of
-// the block's products (four test vectors or rows by four right-hand sides),
-// so one pair of 32-byte LDS reads feeds sixteen complex FMAs.
-constexpr int kTransferRT = 64;     // right-hand sides per workgroup
-constexpr int kTransferTB = 256;    // threads per workgroup
-constexpr int kRestrictLDS = 24576; // bytes of streamed P rows and restricted inputs
-constexpr int kProlongLDS = 24576;  // bytes of streamed (transposed) P rows
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef double d4_t __attribute__((ext_vector_type(4)));
+template <typename R>
+struct Mm;
+template <>
+struct Mm<float> {
+  using V4 = f4_t;
+  __device__ __forceinline__ static V4 mfma(float a, float b, V4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ __forceinline__ static int row(int q, int j) { return 4 * q + j; }
+};
+template <>
+struct Mm<double> {
+  using V4 = d4_t;
+  __device__ __forceinline__ static V4 mfma(double a, double b, V4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  __device__ __forceinline__ static int row(int q, int j) { return 4 * j + q; }
+};
 
-__host__ __device__ inline int round4(int v) { return (v + 3) & ~3; }
-__host__ __device__ inline int sites_bytes(int bvol) { return (bvol * 8 + 15) & ~15; }
-
-// restrict: the rhs tile of width rt splits into T = (Kp/4)(rtp/4) output
-// tiles; G = 256 / T thread groups share the rows of a chunk
-__host__ __device__ inline int restrict_groups(int K, int rt) { return kTransferTB / ((round4(K) / 4) * (round4(rt) / 4)); }
-
-// rows per chunk: the fewest equal chunks that fit the byte budget, rounded
-// up to a multiple of `mult` when that still fits
-inline int balanced_chunk(int rows, int rc_max, int mult) {
-  if (rc_max < 1) rc_max = 1;
-  if (rc_max >= rows) return rows;
-  const int n = (rows + rc_max - 1) / rc_max;
-  int rc = (rows + n - 1) / n;
-  const int up = (rc + mult - 1) / mult * mult;
-  return up <= rc_max ? up : rc;
-}
-
-inline int restrict_chunk_rows(const TGeom& t, int rt, int cbytes) {
-  const int Kp = round4(t.ntv), rtp = round4(rt);
-  return balanced_chunk(t.rows, kRestrictLDS / ((Kp + rtp) * cbytes), restrict_groups(t.ntv, rt));
-}
-inline size_t restrict_lds(const TGeom& t, int rt, int rc, int cbytes) {
-  const size_t chunk = (size_t)rc * (round4(t.ntv) + round4(rt)) * cbytes;
-  const size_t red = (size_t)kTransferTB * 4 * cbytes;
-  return sites_bytes(t.bvol) + (chunk > red ? chunk : red);
-}
-// prolong: TI rows per thread, chunks of about one tile per thread (at
-// most kProlongLDS bytes of P), rows a multiple of TI
-inline int prolong_chunk_rows(const TGeom& t, int rt, int cbytes, int TI) {
-  const int ntr = round4(rt) / 4;
-  const int want = TI * ((kTransferTB + ntr - 1) / ntr);
-  int cap = kProlongLDS / (t.ntv * cbytes);
-  cap = (cap < want ? cap : want) / TI * TI;
-  if (cap < TI) cap = TI;
-  const int rows = (t.rows + TI - 1) / TI * TI;
-  const int rc = balanced_chunk(rows, cap, TI);
-  return (rc + TI - 1) / TI * TI;
-}
-inline size_t prolong_lds(const TGeom& t, int rt, int rc, int cbytes) {
-  return sites_bytes(t.bvol) + ((size_t)t.ntv * round4(rt) + (size_t)rc * t.ntv) * cbytes;
-}
-// rhs per prolongation workgroup: kTransferRT, halved while the coarse
-// values of a full tile would take more than half of the 64 KiB LDS (FP64
-// with more than 32 test vectors, FP32 with more than 64)
-inline int prolong_rt(const TGeom& t, int cbytes) {
-  int rt = kTransferRT;
-  while (rt > 4 && (size_t)t.ntv * rt * cbytes > 32768) rt /= 2;
-  return rt;
-}
-// rhs per restriction workgroup: kTransferRT, halved while the 4 x 4 output
-// tiles of (test vectors) x (rhs) outnumber the workgroup's threads (more
-// than 64 test vectors)
-inline int restrict_rt(const TGeom& t) {
-  int rt = kTransferRT;
-  while (rt > 4 && (round4(t.ntv) / 4) * (rt / 4) > kTransferTB) rt /= 2;
-  return rt;
-}
-
-// fine sites of aggregate a, in local (lexicographic) order, into LDS
-__device__ __forceinline__ void aggregate_sites(const TGeom& t, int64_t a, int64_t* sites) {
+// Entry of the fine vector (one rhs, one chirality) that row = loc * half + j of
+// aggregate a stands for, j Vf + site(loc), into LDS: half * Vf < 2^32, as a
+// level's vectors and operator have to fit the device.
+__device__ __forceinline__ void aggregate_rows(const TGeom& t, int64_t a, uint32_t* tab, int i0, int step) {
   int ca[4];
   coords_of(t.c, a, ca);
-  for (int loc = threadIdx.x; loc < t.bvol; loc += kTransferTB) {
+  for (int row = i0; row < t.rows; row += step) {
+    const int loc = row / t.half, j = row - loc * t.half;
     int rem = loc, f[4];
 #pragma unroll
     for (int m = 0; m < 4; m++) {
@@ -170,262 +138,410 @@ __device__ __forceinline__ void aggregate_sites(const TGeom& t, int64_t a, int64
       rem /= t.b[m];
       f[m] = ca[m] * t.b[m] + l;
     }
-    sites[loc] = index_of(t.f, f);
+    tab[row] = (uint32_t)(j * t.f.V + index_of(t.f, f));
   }
 }
-
-// P rows [row0, row0 + nr) of one (aggregate, chirality) block into LDS as
-// complex R: entry (row ii, vector k) goes to sP[ii * ld + k] (row-major,
-// columns K..ld-1 zeroed) or, transposed, to sP[k * ld + ii].  FP16 blocks
-// with K % 4 == 0 move 16 bytes (4 entries) per lane.
-template <class PM, typename R, bool TRANS>
-__device__ __forceinline__ void stage_p_rows(const typename PM::S* __restrict__ pb, int row0, int nr, int K, int ld,
-                                             cx<R>* sP) {
-  if constexpr (std::is_same<PM, F16>::value) {
-    if ((K & 3) == 0) {
-      const int K4 = K >> 2;
-      const uint4* src = reinterpret_cast<const uint4*>(pb + (int64_t)row0 * K);
-      for (int i = threadIdx.x; i < nr * K4; i += kTransferTB) {
-        const uint4 v = src[i];
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        const int ii = i / K4, k0 = (i - ii * K4) * 4;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          __half2 h;
-          __builtin_memcpy(&h, &w[e], 4);
-          const float2 f = __half22float2(h);
-          if (TRANS)
-            sP[(k0 + e) * ld + ii] = {(R)f.x, (R)f.y};
-          else
-            sP[ii * ld + k0 + e] = {(R)f.x, (R)f.y};  // ld == K here
-        }
-      }
-      return;
-    }
-  }
-  if (TRANS) {
-    for (int i = threadIdx.x; i < nr * K; i += kTransferTB) {
-      const int ii = i / K, k = i - ii * K;
-      const cx<typename PM::R> v = PM::ld(pb, (int64_t)row0 * K + i);
-      sP[k * ld + ii] = {(R)v.re, (R)v.im};
-    }
-  } else {
-    for (int i = threadIdx.x; i < nr * ld; i += kTransferTB) {
-      const int ii = i / ld, k = i - ii * ld;
-      cx<R> v = {0, 0};
-      if (k < K) {
-        const cx<typename PM::R> u = PM::ld(pb, (int64_t)(row0 + ii) * K + k);
-        v = {(R)u.re, (R)u.im};
-      }
-      sP[i] = v;
-    }
-  }
-}
-
-// four consecutive complex entries from 16-byte aligned LDS
-template <typename R>
-__device__ __forceinline__ void lds_ld4(const cx<R>* p, cx<R> (&v)[4]) {
-  if constexpr (std::is_same<R, float>::value) {
-    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
-    v[0] = {a.x, a.y};
-    v[1] = {a.z, a.w};
-    v[2] = {b.x, b.y};
-    v[3] = {b.z, b.w};
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const double2 a = reinterpret_cast<const double2*>(p)[j];
-      v[j] = {a.x, a.y};
-    }
-  }
-}
+__host__ __device__ inline int row_words(int rows) { return (rows + 3) & ~3; }
 
 // y_c[chi k][a][r] = sum_rows conj(P[a][chi][row][k]) x[chi half + j][site(loc)][r]
-// Thread (g, u) accumulates the output tile u = (k/4, r/4) over the rows
-// g, g + G, ... of every chunk; the G partial tiles are then summed in group
-// order through LDS.
-// The input x may be stored in another format PX, scaled per rhs by xs, and
-// in column groups of xgs right-hand sides (xgs = nrhs: plain layout).
-template <class P, class PM, class PX = P>
-__global__ __launch_bounds__(256) void k_restrict(const typename PX::S* __restrict__ x, typename P::S* __restrict__ yc,
-                                                  const typename PM::S* __restrict__ Pm, TGeom t, int nrhs, int rc,
-                                                  int rtile, const double* __restrict__ xs, int xgs) {
+// As real products: the test vectors are the A tiles, MT of them from
+// 16 MT blockIdx.z on, the 2 nr columns (re, im of each rhs side by side) the B
+// tiles, NT of them from rhs 8 NT blockIdx.y on.  Wave w of wpa sums the row
+// quadruples w, w + wpa, ..., four in a chain, the chains then one after the other
+// (a chain of a whole share was up to 1.8 times further from FP64 sums), and
+// the wpa partial tiles are added in order through LDS.
+template <class P, class PM, int MT, int NT>
+__global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restrict__ x, typename P::S* __restrict__ yc,
+                                                  const typename PM::S* __restrict__ Pm, TGeom t, int nrhs, int wpa) {
   using R = typename P::R;
+  using MM = Mm<R>;
+  using V4 = typename MM::V4;
   extern __shared__ __align__(16) char smem[];
-  const int64_t a = blockIdx.x >> 1;
-  const int chi = blockIdx.x & 1;
-  const int r0 = blockIdx.y * rtile;
-  const int rt = nrhs - r0 < rtile ? nrhs - r0 : rtile;
-  const int K = t.ntv, half = t.half, rows = t.rows;
-  const int Kp = round4(K), rtp = round4(rt), ntr = rtp >> 2;
-  const int T = (Kp >> 2) * ntr, G = kTransferTB / T;
-  const int64_t Vc = t.c.V, Vf = t.f.V;
-  const int tid = threadIdx.x;
-  const bool active = tid < G * T;
-  const int g = tid / T, u = tid - g * T;
-  const int kt = u / ntr, rtt = u - kt * ntr;
-  int64_t* sS = reinterpret_cast<int64_t*>(smem);                        // [bvol] fine sites
-  cx<R>* sP = reinterpret_cast<cx<R>*>(smem + sites_bytes(t.bvol));      // [rc][Kp]
-  cx<R>* sX = sP + (size_t)rc * Kp;                                       // [rc][rtp]
-  aggregate_sites(t, a, sS);
+  const int64_t nblk = gridDim.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
+  const int sub = wave / wpa, w = wave - sub * wpa;  // block of P of this wave, its share of the rows
+  const int64_t ac = xcd_block(blockIdx.x, nblk) * (4 / wpa) + sub;
+  const bool live = ac < 2 * t.c.V;
+  const int64_t a = live ? ac >> 1 : 0;
+  const int chi = live ? (int)(ac & 1) : 0;
+  const int K = t.ntv, rows = t.rows;
+  const int64_t Vc = t.c.V;
+  uint32_t* tab = reinterpret_cast<uint32_t*>(smem) + sub * row_words(rows);
+  aggregate_rows(t, a, tab, w * 64 + lane, wpa * 64);
   __syncthreads();
-  cx<R> acc[4][4];
+  V4 tot[MT][NT], acc[MT][NT];
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+  for (int m = 0; m < MT; m++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) acc[i][j] = {0, 0};
+    for (int s = 0; s < NT; s++) tot[m][s] = acc[m][s] = (V4){0, 0, 0, 0};
   const typename PM::S* pb = Pm + ((a * 2 + chi) * rows) * (int64_t)K;
-  for (int row0 = 0; row0 < rows; row0 += rc) {
-    const int nr = rows - row0 < rc ? rows - row0 : rc;
-    stage_p_rows<PM, R, false>(pb, row0, nr, K, Kp, sP);
-    for (int i = tid; i < nr * rtp; i += kTransferTB) {
-      const int ii = i / rtp, r = i - ii * rtp;
-      cx<R> v = {0, 0};
-      if (r < rt) {
-        const int row = row0 + ii, loc = row / half, j = row - loc * half;
-        const cx<typename PX::R> u =
-            PX::ld(x, grouped_index((int64_t)(chi * half + j) * Vf + sS[loc], r0 + r, nrhs, xgs, 2 * half * Vf));
-        v = {(R)u.re, (R)u.im};
-        if (xs) v = (R)xs[r0 + r] * v;
-      }
-      sX[i] = v;
-    }
-    __syncthreads();
-    if (active) {
-      for (int i = g; i < nr; i += G) {
-        cx<R> pv[4], xv[4];
-        lds_ld4(sP + i * Kp + 4 * kt, pv);
-        lds_ld4(sX + i * rtp + 4 * rtt, xv);
+  // This lane's rows of the A tiles and columns of the B tiles.  Loads are
+  // unconditional (the last valid test vector or rhs instead of one beyond:
+  // those rows and columns of the result are not stored), so that they stay in
+  // flight together.
+  int ka[MT];
+  const typename P::S* xb[NT];
 #pragma unroll
-        for (int kk = 0; kk < 4; kk++)
-#pragma unroll
-          for (int rr = 0; rr < 4; rr++) fmac_(acc[kk][rr], pv[kk], xv[rr]);
-      }
-    }
-    __syncthreads();
+  for (int m = 0; m < MT; m++) {
+    const int k = 16 * (MT * (int)blockIdx.z + m) + n;
+    ka[m] = k < K ? k : K - 1;
   }
-  // group reduction, one k row of the tiles at a time: sR[(g T + u) 4 + rr]
-  cx<R>* sR = sP;
+  const int part = n & 1;
 #pragma unroll
-  for (int kk = 0; kk < 4; kk++) {
-    if (active) {
+  for (int s = 0; s < NT; s++) {
+    const int r = 8 * (NT * (int)blockIdx.y + s) + (n >> 1);
+    xb[s] = x + (int64_t)chi * t.half * t.f.V * nrhs + (r < nrhs ? r : nrhs - 1);
+  }
+  const int quads = (rows + 3) >> 2;
+  int nchain = 0;  // steps summed in acc
+#pragma unroll 1
+  for (int u0 = w; u0 < quads; u0 += 2 * wpa) {
+    typename PM::S praw[2][MT];
+    typename P::S xraw[2][NT];
+    bool in[2];
 #pragma unroll
-      for (int rr = 0; rr < 4; rr++) sR[tid * 4 + rr] = acc[kk][rr];
+    for (int h = 0; h < 2; h++) {
+      const int row = 4 * (u0 + h * wpa) + kq;
+      in[h] = row < rows;
+      const int rw = in[h] ? row : 0;
+      const int64_t off = (int64_t)tab[rw] * nrhs;
+#pragma unroll
+      for (int m = 0; m < MT; m++) praw[h][m] = pb[rw * K + ka[m]];
+#pragma unroll
+      for (int s = 0; s < NT; s++) xraw[h][s] = xb[s][off];
     }
-    __syncthreads();
-    for (int o = tid; o < T * 4; o += kTransferTB) {
-      const int uo = o >> 2, rr = o & 3;
-      const int k = 4 * (uo / ntr) + kk, r = 4 * (uo % ntr) + rr;
-      if (k < K && r < rt) {
-        cx<R> s = sR[o];
-        for (int g2 = 1; g2 < G; g2++) s = s + sR[g2 * T * 4 + o];
-        P::st(yc, ((int64_t)(chi * K + k) * Vc + a) * nrhs + r0 + r, s);
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      // conj(P) x: re = Pre xre + Pim xim, im = Pre xim - Pim xre
+      R b1[NT], b2[NT];
+#pragma unroll
+      for (int s = 0; s < NT; s++) {
+        const cx<R> v = P::ld(&xraw[h][s], 0);
+        b1[s] = part ? v.im : v.re;
+        b2[s] = part ? -v.re : v.im;
+        if (!in[h]) b1[s] = b2[s] = 0;
+      }
+#pragma unroll
+      for (int m = 0; m < MT; m++) {
+        const cx<typename PM::R> v = PM::ld(&praw[h][m], 0);
+        const R a1 = in[h] ? (R)v.re : (R)0, a2 = in[h] ? (R)v.im : (R)0;
+#pragma unroll
+        for (int s = 0; s < NT; s++) acc[m][s] = MM::mfma(a1, b1[s], acc[m][s]);
+#pragma unroll
+        for (int s = 0; s < NT; s++) acc[m][s] = MM::mfma(a2, b2[s], acc[m][s]);
       }
     }
+    if (++nchain == 2 || u0 + 2 * wpa >= quads) {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) {
+          tot[m][s] += acc[m][s];
+          acc[m][s] = (V4){0, 0, 0, 0};
+        }
+      nchain = 0;
+    }
+  }
+  if (wpa > 1) {
+    // [w - 1][MT][NT][lane] partial tiles; the first wave adds them in order
+    V4* sT = reinterpret_cast<V4*>(smem + sizeof(uint32_t) * (4 / wpa) * row_words(rows)) +
+             sub * (wpa - 1) * MT * NT * 64;
+    if (w > 0) {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) sT[(((w - 1) * MT + m) * NT + s) * 64 + lane] = tot[m][s];
+    }
     __syncthreads();
+    if (w > 0) return;
+    for (int o = 1; o < wpa; o++)
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) tot[m][s] += sT[(((o - 1) * MT + m) * NT + s) * 64 + lane];
+  }
+  if (!live) return;
+#pragma unroll
+  for (int s = 0; s < NT; s++) {
+    const int r = 8 * (NT * (int)blockIdx.y + s) + (n >> 1);
+    if (r >= nrhs) continue;
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int k = 16 * (MT * (int)blockIdx.z + m) + MM::row(kq, j);
+        if (k < K)
+          reinterpret_cast<R*>(yc)[2 * (((int64_t)(chi * K + k) * Vc + a) * nrhs + r) + part] = tot[m][s][j];
+      }
+  }
+}
+
+// The restriction of FP16 vectors, y_c = xs (P^H x16): products of FP16 operands
+// are exact in FP32, so they run on v_mfma_f32_16x16x16_f16 (FP32 sums) without a
+// conversion, and the scale is applied to the sums.  Lane (n, kq) holds rows
+// 4 kq .. 4 kq + 3 of the sixteen of a step: of test vector and part n (A), of
+// rhs n (B).
+typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ h4_t pick4(const uint32_t (&v)[4], bool hi) {
+  const uint32_t sel = hi ? 0x07060302u : 0x05040100u;  // upper or lower halves of two words
+  const uint2 o = make_uint2(__builtin_amdgcn_perm(v[1], v[0], sel), __builtin_amdgcn_perm(v[3], v[2], sel));
+  return __builtin_bit_cast(h4_t, o);
+}
+template <int MT, int NT>
+__global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__ x, float2* __restrict__ yc,
+                                                    const uint32_t* __restrict__ Pm, TGeom t, int nrhs, int wpa,
+                                                    const double* __restrict__ xs, int xgs) {
+  extern __shared__ __align__(16) char smem[];
+  const int64_t nblk = gridDim.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
+  const int sub = wave / wpa, w = wave - sub * wpa;
+  const int64_t ac = xcd_block(blockIdx.x, nblk) * (4 / wpa) + sub;
+  const bool live = ac < 2 * t.c.V;
+  const int64_t a = live ? ac >> 1 : 0;
+  const int chi = live ? (int)(ac & 1) : 0;
+  const int K = t.ntv, half = t.half, rows = t.rows;
+  const int64_t Vc = t.c.V, Vf = t.f.V;
+  uint32_t* tab = reinterpret_cast<uint32_t*>(smem) + sub * row_words(rows);
+  aggregate_rows(t, a, tab, w * 64 + lane, wpa * 64);
+  __syncthreads();
+  f4_t acc[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; m++)
+#pragma unroll
+    for (int s = 0; s < NT; s++) acc[m][s] = (f4_t){0, 0, 0, 0};
+  const uint32_t* pb = Pm + ((a * 2 + chi) * rows) * (int64_t)K;
+  int ka[MT], rb[NT];
+#pragma unroll
+  for (int m = 0; m < MT; m++) {
+    const int k = 8 * (MT * (int)blockIdx.z + m) + (n >> 1);
+    ka[m] = k < K ? k : K - 1;
+  }
+  const bool im = n & 1;
+  const uint32_t flip = im ? 0x80008000u : 0u;
+  const uint32_t* xb[NT];
+#pragma unroll
+  for (int s = 0; s < NT; s++) {
+    const int r = 16 * (NT * (int)blockIdx.y + s) + n;
+    rb[s] = r < nrhs ? r : nrhs - 1;
+    xb[s] = x + grouped_index(chi * half * Vf, rb[s], nrhs, xgs, 2 * half * Vf);
+  }
+  const int nstep = (rows + 15) >> 4;
+#pragma unroll 1
+  for (int u = w; u < nstep; u += wpa) {
+    const int row0 = 16 * u + 4 * kq;
+    uint32_t pv[MT][4], xv[NT][4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int rw = row0 + e < rows ? row0 + e : rows - 1;
+      const int64_t off = (int64_t)tab[rw] * xgs;
+#pragma unroll
+      for (int m = 0; m < MT; m++) pv[m][e] = pb[rw * K + ka[m]];
+#pragma unroll
+      for (int s = 0; s < NT; s++) xv[s][e] = xb[s][off];
+    }
+    if (16 * u + 16 > rows) {  // last step of a row count not divisible by 16
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        if (row0 + e >= rows) {
+#pragma unroll
+          for (int m = 0; m < MT; m++) pv[m][e] = 0;
+#pragma unroll
+          for (int s = 0; s < NT; s++) xv[s][e] = 0;
+        }
+    }
+    h4_t xr[NT], xi[NT];
+#pragma unroll
+    for (int s = 0; s < NT; s++) {
+      xr[s] = pick4(xv[s], false);
+      xi[s] = pick4(xv[s], true);
+    }
+    // conj(P) x: re = Pre xre + Pim xim, im = -Pim xre + Pre xim
+#pragma unroll
+    for (int m = 0; m < MT; m++) {
+      const uint2 b1 = __builtin_bit_cast(uint2, pick4(pv[m], im));
+      const h4_t a1 = __builtin_bit_cast(h4_t, make_uint2(b1.x ^ flip, b1.y ^ flip)), a2 = pick4(pv[m], !im);
+#pragma unroll
+      for (int s = 0; s < NT; s++) acc[m][s] = __builtin_amdgcn_mfma_f32_16x16x16f16(a1, xr[s], acc[m][s], 0, 0, 0);
+#pragma unroll
+      for (int s = 0; s < NT; s++) acc[m][s] = __builtin_amdgcn_mfma_f32_16x16x16f16(a2, xi[s], acc[m][s], 0, 0, 0);
+    }
+  }
+  if (wpa > 1) {
+    f4_t* sT = reinterpret_cast<f4_t*>(smem + sizeof(uint32_t) * (4 / wpa) * row_words(rows)) +
+               sub * (wpa - 1) * MT * NT * 64;
+    if (w > 0) {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) sT[(((w - 1) * MT + m) * NT + s) * 64 + lane] = acc[m][s];
+    }
+    __syncthreads();
+    if (w > 0) return;
+    for (int o = 1; o < wpa; o++)
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) acc[m][s] += sT[(((o - 1) * MT + m) * NT + s) * 64 + lane];
+  }
+  if (!live) return;
+#pragma unroll
+  for (int s = 0; s < NT; s++) {
+    const int r = 16 * (NT * (int)blockIdx.y + s) + n;
+    if (r >= nrhs) continue;
+    const float sc = (float)xs[r];
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) {
+        const int k = 8 * (MT * (int)blockIdx.z + m) + ((4 * kq + j) >> 1);
+        if (k < K)
+          yc[((int64_t)(chi * K + k) * Vc + a) * nrhs + r] = make_float2(sc * acc[m][s][j], sc * acc[m][s][j + 1]);
+      }
   }
 }
 
 // y = P x_c (mode 0), x - P x_c (mode 1), y + P x_c (mode 2), or
 // xs * x + P x_c (mode 3, x stored as PX, scaled per rhs by xs and in column
 // groups of xgs right-hand sides)
-// P rows of a chunk sit transposed in LDS; thread u = (q, r/4) owns rows
-// q, q + Q, ..., q + (TI-1) Q of the chunk (Q = rc / TI) by four right-hand
-// sides, and loads the destination entries it updates before its products.
-template <class P, class PM, int TI, class PX = P>
+// As real products: rows of P are the A tiles, two tiles of 16 at a time per
+// wave, the 2 nr columns (re, im of each rhs side by side, nr rhs from
+// 8 NT blockIdx.y on) the B tiles, from an LDS copy of the aggregate's coarse
+// values.  VK consecutive test vectors per A load (VK divides N_tv).
+template <class P, class PM, class PX, int NT, int VK>
 __global__ __launch_bounds__(256) void k_prolong(const typename P::S* __restrict__ xc, const typename P::S* __restrict__ x,
                                                  typename P::S* __restrict__ y, const typename PM::S* __restrict__ Pm,
-                                                 TGeom t, int nrhs, int mode, int rc, int rtile,
+                                                 TGeom t, int nrhs, int mode, int wpa,
                                                  const typename PX::S* __restrict__ xq, const double* __restrict__ xs,
                                                  int xgs) {
   using R = typename P::R;
+  using MM = Mm<R>;
+  using V4 = typename MM::V4;
+  constexpr int MT = 2, NC = 8 * NT;  // row tiles per step, rhs per workgroup
   extern __shared__ __align__(16) char smem[];
-  const int64_t a = blockIdx.x >> 1;
-  const int chi = blockIdx.x & 1;
-  const int r0 = blockIdx.y * rtile;
-  const int rt = nrhs - r0 < rtile ? nrhs - r0 : rtile;
-  const int K = t.ntv, half = t.half, rows = t.rows;
-  const int rtp = round4(rt), ntr = rtp >> 2;
-  const int Q = rc / TI, NT = Q * ntr;
+  const int64_t nblk = gridDim.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
+  const int sub = wave / wpa, w = wave - sub * wpa;
+  const int64_t ac = xcd_block(blockIdx.x, nblk) * (4 / wpa) + sub;
+  const bool live = ac < 2 * t.c.V;
+  const int64_t a = live ? ac >> 1 : 0;
+  const int chi = live ? (int)(ac & 1) : 0;
+  const int K = t.ntv, half = t.half, rows = t.rows, r0 = NC * (int)blockIdx.y;
+  const int Kp = (K + 4 * VK - 1) / (4 * VK) * (4 * VK);
   const int64_t Vc = t.c.V, Vf = t.f.V;
-  const int tid = threadIdx.x;
-  int64_t* sS = reinterpret_cast<int64_t*>(smem);                        // [bvol] fine sites
-  cx<R>* sC = reinterpret_cast<cx<R>*>(smem + sites_bytes(t.bvol));      // [K][rtp] coarse values
-  cx<R>* sPT = sC + (size_t)K * rtp;                                      // [K][rc] P^T of the chunk
-  aggregate_sites(t, a, sS);
-  for (int i = tid; i < K * rtp; i += kTransferTB) {
-    const int k = i / rtp, r = i - k * rtp;
+  uint32_t* tab = reinterpret_cast<uint32_t*>(smem) + sub * row_words(t.rows);
+  cx<R>* sC = reinterpret_cast<cx<R>*>(smem + sizeof(uint32_t) * (4 / wpa) * row_words(t.rows)) +
+              sub * Kp * NC;  // [Kp][NC] coarse values
+  aggregate_rows(t, a, tab, w * 64 + lane, wpa * 64);
+  for (int i = w * 64 + lane; i < Kp * NC; i += wpa * 64) {
+    const int k = i / NC, r = r0 + i - k * NC;
     cx<R> v = {0, 0};
-    if (r < rt) v = P::ld(xc, ((int64_t)(chi * K + k) * Vc + a) * nrhs + r0 + r);
+    if (k < K && r < nrhs) v = P::ld(xc, ((int64_t)(chi * K + k) * Vc + a) * nrhs + r);
     sC[i] = v;
   }
+  __syncthreads();
+  if (!live) return;
   const typename PM::S* pb = Pm + ((a * 2 + chi) * rows) * (int64_t)K;
-  const typename P::S* src = mode == 1 ? x : y;
-  for (int row0 = 0; row0 < rows; row0 += rc) {
-    const int nr = rows - row0 < rc ? rows - row0 : rc;
-    __syncthreads();  // previous chunk consumed (and sC, sS written on the first pass)
-    stage_p_rows<PM, R, true>(pb, row0, nr, K, rc, sPT);
-    __syncthreads();
-    for (int uo = tid; uo < NT; uo += kTransferTB) {
-      const int q = uo / ntr, rtt = uo - q * ntr;
-      if (q >= nr) continue;
-      int64_t base[TI], frow[TI];
-      cx<R> acc[TI][4];
+  const int part = n & 1;
+  // as in the restriction, loads are unconditional: rows and columns beyond the
+  // last read the last and are not stored
+  R sc[NT];
+  int rb[NT];
+  int64_t xo[NT];
 #pragma unroll
-      for (int i = 0; i < TI; i++) {
-        const int ii = q + Q * i;
-        base[i] = -1;
-        frow[i] = 0;
-        if (ii < nr) {
-          const int row = row0 + ii, loc = row / half, j = row - loc * half;
-          frow[i] = (int64_t)(chi * half + j) * Vf + sS[loc];
-          base[i] = frow[i] * nrhs + r0 + 4 * rtt;
-        }
+  for (int s = 0; s < NT; s++) {
+    const int r = r0 + 8 * s + (n >> 1);
+    rb[s] = r < nrhs ? r : nrhs - 1;
+    sc[s] = mode == 3 ? (R)xs[rb[s]] : (R)1;
+    xo[s] = mode == 3 ? grouped_index(0, rb[s], nrhs, xgs, 2 * half * Vf) : (int64_t)rb[s];
+  }
+  const R* src = reinterpret_cast<const R*>(mode == 1 ? x : y);
+  const int ntile = (rows + 15) >> 4;
+#pragma unroll 1
+  for (int t0 = MT * w; t0 < ntile; t0 += MT * wpa) {
+    V4 acc[MT][NT];
+    int64_t frow[MT][4];
 #pragma unroll
-        for (int rr = 0; rr < 4; rr++) {
-          acc[i][rr] = {0, 0};
-          if (mode != 0 && base[i] >= 0 && 4 * rtt + rr < rt) {
-            if (mode == 3) {
-              const cx<typename PX::R> u =
-                  PX::ld(xq, grouped_index(frow[i], r0 + 4 * rtt + rr, nrhs, xgs, 2 * half * Vf));
-              acc[i][rr] = (R)xs[r0 + 4 * rtt + rr] * cx<R>{(R)u.re, (R)u.im};
-            } else {
-              acc[i][rr] = P::ld(src, base[i] + rr);
-            }
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int row = 16 * (t0 + m) + MM::row(kq, j), rw = row < rows ? row : rows - 1;
+        frow[m][j] = chi * half * Vf + tab[rw];
+      }
+    if (mode == 3) {
+      typename PX::S raw[MT][4][NT];
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+          for (int s = 0; s < NT; s++) raw[m][j][s] = xq[frow[m][j] * xgs + xo[s]];
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+          for (int s = 0; s < NT; s++) {
+            const cx<typename PX::R> u = PX::ld(&raw[m][j][s], 0);
+            acc[m][s][j] = sc[s] * (R)(part ? u.im : u.re);
           }
-        }
-      }
-      if (mode == 1) {
+    } else if (mode != 0) {
 #pragma unroll
-        for (int i = 0; i < TI; i++)
+      for (int m = 0; m < MT; m++)
 #pragma unroll
-          for (int rr = 0; rr < 4; rr++) acc[i][rr] = {-acc[i][rr].re, -acc[i][rr].im};
-      }
-      // acc holds -x (mode 1), y (mode 2) or 0; the sum over k is added on
-      // top and the sign restored for mode 1
-      for (int k = 0; k < K; k++) {
-        cx<R> cv[4], pv[TI];
-        lds_ld4(sC + k * rtp + 4 * rtt, cv);
+        for (int j = 0; j < 4; j++)
 #pragma unroll
-        for (int i = 0; i < TI; i++) pv[i] = sPT[k * rc + q + Q * i];
-#pragma unroll
-        for (int i = 0; i < TI; i++)
-#pragma unroll
-          for (int rr = 0; rr < 4; rr++) fma_(acc[i][rr], pv[i], cv[rr]);
-      }
-#pragma unroll
-      for (int i = 0; i < TI; i++) {
-        if (base[i] < 0) continue;
-#pragma unroll
-        for (int rr = 0; rr < 4; rr++) {
-          if (4 * rtt + rr < rt) {
-            cx<R> v = acc[i][rr];
-            if (mode == 1) v = {-v.re, -v.im};
-            P::st(y, base[i] + rr, v);
+          for (int s = 0; s < NT; s++) {
+            const R v = src[2 * (frow[m][j] * nrhs + xo[s]) + part];
+            acc[m][s][j] = mode == 1 ? -v : v;
           }
-        }
-      }
+    } else {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) acc[m][s] = (V4){0, 0, 0, 0};
     }
+    // acc holds -x (mode 1), y (mode 2), xs x (mode 3) or 0; the sum over k is
+    // added on top and the sign restored for mode 1
+    const typename PM::S* pr[MT];
+#pragma unroll
+    for (int m = 0; m < MT; m++) {
+      const int row = 16 * (t0 + m) + n;
+      pr[m] = pb + (row < rows ? row : rows - 1) * K;
+    }
+#pragma unroll 2
+    for (int k0 = 0; k0 < K; k0 += 4 * VK) {
+      const int kl = k0 + VK * kq;           // this lane's first test vector
+      const bool in = VK > 1 || kl < K;      // VK > 1 only where 4 VK divides K
+      cx<R> pv[MT][VK];
+#pragma unroll
+      for (int m = 0; m < MT; m++) {
+        cx<typename PM::R> v[VK];
+        PM::template ldv<VK>(pr[m], in ? kl : 0, v);
+#pragma unroll
+        for (int e = 0; e < VK; e++) pv[m][e] = in ? cx<R>{(R)v[e].re, (R)v[e].im} : cx<R>{0, 0};
+      }
+#pragma unroll
+      for (int e = 0; e < VK; e++)
+#pragma unroll
+        for (int s = 0; s < NT; s++) {
+          const cx<R> c = sC[(kl + e) * NC + 8 * s + (n >> 1)];
+          const R b1 = part ? c.im : c.re, b2 = part ? c.re : -c.im;
+#pragma unroll
+          for (int m = 0; m < MT; m++) acc[m][s] = MM::mfma(pv[m][e].re, b1, acc[m][s]);
+#pragma unroll
+          for (int m = 0; m < MT; m++) acc[m][s] = MM::mfma(pv[m][e].im, b2, acc[m][s]);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        if (16 * (t0 + m) + MM::row(kq, j) >= rows) continue;
+#pragma unroll
+        for (int s = 0; s < NT; s++)
+          if (r0 + 8 * s + (n >> 1) < nrhs)
+            reinterpret_cast<R*>(y)[2 * (frow[m][j] * nrhs + rb[s]) + part] = mode == 1 ? -acc[m][s][j] : acc[m][s][j];
+      }
   }
 }
 
@@ -435,79 +551,141 @@ double Transfer::bytes(mgm_prec p, int nrhs) const {
          (double)t.c.V * t.c.dof * nrhs * w;
 }
 
-void Transfer::restrict_(mgm_prec p, const void* x, void* yc, int nrhs) const {
-  ProfScope ps(ctx, KC_TRANSFER, bytes(p, nrhs));
-  MGM_CHECK(t.ntv <= 128 && t.bvol <= 1024, MGM_ERR_SHAPE,
+// waves per aggregate and chirality: 2^4 aggregates of the fine level have 96
+// rows, six per wave quadruple and step (FP16 restriction, 12 test vectors, 12 rhs
+// on 16^4: 20 us with one wave, 26 with four)
+static int transfer_wpa(const TGeom& t) { return t.rows >= 256 ? 4 : 1; }
+static void check_transfer(const TGeom& t) {
+  MGM_CHECK(t.ntv <= 128 && t.bvol <= 1024 && t.rows <= 4096, MGM_ERR_SHAPE,
             "transfers support at most 128 test vectors and 1024 sites per aggregate");
-  const int tile = restrict_rt(t), rt = nrhs < tile ? nrhs : tile;
-  const dim3 nb((unsigned)(2 * t.c.V), (unsigned)((nrhs + tile - 1) / tile)), tb(kTransferTB);
-  if (p == MGM_PREC_F64) {
-    const int rc = restrict_chunk_rows(t, rt, 16);
-    hipLaunchKernelGGL((k_restrict<F64, F64>), nb, tb, restrict_lds(t, rt, rc, 16), ctx->stream,
-                       (const double2*)x, (double2*)yc, P64, t, nrhs, rc, tile, nullptr, nrhs);
-  } else if (p == MGM_PREC_F32) {
-    const int rc = restrict_chunk_rows(t, rt, 8);
-    hipLaunchKernelGGL((k_restrict<F32, F16>), nb, tb, restrict_lds(t, rt, rc, 8), ctx->stream,
-                       (const float2*)x, (float2*)yc, P16, t, nrhs, rc, tile, nullptr, nrhs);
-  } else {
-    throw Error(MGM_ERR_INVALID_ARG, "restrict: precision must be F64 or F32");
+}
+
+// Tiles of 8 rhs per workgroup: all up to four, else the split into fours or
+// threes with the fewest empty ones.  Four are halved where a wave has an
+// aggregate of its own (few rows, so that P is cheap to read twice): 12 test
+// vectors, 32 rhs on 16^4 in 2^4 aggregates, prolongation 75 us against 92.
+static int transfer_nt(int nrhs, int wpa) {
+  const int nt = (nrhs + 7) / 8, NT = nt <= 4 ? nt : (nt + 3) / 4 * 4 <= (nt + 2) / 3 * 3 ? 4 : 3;
+  return NT == 4 && wpa == 1 ? 2 : NT;
+}
+
+template <class P, class PM, int MT>
+static void launch_restrict_nt(Context* c, const TGeom& t, const typename P::S* x, typename P::S* yc,
+                               const typename PM::S* Pm, int nrhs) {
+  using V4 = typename Mm<typename P::R>::V4;
+  const int wpa = transfer_wpa(t), nt = (nrhs + 7) / 8, NT = transfer_nt(nrhs, wpa);
+  const int mz = (t.ntv + 16 * MT - 1) / (16 * MT);
+  const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((nt + NT - 1) / NT), (unsigned)mz), tb(256);
+  const size_t lds = sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) +
+                     (size_t)(4 / wpa) * (wpa - 1) * MT * NT * 64 * sizeof(V4);
+  switch (NT) {
+    case 1: hipLaunchKernelGGL((k_restrict<P, PM, MT, 1>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
+    case 2: hipLaunchKernelGGL((k_restrict<P, PM, MT, 2>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
+    case 3: hipLaunchKernelGGL((k_restrict<P, PM, MT, 3>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
+    default: hipLaunchKernelGGL((k_restrict<P, PM, MT, 4>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
   }
   MGM_LAUNCH_CHECK();
+}
+template <class P, class PM>
+static void launch_restrict(Context* c, const TGeom& t, const typename P::S* x, typename P::S* yc,
+                            const typename PM::S* Pm, int nrhs) {
+  check_transfer(t);
+  if (t.ntv <= 16)
+    launch_restrict_nt<P, PM, 1>(c, t, x, yc, Pm, nrhs);
+  else
+    launch_restrict_nt<P, PM, 2>(c, t, x, yc, Pm, nrhs);
+}
+
+template <class P, class PM, class PX, int VK>
+static void launch_prolong_vk(Context* c, const TGeom& t, const typename P::S* xc, const typename P::S* x,
+                              typename P::S* y, const typename PM::S* Pm, int nrhs, int mode,
+                              const typename PX::S* xq, const double* xs, int xgs) {
+  const int ntile = (2 * nrhs + 15) / 16;
+  const size_t cb = sizeof(typename P::S);
+  const int Kp = (t.ntv + 4 * VK - 1) / (4 * VK) * (4 * VK);
+  int wpa = transfer_wpa(t), NT = transfer_nt(nrhs, wpa);
+  // coarse values of more than 64 KiB: fewer rhs per workgroup, or one
+  // aggregate and chirality (four waves) instead of four
+  auto need = [&](int nt) {
+    return sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) + (size_t)(4 / wpa) * Kp * 8 * nt * cb;
+  };
+  while (NT > 2 && need(NT) > 65536) NT--;
+  if (need(NT) > 65536) wpa = 4;
+  while (NT > 1 && need(NT) > 65536) NT--;
+  const size_t lds = need(NT);
+  const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((ntile + NT - 1) / NT)), tb(256);
+  switch (NT) {
+    case 1: hipLaunchKernelGGL((k_prolong<P, PM, PX, 1, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
+    case 2: hipLaunchKernelGGL((k_prolong<P, PM, PX, 2, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
+    case 3: hipLaunchKernelGGL((k_prolong<P, PM, PX, 3, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
+    default: hipLaunchKernelGGL((k_prolong<P, PM, PX, 4, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
+  }
+  MGM_LAUNCH_CHECK();
+}
+template <class P, class PM, class PX>
+static void launch_prolong(Context* c, const TGeom& t, const typename P::S* xc, const typename P::S* x,
+                           typename P::S* y, const typename PM::S* Pm, int nrhs, int mode,
+                           const typename PX::S* xq, const double* xs, int xgs) {
+  check_transfer(t);
+  // two test vectors (8 bytes of FP16) per A load where the rows are so aligned
+  if (std::is_same<PM, F16>::value && t.ntv % 8 == 0)
+    launch_prolong_vk<P, PM, PX, 2>(c, t, xc, x, y, Pm, nrhs, mode, xq, xs, xgs);
+  else
+    launch_prolong_vk<P, PM, PX, 1>(c, t, xc, x, y, Pm, nrhs, mode, xq, xs, xgs);
+}
+
+void Transfer::restrict_(mgm_prec p, const void* x, void* yc, int nrhs) const {
+  ProfScope ps(ctx, KC_TRANSFER, bytes(p, nrhs));
+  if (p == MGM_PREC_F64)
+    launch_restrict<F64, F64>(ctx, t, (const double2*)x, (double2*)yc, P64, nrhs);
+  else if (p == MGM_PREC_F32)
+    launch_restrict<F32, F16>(ctx, t, (const float2*)x, (float2*)yc, P16, nrhs);
+  else
+    throw Error(MGM_ERR_INVALID_ARG, "restrict: precision must be F64 or F32");
 }
 
 void Transfer::prolong(mgm_prec p, const void* xc, const void* x, void* y, int nrhs, int mode) const {
   ProfScope ps(ctx, KC_TRANSFER, bytes(p, nrhs));
-  MGM_CHECK(t.ntv <= 128 && t.bvol <= 1024, MGM_ERR_SHAPE,
-            "transfers support at most 128 test vectors and 1024 sites per aggregate");
-  if (p == MGM_PREC_F64) {
-    const int tile = prolong_rt(t, 16), rt = nrhs < tile ? nrhs : tile;
-    const dim3 nb((unsigned)(2 * t.c.V), (unsigned)((nrhs + tile - 1) / tile)), tb(kTransferTB);
-    const int rc = prolong_chunk_rows(t, rt, 16, 1);
-    hipLaunchKernelGGL((k_prolong<F64, F64, 1>), nb, tb, prolong_lds(t, rt, rc, 16), ctx->stream,
-                       (const double2*)xc, (const double2*)x, (double2*)y, P64, t, nrhs, mode, rc, tile, nullptr,
-                       nullptr, nrhs);
-  } else if (p == MGM_PREC_F32) {
-    const int tile = prolong_rt(t, 8), rt = nrhs < tile ? nrhs : tile;
-    const dim3 nb((unsigned)(2 * t.c.V), (unsigned)((nrhs + tile - 1) / tile)), tb(kTransferTB);
-    const int rc = prolong_chunk_rows(t, rt, 8, 2);
-    hipLaunchKernelGGL((k_prolong<F32, F16, 2>), nb, tb, prolong_lds(t, rt, rc, 8), ctx->stream,
-                       (const float2*)xc, (const float2*)x, (float2*)y, P16, t, nrhs, mode, rc, tile, nullptr,
-                       nullptr, nrhs);
-  } else {
+  if (p == MGM_PREC_F64)
+    launch_prolong<F64, F64, F64>(ctx, t, (const double2*)xc, (const double2*)x, (double2*)y, P64, nrhs, mode, nullptr,
+                                  nullptr, nrhs);
+  else if (p == MGM_PREC_F32)
+    launch_prolong<F32, F16, F32>(ctx, t, (const float2*)xc, (const float2*)x, (float2*)y, P16, nrhs, mode, nullptr,
+                                  nullptr, nrhs);
+  else
     throw Error(MGM_ERR_INVALID_ARG, "prolong: precision must be F64 or F32");
-  }
-  MGM_LAUNCH_CHECK();
 }
 
 void Transfer::restrict16(const __half2* x16, const double* xs, float2* yc, int nrhs, int xgs) const {
   ProfScope ps(ctx, KC_TRANSFER, bytes(MGM_PREC_F32, nrhs));
-  MGM_CHECK(t.ntv <= 128 && t.bvol <= 1024, MGM_ERR_SHAPE,
-            "transfers support at most 128 test vectors and 1024 sites per aggregate");
+  check_transfer(t);
   MGM_CHECK(P16 != nullptr && xs != nullptr, MGM_ERR_INVALID_ARG, "FP16 transfer input needs P16 and scales");
   if (xgs <= 0) xgs = nrhs;
   MGM_CHECK(nrhs % xgs == 0, MGM_ERR_INVALID_ARG, "column groups must divide the rhs count");
-  const int tile = restrict_rt(t), rt = nrhs < tile ? nrhs : tile;
-  const dim3 nb((unsigned)(2 * t.c.V), (unsigned)((nrhs + tile - 1) / tile)), tb(kTransferTB);
-  const int rc = restrict_chunk_rows(t, rt, 8);
-  hipLaunchKernelGGL((k_restrict<F32, F16, F16>), nb, tb, restrict_lds(t, rt, rc, 8), ctx->stream, x16, yc, P16, t,
-                     nrhs, rc, tile, xs, xgs);
+  const int wpa = transfer_wpa(t), ntile = (nrhs + 15) / 16, mt = (t.ntv + 7) / 8;
+  const int MT = mt <= 4 ? mt : (mt + 3) / 4 * 4 <= (mt + 2) / 3 * 3 ? 4 : 3;
+  const int NT = ntile <= 4 ? ntile : (ntile + 3) / 4 * 4 <= (ntile + 2) / 3 * 3 ? 4 : 3;
+  const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((ntile + NT - 1) / NT), (unsigned)((mt + MT - 1) / MT));
+  const size_t lds = sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) +
+                     (size_t)(4 / wpa) * (wpa - 1) * MT * NT * 64 * sizeof(f4_t);
+#define MGM_R16(M, N)                                                                                              \
+  if (MT == M && NT == N)                                                                                          \
+    hipLaunchKernelGGL((k_restrict16<M, N>), nb, dim3(256), lds, ctx->stream, (const uint32_t*)x16, yc,            \
+                       (const uint32_t*)P16, t, nrhs, wpa, xs, xgs);
+  MGM_R16(1, 1) MGM_R16(1, 2) MGM_R16(1, 3) MGM_R16(1, 4) MGM_R16(2, 1) MGM_R16(2, 2) MGM_R16(2, 3) MGM_R16(2, 4)
+  MGM_R16(3, 1) MGM_R16(3, 2) MGM_R16(3, 3) MGM_R16(3, 4) MGM_R16(4, 1) MGM_R16(4, 2) MGM_R16(4, 3) MGM_R16(4, 4)
+#undef MGM_R16
   MGM_LAUNCH_CHECK();
 }
 
 void Transfer::prolong16(const float2* xc, const __half2* x16, const double* xs, float2* y, int nrhs,
                          int xgs) const {
   ProfScope ps(ctx, KC_TRANSFER, bytes(MGM_PREC_F32, nrhs));
-  const int tile = prolong_rt(t, 8), rt = nrhs < tile ? nrhs : tile;
-  const dim3 nb((unsigned)(2 * t.c.V), (unsigned)((nrhs + tile - 1) / tile)), tb(kTransferTB);
-  MGM_CHECK(t.ntv <= 128 && t.bvol <= 1024, MGM_ERR_SHAPE,
-            "transfers support at most 128 test vectors and 1024 sites per aggregate");
+  check_transfer(t);
   MGM_CHECK(P16 != nullptr && xs != nullptr, MGM_ERR_INVALID_ARG, "FP16 transfer input needs P16 and scales");
   if (xgs <= 0) xgs = nrhs;
   MGM_CHECK(nrhs % xgs == 0, MGM_ERR_INVALID_ARG, "column groups must divide the rhs count");
-  const int rc = prolong_chunk_rows(t, rt, 8, 2);
-  hipLaunchKernelGGL((k_prolong<F32, F16, 2, F16>), nb, tb, prolong_lds(t, rt, rc, 8), ctx->stream, xc,
-                     (const float2*)nullptr, y, P16, t, nrhs, 3, rc, tile, x16, xs, xgs);
-  MGM_LAUNCH_CHECK();
+  launch_prolong<F32, F16, F16>(ctx, t, xc, (const float2*)nullptr, y, P16, nrhs, 3, x16, xs, xgs);
 }
 
 // ------------------------------------------------------------ block QR
