@@ -16,6 +16,8 @@
 #include "fine_dev.h"
 #include "devonce.h"
 
+#include <type_traits>
+
 namespace mgm {
 
 // ------------------------------------------------------------ sigma table
@@ -88,7 +90,7 @@ __device__ __forceinline__ M3 ldU(const double2* U, int64_t V, int mu, int64_t s
   M3 m;
 #pragma unroll
   for (int k = 0; k < 9; k++) {
-    double2 v = U[(int64_t)(mu * 9 + k) * V + s];
+    double2 v = U[link_pos<F64>(V, mu, k, s)];
     m.a[k / 3][k % 3] = {v.x, v.y};
   }
   return m;
@@ -184,34 +186,38 @@ __global__ void k_clover(double* __restrict__ C, const double2* __restrict__ U, 
           }
     }
   for (int chi = 0; chi < 2; chi++) {
-    double* o = C + (int64_t)(36 * chi) * g.V + s;
-    for (int i = 0; i < 6; i++) o[(int64_t)i * g.V] = blk[chi][i][i].re;
+    auto put = [&](int j, double v) { C[clover_pos<F64>(g.V, 36 * chi + j, s)] = v; };
+    for (int i = 0; i < 6; i++) put(i, blk[chi][i][i].re);
     int q = 0;
     for (int i = 1; i < 6; i++)
       for (int j = 0; j < i; j++, q++) {
-        o[(int64_t)(6 + 2 * q) * g.V] = blk[chi][i][j].re;
-        o[(int64_t)(7 + 2 * q) * g.V] = blk[chi][i][j].im;
+        put(6 + 2 * q, blk[chi][i][j].re);
+        put(7 + 2 * q, blk[chi][i][j].im);
       }
   }
 }
 
 // ---------------------------------------------------------- conversions
 
-__global__ void k_cvt_c64_c32(float2* o, const double2* in, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) o[i] = make_float2((float)in[i].x, (float)in[i].y);
+// links and clover of the narrower formats, one thread per entry [36][V], [72][V]
+template <class P>
+__global__ void k_cvt_links(typename P::S* __restrict__ o, const double2* __restrict__ in, int64_t V) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= 36 * V) return;
+  const int e = (int)(i / V);
+  const int64_t s = i - e * V;
+  const double2 v = in[link_pos<F64>(V, e / 9, e % 9, s)];
+  P::st(o, link_pos<P>(V, e / 9, e % 9, s), cx<float>{(float)v.x, (float)v.y});
 }
-__global__ void k_cvt_c64_c16(__half2* o, const double2* in, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) o[i] = __floats2half2_rn((float)in[i].x, (float)in[i].y);
-}
-__global__ void k_cvt_r64_r32(float* o, const double* in, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) o[i] = (float)in[i];
-}
-__global__ void k_cvt_r64_r16(__half* o, const double* in, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) o[i] = __float2half_rn((float)in[i]);
+template <class P>
+__global__ void k_cvt_clover(typename P::RS* __restrict__ o, const double* __restrict__ in, int64_t V) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= 72 * V) return;
+  const int j = (int)(i / V);
+  const int64_t s = i - j * V;
+  const double v = in[clover_pos<F64>(V, j, s)];
+  if constexpr (std::is_same<P, F16>::value) o[clover_pos<P>(V, j, s)] = __float2half_rn((float)v);
+  else o[clover_pos<P>(V, j, s)] = (float)v;
 }
 
 // ---------------------------------------------------------------- dslash
@@ -346,14 +352,18 @@ __device__ __forceinline__ void ordered_site(const Geom& g, const SiteOrder& o, 
 // of one site, so the links, clover entries and index arithmetic are shared by
 // the columns (16-byte FP32, 8-byte FP16 spinor loads at RB = 2).  Bound by the
 // L1 misses a CU keeps in flight: all nine spinor reads of a site miss L1
-// (about 60 outstanding 128-byte lines at 560 cycles, FP64 at 20 rhs on
-// 16^3 x 32), 230 ps a site and rhs in FP64, 105 in FP32, 78 in FP16 whatever the
-// lattice.
+// (60 to 77 outstanding 128-byte lines at 560 cycles).  Fields in groups of 16
+// bytes and 32-bit offsets from uniform bases took 174 registers to 156 in FP64,
+// 123 to 81 in FP32 and 140 to 109 in the step, and half the load instructions:
+// FP64 at 20 rhs on 16^3 x 32 603 us to 535, FP32 at 12 rhs on 24^3 x 48 842 to 810,
+// one FP64 rhs on 8^4 16.4 to 14.1, the FP16 marching step at 4 rhs on 32^3 x 64 671 to
+// 622.
 // DOT: also reduce q^H in and |q|^2 per rhs for the minimal-residual smoother
 // (q = D in), written per block to dpart[2][nrhs][block] (q^H in, then |q|^2).
 // MR (with DOT): the smoother step of k_dslash_march (see there): q is not
 // stored, out = in - omega q, xio += omega in, dots of the unrounded q.
-template <class P, bool DOT, bool MR, int RB>
+// O: the type of a byte offset into a dof plane, 32 bits where a plane fits.
+template <class P, bool DOT, bool MR, int RB, class O>
 __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
                                                 const typename P::S* __restrict__ in,
                                                 const typename P::S* __restrict__ U,
@@ -380,9 +390,11 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
   if (!DOT && !active) return;
   int c[4];
   ordered_site(g, ord, active ? (uint32_t)p : 0u, c);
-  const int64_t sy = g.X, sz = (int64_t)g.X * g.Y, st = sz * g.Z;
-  const int64_t s = c[0] + sy * c[1] + sz * c[2] + st * c[3];
-  const int64_t es = s * nrhs + r0;  // this thread's first element in a plane
+  const uint32_t sy = g.X, sz = sy * (uint32_t)g.Y, st = sz * (uint32_t)g.Z;
+  const uint32_t s = c[0] + sy * c[1] + sz * c[2] + st * c[3];
+  constexpr uint32_t kSB = sizeof(typename P::S);
+  // byte offset of this thread's first element in a plane
+  const O es = ((O)s * (O)nrhs + (O)r0) * kSB;
 
   cx<R> acc[12][RB];
 #pragma unroll
@@ -398,22 +410,22 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
     const bool fwd = (hop & 1) == 0;
     const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
     const int ex = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
-    const int64_t sd = mu == 0 ? 1 : mu == 1 ? sy : mu == 2 ? sz : st;
+    const uint32_t sd = mu == 0 ? 1u : mu == 1 ? sy : mu == 2 ? sz : st;
     const bool wrap = fwd ? (cm == ex - 1) : (cm == 0);
-    const int64_t span = (int64_t)(ex - 1) * sd;
-    const int64_t sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
+    const uint32_t span = (uint32_t)(ex - 1) * sd;
+    const uint32_t sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
     // -1/2 (1 -/+ g_mu), times -1 on hops across the time boundary
     const R f = (mu == 3 && wrap && g.antiperiodic) ? (R)0.5 : (R)-0.5;
     const R sg = fwd ? (R)-1 : (R)1;  // half spinor h = u + sg * A_mu l
-    const int64_t e = sn * nrhs + r0;
+    const O e = ((O)sn * (O)nrhs + (O)r0) * kSB;
     cx<R> h[2][3][RB];
 #pragma unroll
     for (int a = 0; a < 3; a++) {
       cx<R> u0[RB], u1[RB], l0[RB], l1[RB];
-      P::template ldv<RB>(in, (int64_t)(0 * 3 + a) * N + e, u0);
-      P::template ldv<RB>(in, (int64_t)(1 * 3 + a) * N + e, u1);
-      P::template ldv<RB>(in, (int64_t)(2 * 3 + a) * N + e, l0);
-      P::template ldv<RB>(in, (int64_t)(3 * 3 + a) * N + e, l1);
+      P::template ldv<RB>(at_byte(in + (0 * 3 + a) * N, e), 0, u0);
+      P::template ldv<RB>(at_byte(in + (1 * 3 + a) * N, e), 0, u1);
+      P::template ldv<RB>(at_byte(in + (2 * 3 + a) * N, e), 0, l0);
+      P::template ldv<RB>(at_byte(in + (3 * 3 + a) * N, e), 0, l1);
 #pragma unroll
       for (int j = 0; j < RB; j++) {
         cx<R> a0, a1;
@@ -423,10 +435,11 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
       }
     }
     // forward: U_mu(x) h ; backward: U_mu(x - mu)^H h
-    const typename P::S* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
+    typename P::S lk[9];
+    link_load<P>(U, V, mu, fwd ? s : sn, lk);
     cx<R> Um[3][3];
 #pragma unroll
-    for (int k = 0; k < 9; k++) Um[k / 3][k % 3] = P::ld(Ub, (int64_t)k * V);
+    for (int k = 0; k < 9; k++) Um[k / 3][k % 3] = P::ld(lk, k);
 #pragma unroll
     for (int j = 0; j < RB; j++)
 #pragma unroll
@@ -474,18 +487,20 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
   for (int chi = 0; chi < 2; chi++) {
     cx<R> pv[6][RB];
 #pragma unroll
-    for (int k = 0; k < 6; k++) P::template ldv<RB>(in, (int64_t)(6 * chi + k) * N + es, pv[k]);
+    for (int k = 0; k < 6; k++) P::template ldv<RB>(at_byte(in + (6 * chi + k) * N, es), 0, pv[k]);
     cx<R> xv[6][RB];
     if (MR) {
 #pragma unroll
-      for (int k = 0; k < 6; k++) P::template ldv<RB>(xio, (int64_t)(6 * chi + k) * N + es, xv[k]);
+      for (int k = 0; k < 6; k++) P::template ldv<RB>(at_byte(xio + (6 * chi + k) * N, es), 0, xv[k]);
     }
+    R cl[36];
+    clover_load<P>(C, V, s, chi, cl);
 #pragma unroll
     for (int j = 0; j < RB; j++) {
       cx<R> x6[6], q6[6];
 #pragma unroll
       for (int k = 0; k < 6; k++) x6[k] = pv[k][j];
-      clover_block<P>(C, V, s, chi, x6, q6);
+      clover_mul(cl, x6, q6);
 #pragma unroll
       for (int k = 0; k < 6; k++) {
         cx<R> o;
@@ -515,8 +530,8 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
     if (MR && active) {
 #pragma unroll
       for (int k = 0; k < 6; k++) {
-        P::template stv<RB>(out, (int64_t)(6 * chi + k) * N + es, pv[k]);
-        P::template stv<RB>(xio, (int64_t)(6 * chi + k) * N + es, xv[k]);
+        P::template stv<RB>(at_byte(out + (6 * chi + k) * N, es), 0, pv[k]);
+        P::template stv<RB>(at_byte(xio + (6 * chi + k) * N, es), 0, xv[k]);
       }
     }
   }
@@ -528,7 +543,7 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
     }
   } else if (active) {
 #pragma unroll
-    for (int k = 0; k < 12; k++) P::template stv<RB>(out, (int64_t)k * N + es, acc[k]);
+    for (int k = 0; k < 12; k++) P::template stv<RB>(at_byte(out + k * N, es), 0, acc[k]);
   }
   if (DOT) dot_block_store<RB>(dqr, dqq, active, base, nrhs, nblocks, dpart);
 }
@@ -627,9 +642,6 @@ struct BufIO<F32> {
     return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, (int)so, AUX));
   }
   __device__ __forceinline__ static cx<float> cvt(S v) { return {v.x, v.y}; }
-  __device__ __forceinline__ static float re(Rsrc r, uint32_t vo, uint32_t so) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, 0));
-  }
   template <int AUX = 0>
   __device__ __forceinline__ static void st(Rsrc r, uint32_t vo, uint32_t so, cx<float> v) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0)), make_float2(v.re, v.im)), r, (int)vo, (int)so, AUX);
@@ -647,9 +659,6 @@ struct BufIO<F16> {
     const float2 f = __half22float2(v);
     return {f.x, f.y};
   }
-  __device__ __forceinline__ static float re(Rsrc r, uint32_t vo, uint32_t so) {
-    return __half2float(__builtin_bit_cast(__half, __builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, (int)so, 0)));
-  }
   template <int AUX = 0>
   __device__ __forceinline__ static void st(Rsrc r, uint32_t vo, uint32_t so, cx<float> v) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, __floats2half2_rn(v.re, v.im)), r, (int)vo,
@@ -657,36 +666,60 @@ struct BufIO<F16> {
   }
 };
 
-// link U_mu at the site whose byte offset (in a link plane) is vo
+// NB bytes at vo + so as words
+template <int NB>
+__device__ __forceinline__ auto buf_words(Rsrc r, uint32_t vo, uint32_t so) {
+  if constexpr (NB == 16) return __builtin_amdgcn_raw_buffer_load_b128(r, (int)vo, (int)so, 0);
+  else return __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, (int)so, 0);
+}
+// the nine stored entries of U_mu(ls) (order of link_load); plane_b: bytes of V
+// entries
 template <class P>
-__device__ __forceinline__ void buf_link(Rsrc ru, uint32_t plane_b, int mu, uint32_t vo,
-                                         cx<typename P::R> (&Um)[3][3]) {
+__device__ __forceinline__ void buf_link_raw(Rsrc ru, uint32_t plane_b, int mu, uint32_t ls,
+                                             typename P::S (&w)[9]) {
+  using S = typename P::S;
+  constexpr int LG = FieldGroup<P>::LG;
 #pragma unroll
-  for (int k = 0; k < 9; k++)
-    Um[k / 3][k % 3] = BufIO<P>::cvt(BufIO<P>::raw(ru, vo, (uint32_t)(mu * 9 + k) * plane_b));
+  for (int c = 0; c < 8 / LG; c++) {
+    const auto v = buf_words<LG * sizeof(S)>(ru, ls * (uint32_t)(LG * sizeof(S)), (uint32_t)(mu * 8 + c * LG) * plane_b);
+    static_assert(sizeof(v) == LG * sizeof(S), "group size");
+    __builtin_memcpy(&w[c * LG], &v, sizeof(v));
+  }
+  w[8] = BufIO<P>::raw(ru, ls * (uint32_t)sizeof(S), (uint32_t)(32 + mu) * plane_b);
+}
+// the 36 stored reals of block chi at site s
+template <class P>
+__device__ __forceinline__ void buf_clover_raw(Rsrc rc, uint32_t plane_b, uint32_t s, int chi,
+                                               typename P::RS (&c)[36]) {
+  using T = typename P::RS;
+  constexpr int CG = FieldGroup<P>::CG;
+#pragma unroll
+  for (int k = 0; k < 36; k += CG) {
+    const auto v = buf_words<CG * sizeof(T)>(rc, s * (uint32_t)(CG * sizeof(T)), (uint32_t)(36 * chi + k) * plane_b);
+    static_assert(sizeof(v) == CG * sizeof(T), "group size");
+    __builtin_memcpy(&c[k], &v, sizeof(v));
+  }
+}
+// link U_mu at site ls
+template <class P>
+__device__ __forceinline__ void buf_link(Rsrc ru, uint32_t plane_b, int mu, uint32_t ls,
+                                         cx<typename P::R> (&Um)[3][3]) {
+  typename P::S w[9];
+  buf_link_raw<P>(ru, plane_b, mu, ls, w);
+#pragma unroll
+  for (int k = 0; k < 9; k++) Um[k / 3][k % 3] = BufIO<P>::cvt(w[k]);
 }
 
-// Hermitian 6x6 clover block times p (same arithmetic as clover_block)
+// Hermitian 6x6 clover block times x
 template <class P>
-__device__ __forceinline__ void buf_clover(Rsrc rc, uint32_t plane_b, uint32_t vo, int chi,
+__device__ __forceinline__ void buf_clover(Rsrc rc, uint32_t plane_b, uint32_t s, int chi,
                                            const cx<typename P::R>* x, cx<typename P::R>* y) {
-  using R = typename P::R;
-  const uint32_t b0 = (uint32_t)(36 * chi) * plane_b;
+  typename P::RS w[36];
+  buf_clover_raw<P>(rc, plane_b, s, chi, w);
+  typename P::R c[36];
 #pragma unroll
-  for (int i = 0; i < 6; i++) {
-    R d = BufIO<P>::re(rc, vo, b0 + (uint32_t)i * plane_b);
-    y[i] = d * x[i];
-  }
-  int q = 0;
-#pragma unroll
-  for (int i = 1; i < 6; i++)
-#pragma unroll
-    for (int j = 0; j < i; j++, q++) {
-      cx<R> cij = {BufIO<P>::re(rc, vo, b0 + (uint32_t)(6 + 2 * q) * plane_b),
-                   BufIO<P>::re(rc, vo, b0 + (uint32_t)(7 + 2 * q) * plane_b)};
-      fma_(y[i], cij, x[j]);
-      fmac_(y[j], cij, x[i]);
-    }
+  for (int k = 0; k < 36; k++) c[k] = P::ldr(w, k);
+  clover_mul(c, x, y);
 }
 
 // ------------------------------------------------ packed FP16 arithmetic
@@ -768,27 +801,26 @@ __device__ __forceinline__ void link_mul_pk(bool fwd, const hv2 (&U)[3][3], cons
   }
 }
 
-// the nine links U_mu at byte offset vo, in their FP16 storage
-__device__ __forceinline__ void buf_link_pk(Rsrc ru, uint32_t plane_b, int mu, uint32_t vo, hv2 (&U)[3][3]) {
+// the nine entries of U_mu(ls) in their FP16 storage
+__device__ __forceinline__ void buf_link_pk(Rsrc ru, uint32_t plane_b, int mu, uint32_t ls, hv2 (&U)[3][3]) {
+  __half2 w[9];
+  buf_link_raw<F16>(ru, plane_b, mu, ls, w);
 #pragma unroll
-  for (int k = 0; k < 9; k++)
-    U[k / 3][k % 3] = __builtin_bit_cast(hv2, __builtin_amdgcn_raw_buffer_load_b32(ru, (int)vo,
-                                                                                 (int)((uint32_t)(mu * 9 + k) * plane_b), 0));
+  for (int k = 0; k < 9; k++) U[k / 3][k % 3] = hv(w[k]);
 }
 
-// Hermitian 6x6 clover block (FP16 planes: 6 diagonal reals, then the 15
-// entries below the diagonal as (re, im) plane pairs) times x: diagonal in
+// Hermitian 6x6 clover block (FP16: 6 diagonal reals, then the 15 entries below
+// the diagonal as (re, im) pairs) times x: diagonal in
 // FP32, off-diagonal products by dot2
-__device__ __forceinline__ void buf_clover_pk(Rsrc rc, uint32_t plane_b, uint32_t vo, int chi, const hv2 (&x)[6],
+__device__ __forceinline__ void buf_clover_pk(Rsrc rc, uint32_t plane_b, uint32_t s, int chi, const hv2 (&x)[6],
                                               cx<float> (&y)[6]) {
-  const uint32_t b0 = (uint32_t)(36 * chi) * plane_b;
-  auto ld16 = [&](uint32_t so) {
-    return __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(rc, (int)vo, (int)so, 0));
-  };
+  __half w[36];
+  buf_clover_raw<F16>(rc, plane_b, s, chi, w);
+  auto h16 = [&](int k) { return __builtin_bit_cast(_Float16, w[k]); };
   hv2 xn[6], xs[6], xm[6];
 #pragma unroll
   for (int i = 0; i < 6; i++) {
-    const float d = (float)ld16(b0 + (uint32_t)i * plane_b);
+    const float d = (float)h16(i);
     y[i] = {d * (float)x[i].x, d * (float)x[i].y};
     xn[i] = hv2{x[i].x, (_Float16)-x[i].y};
     xs[i] = hv2{x[i].y, x[i].x};
@@ -799,7 +831,7 @@ __device__ __forceinline__ void buf_clover_pk(Rsrc rc, uint32_t plane_b, uint32_
   for (int i = 1; i < 6; i++)
 #pragma unroll
     for (int j = 0; j < i; j++, q++) {
-      const hv2 c = hv2{ld16(b0 + (uint32_t)(6 + 2 * q) * plane_b), ld16(b0 + (uint32_t)(7 + 2 * q) * plane_b)};
+      const hv2 c = hv2{h16(6 + 2 * q), h16(7 + 2 * q)};
       y[i].re = dot2(c, xn[j], y[i].re);  // c x_j
       y[i].im = dot2(c, xs[j], y[i].im);
       y[j].re = dot2(c, x[i], y[j].re);   // conj(c) x_i
@@ -808,24 +840,24 @@ __device__ __forceinline__ void buf_clover_pk(Rsrc rc, uint32_t plane_b, uint32_
 }
 
 // gg of one hop from the twelve stored components of the neighbour spinor
-// and the link at byte offset lvo: FP32 arithmetic on converted values, or
+// and the link of site ls: FP32 arithmetic on converted values, or
 // (PK, FP16 storage only) the packed FP16 form above
 template <class P, bool PK>
 __device__ __forceinline__ void hop_raw(const typename P::S (&raw)[12], int mu, bool fwd, Rsrc ru, uint32_t upb,
-                                        uint32_t lvo, cx<typename P::R> (&gg)[2][3]) {
+                                        uint32_t ls, cx<typename P::R> (&gg)[2][3]) {
   if constexpr (PK) {
     hv2 ps[12];
 #pragma unroll
     for (int k = 0; k < 12; k++) ps[k] = hv(raw[k]);
     hv2 U[3][3], h[2][3];
-    buf_link_pk(ru, upb, mu, lvo, U);
+    buf_link_pk(ru, upb, mu, ls, U);
     half_spinor_pk(mu, fwd, ps, h);
     link_mul_pk(fwd, U, h, gg);
   } else {
     cx<typename P::R> ps[12], Um[3][3];
 #pragma unroll
     for (int k = 0; k < 12; k++) ps[k] = BufIO<P>::cvt(raw[k]);
-    buf_link<P>(ru, upb, mu, lvo, Um);
+    buf_link<P>(ru, upb, mu, ls, Um);
     hop_half<P>(mu, fwd, ps, Um, gg);
   }
 }
@@ -938,7 +970,7 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
       cx<R> gg[2][3];
 #pragma unroll
       for (int k = 0; k < 12; k++) ps[k] = IO::raw(rin, (sn * nrhs + r) * IO::SB, (uint32_t)k * spb);
-      hop_raw<P, PK>(ps, 3, fwd, ru, upb, (fwd ? s_own : sn) * IO::SB, gg);
+      hop_raw<P, PK>(ps, 3, fwd, ru, upb, (fwd ? s_own : sn), gg);
       hop_add<P>(3, fwd, fwd ? ftp : ftm, gg, a);
     }
   };
@@ -953,7 +985,7 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
     cx<R> gg[2][3];
 #pragma unroll
     for (int k = 0; k < 12; k++) pm[k] = IO::raw(rin, (sm * nrhs + r) * IO::SB, (uint32_t)k * spb);
-    hop_raw<P, PK>(pm, 2, false, ru, upb, sm * IO::SB, gg);
+    hop_raw<P, PK>(pm, 2, false, ru, upb, sm, gg);
 #pragma unroll
     for (int k = 0; k < 12; k++) acc[k] = {0, 0};
     hop_add<P>(2, false, (R)-0.5, gg, acc);
@@ -996,7 +1028,7 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
       cx<R> gg[2][3];
 #pragma unroll
       for (int k = 0; k < 12; k++) ps[k] = cur[lidx(k, lrow, lcol)];
-      hop_raw<P, PK>(ps, mu, fwd, ru, upb, ls * IO::SB, gg);
+      hop_raw<P, PK>(ps, mu, fwd, ru, upb, ls, gg);
       hop_add<P>(mu, fwd, (R)-0.5, gg, acc);
     }
     if (!kTEarly) t_hops(z, acc);
@@ -1015,12 +1047,12 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
         hv2 x6[6];
 #pragma unroll
         for (int k = 0; k < 6; k++) x6[k] = hv(cur[lidx(6 * chi + k, yl + 1, col)]);
-        buf_clover_pk(rc, cpb, s * IO::RB, chi, x6, q6);
+        buf_clover_pk(rc, cpb, s, chi, x6, q6);
       } else {
         cx<R> p6[6];
 #pragma unroll
         for (int k = 0; k < 6; k++) p6[k] = IO::cvt(cur[lidx(6 * chi + k, yl + 1, col)]);
-        buf_clover<P>(rc, cpb, s * IO::RB, chi, p6, q6);
+        buf_clover<P>(rc, cpb, s, chi, p6, q6);
       }
 #pragma unroll
       for (int k = 0; k < 6; k++) {
@@ -1031,7 +1063,7 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
     // forward z hop from the next plane
     {
       cx<R> gg[2][3];
-      hop_raw<P, PK>(nx, 2, true, ru, upb, s * IO::SB, gg);
+      hop_raw<P, PK>(nx, 2, true, ru, upb, s, gg);
       hop_add<P>(2, true, (R)-0.5, gg, acc);
     }
     // stage the next plane (own rows from the registers, halo rows loaded)
@@ -1059,7 +1091,7 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
         S pv[12];
 #pragma unroll
         for (int k = 0; k < 12; k++) pv[k] = cur[lidx(k, yl + 1, col)];
-        hop_raw<P, PK>(pv, 2, false, ru, upb, s * IO::SB, gg);
+        hop_raw<P, PK>(pv, 2, false, ru, upb, s, gg);
       }
       const uint32_t vo = (s * nrhs + r) * IO::SB;
       cx<R> sqr = {0, 0};  // this site's dots in the working precision,
@@ -1171,10 +1203,10 @@ void FineOp::build(const double* gauge_host) {
                      csw);
   MGM_LAUNCH_CHECK();
   const int64_t nu = 36 * V, nc = 72 * V;
-  hipLaunchKernelGGL(k_cvt_c64_c32, dim3(nblocks_for(nu, 256)), dim3(256), 0, ctx->stream, U32, U64, nu);
-  hipLaunchKernelGGL(k_cvt_c64_c16, dim3(nblocks_for(nu, 256)), dim3(256), 0, ctx->stream, U16, U64, nu);
-  hipLaunchKernelGGL(k_cvt_r64_r32, dim3(nblocks_for(nc, 256)), dim3(256), 0, ctx->stream, C32, C64, nc);
-  hipLaunchKernelGGL(k_cvt_r64_r16, dim3(nblocks_for(nc, 256)), dim3(256), 0, ctx->stream, C16, C64, nc);
+  hipLaunchKernelGGL(k_cvt_links<F32>, dim3(nblocks_for(nu, 256)), dim3(256), 0, ctx->stream, U32, U64, V);
+  hipLaunchKernelGGL(k_cvt_links<F16>, dim3(nblocks_for(nu, 256)), dim3(256), 0, ctx->stream, U16, U64, V);
+  hipLaunchKernelGGL(k_cvt_clover<F32>, dim3(nblocks_for(nc, 256)), dim3(256), 0, ctx->stream, C32, C64, V);
+  hipLaunchKernelGGL(k_cvt_clover<F16>, dim3(nblocks_for(nc, 256)), dim3(256), 0, ctx->stream, C16, C64, V);
   MGM_LAUNCH_CHECK();
   ctx->sync();  // tmp must outlive the copy
 }
@@ -1218,7 +1250,9 @@ static int64_t launch_site_p(const FineOp& op, const typename P::S* U, const typ
                           int nrhs, double2* dpart, SiteOrder ord, const MrArgs& mr) {
   using S = typename P::S;
   const int64_t nb = (op.g.V * (nrhs / RB) + 255) / 256;
-  hipLaunchKernelGGL((k_dslash<P, DOT, MR, RB>), dim3((unsigned)nb), dim3(256), 0, op.ctx->stream, (S*)y,
+  auto* k = (double)op.g.V * nrhs * sizeof(S) <= 4294967295.0 ? k_dslash<P, DOT, MR, RB, uint32_t>
+                                                             : k_dslash<P, DOT, MR, RB, int64_t>;
+  hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(256), 0, op.ctx->stream, (S*)y,
                      (const S*)x, U, C, op.g, nrhs, nb, ord, dpart, (S*)mr.x, mr.qr, mr.qq);
   MGM_LAUNCH_CHECK();
   return nb;
@@ -1228,8 +1262,8 @@ template <bool DOT, int RB>
 static int64_t launch_rb(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart,
                       SiteOrder ord) {
   switch (p) {
-    case MGM_PREC_F64:
-      return launch_site_p<F64, DOT, false, RB>(op, op.U64, op.C64, x, y, nrhs, dpart, ord, MrArgs());
+    case MGM_PREC_F64:  // one rhs per thread
+      return launch_site_p<F64, DOT, false, 1>(op, op.U64, op.C64, x, y, nrhs, dpart, ord, MrArgs());
     case MGM_PREC_F32:
       return launch_site_p<F32, DOT, false, RB>(op, op.U32, op.C32, x, y, nrhs, dpart, ord, MrArgs());
     case MGM_PREC_F16:

@@ -14,9 +14,9 @@ struct FineOp {
   Context* ctx = nullptr;
   Geom g{};
   double m0 = 0, csw = 0;
-  // links [mu][9][V] complex, clover (+ mass) [72][V] real: two 6x6 Hermitian
-  // chirality blocks per site, each 6 diagonal reals then 15 complex lower
-  // entries C[i][j] (i > j) in row order.
+  // links 36 complex and clover (+ mass) 72 real per site, in the order of link_pos and
+  // clover_pos: two 6x6 Hermitian chirality blocks per site, each 6 diagonal reals then
+  // 15 complex lower entries C[i][j] (i > j) in row order.
   double2* U64 = nullptr;
   float2* U32 = nullptr;
   __half2* U16 = nullptr;

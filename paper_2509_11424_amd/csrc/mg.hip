@@ -790,7 +790,7 @@ __device__ void wilson_block(const FineOp& op, int k, int64_t s, int64_t y, cons
   const int64_t ls = fwd ? s : y;  // site owning the link U_mu
   cx<double> U[3][3];
   for (int q = 0; q < 9; q++) {
-    double2 v = op.U64[(int64_t)(mu * 9 + q) * g.V + ls];
+    double2 v = op.U64[link_pos<F64>(g.V, mu, q, ls)];
     U[q / 3][q % 3] = {v.x, v.y};
   }
   cx<double> h[2][3];

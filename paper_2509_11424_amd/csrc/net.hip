@@ -6,6 +6,7 @@
 // Layout: channel-major like the fine spinors, element
 // ((channel * 3 + colour) * V + site) * nrhs + rhs, FP32 complex.
 #include "net.h"
+#include "fine_dev.h"
 
 #include <chrono>
 #include <cmath>
@@ -52,7 +53,7 @@ __device__ __forceinline__ f4_t mfma4(float a, float b, f4_t c) {
 // with scalar FMAs and the links re-read per input channel.  Twelve loads in
 // flight per wave; prefetching the next twelve spills or halves the occupancy
 // (1.71 ms), and so does one colour per wave (2.2 ms).
-template <int NG>
+template <int NG, class O>
 __global__ __launch_bounds__(256) void k_ptc_layer(float2* __restrict__ out, const float2* __restrict__ in,
                                                    const float2* __restrict__ U, const float2* __restrict__ W,
                                                    Geom g, int co, int ci, int nrhs) {
@@ -92,16 +93,16 @@ __global__ __launch_bounds__(256) void k_ptc_layer(float2* __restrict__ out, con
       const int64_t span = (int64_t)(ex - 1) * sd;
       sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
       ph = (mu == 3 && wrap && g.antiperiodic) ? -1.f : 1.f;
-      const float2* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
+      const uint32_t sl = (uint32_t)(fwd ? s : sn);
 #pragma unroll
       for (int cc = 0; cc < 3; cc++)
 #pragma unroll
         for (int k = 0; k < 3; k++) {
-          const float2 w = Ub[(int64_t)(fwd ? 3 * cc + k : 3 * k + cc) * V];
+          const float2 w = link_entry<F32>(U, V, mu, fwd ? 3 * cc + k : 3 * k + cc, sl);
           u[cc][k] = {w.x, fwd ? w.y : -w.y};  // (U^H)_{ak} = conj(U_{ka})
         }
     }
-    const float2* src = in + sn * nrhs + r;
+    const O src = ((O)sn * (O)nrhs + (O)r) * (O)sizeof(float2);  // byte offset in a plane
     const float2* wp = sW + (p * ci * 4 + (threadIdx.x & 3)) * NG;
     // four input channels at a time (c_in is a multiple of 4): twelve loads in
     // flight
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256) void k_ptc_layer(float2* __restrict__ out, con
 #pragma unroll
       for (int j = 0; j < 4; j++)
 #pragma unroll
-        for (int k = 0; k < 3; k++) raw[j][k] = src[(int64_t)((b0 + j) * 3 + k) * N];
+        for (int k = 0; k < 3; k++) raw[j][k] = *at_byte(in + ((b0 + j) * 3 + k) * N, src);
 #pragma unroll
       for (int j = 0; j < 4; j++) {
         cx<float> t[3];
@@ -247,9 +248,7 @@ __global__ __launch_bounds__(256) void k_ptc_wgrad(const float2* __restrict__ go
         const int64_t span = (int64_t)(ex - 1) * sd;
         const int64_t sn = fwd ? (wrap ? s - span : s + sd) : (wrap ? s + span : s - sd);
         if (mu == 3 && wrap && g.antiperiodic) ph[i] = -1.f;
-        const float2* Ub = U + (int64_t)(mu * 9) * V + (fwd ? s : sn);
-#pragma unroll
-        for (int k9 = 0; k9 < 9; k9++) ur[i][k9] = Ub[(int64_t)k9 * V];
+        link_load<F32>(U, V, mu, (uint32_t)(fwd ? s : sn), ur[i]);
         src = in + sn * nrhs + r;
       }
 #pragma unroll
@@ -452,11 +451,15 @@ static void launch_layer(Context* c, const FineOp* op, float2* out, const float2
   while (ng % 2 == 0 && (unsigned)(co / (4 * ng)) * 2u * nb <= (unsigned)c->cu_count) ng /= 2;
   const dim3 grid(nb, co / (4 * ng)), tb(256);
   const size_t lds = (size_t)kNetPaths * ci * 4 * ng * sizeof(float2);
+  auto launch = [&](auto* k) {
+    hipLaunchKernelGGL(k, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs);
+  };
+  const bool wide = (double)N * sizeof(float2) > 4294967295.0;  // a channel plane past 32-bit byte offsets
   switch (ng) {
-    case 1: hipLaunchKernelGGL(k_ptc_layer<1>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
-    case 2: hipLaunchKernelGGL(k_ptc_layer<2>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
-    case 3: hipLaunchKernelGGL(k_ptc_layer<3>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
-    case 4: hipLaunchKernelGGL(k_ptc_layer<4>, grid, tb, lds, c->stream, out, in, op->U32, W, op->g, co, ci, nrhs); break;
+    case 1: launch(wide ? k_ptc_layer<1, int64_t> : k_ptc_layer<1, uint32_t>); break;
+    case 2: launch(wide ? k_ptc_layer<2, int64_t> : k_ptc_layer<2, uint32_t>); break;
+    case 3: launch(wide ? k_ptc_layer<3, int64_t> : k_ptc_layer<3, uint32_t>); break;
+    case 4: launch(wide ? k_ptc_layer<4, int64_t> : k_ptc_layer<4, uint32_t>); break;
     default: throw Error(MGM_ERR_INVALID_ARG, "network widths must be 4, 8, 12 or 16");
   }
   MGM_LAUNCH_CHECK();
