@@ -315,8 +315,10 @@ __device__ __forceinline__ void dot_block_store(cx<double> (&dqr)[RB], double (&
 // Order in which the site-parallel kernel walks the lattice: bands of bt time
 // slices, inside a band bands of bz planes, inside those bands of by rows;
 // within a tile x is fastest, then y, z, t.  by = bz = bt = 0: lexicographic.
+// stream: the result goes past the caches (see streams()).
 struct SiteOrder {
   int by, bz, bt;
+  bool stream;
 };
 
 // coordinates of the p-th site of the order
@@ -348,6 +350,66 @@ __device__ __forceinline__ void ordered_site(const Geom& g, const SiteOrder& o, 
   c[3] = (int)(t0 + q);
 }
 
+// RB consecutive elements in their storage format
+template <class P, int RB>
+using RawV = uint32_t __attribute__((ext_vector_type(RB * sizeof(typename P::S) / 4)));
+template <class P, int RB>
+__device__ __forceinline__ RawV<P, RB> raw_ld(const typename P::S* p, int64_t i) {
+  return *reinterpret_cast<const RawV<P, RB>*>(p + i);
+}
+template <class P, int RB>
+__device__ __forceinline__ void raw_cvt(RawV<P, RB> a, cx<typename P::R> (&v)[RB]) {
+  typename P::S e[RB];
+  __builtin_memcpy(e, &a, sizeof(a));
+#pragma unroll
+  for (int j = 0; j < RB; j++) v[j] = P::ld(e, j);
+}
+// most threads of a tile (registers: 3 waves a SIMD)
+constexpr int kTileThreads = 768;
+
+// per-column block sums of a tile, through LDS
+template <int RB>
+__device__ __forceinline__ void tile_dot_store(const cx<double> (&dqr)[RB], const double (&dqq)[RB], int nrhs, int sites,
+                                               int64_t nblocks, unsigned char* smem, double2* __restrict__ dpart) {
+  const int t = threadIdx.x, n = sites * nrhs;
+  double* sr = reinterpret_cast<double*>(smem);  // [3][n]
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < RB; j++) {
+    sr[t * RB + j] = dqr[j].re;
+    sr[n + t * RB + j] = dqr[j].im;
+    sr[2 * n + t * RB + j] = dqq[j];
+  }
+  __syncthreads();
+  // halve the site count until one is left (any count: odd ones keep the last)
+  for (int m = sites; m > 1;) {
+    const int hlf = m / 2, off = m - hlf;
+#pragma unroll
+    for (int j = 0; j < RB; j++) {
+      const int e = t * RB + j;
+      if (e < hlf * nrhs) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) sr[k * n + e] += sr[k * n + e + off * nrhs];
+      }
+    }
+    m = off;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < RB; j++) {
+    const int e = t * RB + j;
+    if (e < nrhs) {
+      dpart[(int64_t)e * nblocks + blockIdx.x] = make_double2(sr[e], sr[n + e]);
+      dpart[(int64_t)(nrhs + e) * nblocks + blockIdx.x] = make_double2(sr[2 * n + e], 0.0);
+    }
+  }
+}
+
+struct Tile {
+  int b[4];   // extents
+  int sites;  // their product
+};
+// O: the type of a byte offset into a dof plane, 32 bits where a plane fits.
 // Site-parallel dslash: one thread computes RB consecutive right-hand sides
 // of one site, so the links, clover entries and index arithmetic are shared by
 // the columns (16-byte FP32, 8-byte FP16 spinor loads at RB = 2).  Bound by the
@@ -363,39 +425,79 @@ __device__ __forceinline__ void ordered_site(const Geom& g, const SiteOrder& o, 
 // MR (with DOT): the smoother step of k_dslash_march (see there): q is not
 // stored, out = in - omega q, xio += omega in, dots of the unrounded q.
 // O: the type of a byte offset into a dof plane, 32 bits where a plane fits.
-template <class P, bool DOT, bool MR, int RB, class O>
-__global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
+// TILE (FP64, FP32): a block owns all rhs of a box of sites and stages their spinors
+// in LDS, so hops inside the box (4 of 8 in a box of 4 x 2 x 2 x 4) and the centre
+// do not read L1 again.  The box is rarely larger than 32 sites: blocks of three or four
+// waves fill a CU's wave slots and do not wait for each other.  FP64 at 12 rhs on
+// 16^4 161 us to 122, at 4 rhs 90 to 51, at 20 rhs on 16^3 x 32 535 to 497; FP32 at 12 rhs
+// on 24^3 x 48 808 to 699 (38 million L1 lines instead of 66), then bound by reads past
+// L2: the boxes an XCD has in flight exceed its 4 MB, 25 million lines come from
+// beyond, 9 million would do.
+// Same sums in the same order as the untiled form.
+template <class P, bool DOT, bool MR, int RB, class O, bool TILE>
+__global__ __launch_bounds__(TILE ? kTileThreads : 256) void k_dslash(typename P::S* __restrict__ out,
                                                 const typename P::S* __restrict__ in,
                                                 const typename P::S* __restrict__ U,
                                                 const typename P::RS* __restrict__ C, Geom g, int nrhs,
-                                                int64_t nblocks, SiteOrder ord, double2* __restrict__ dpart,
+                                                int64_t nblocks, SiteOrder ord, Tile tile,
+                                                double2* __restrict__ dpart,
                                                 typename P::S* __restrict__ xio, const double2* __restrict__ wqr,
                                                 const double* __restrict__ wqq) {
   using R = typename P::R;
   static_assert(!MR || DOT, "the smoother step also produces the next dots");
+  static_assert(!TILE || !MR, "the step has no tile form");
   const int64_t blk = xcd_block(blockIdx.x, nblocks);
   const int64_t V = g.V;
   const int64_t N = V * nrhs;  // elements per dof plane
   const int nq = nrhs / RB;    // threads per site
-  // the block's first element is split once, in 32 bits where it can be;
-  // V < 2^31 (the FP64 links alone take 576 bytes a site)
-  const int64_t p0 = nblocks < (1 << 23) ? (int64_t)((uint32_t)blk * 256u / (uint32_t)nq) : blk * 256 / nq;
-  const int base = (int)(blk * 256 - p0 * nq);
-  const uint32_t q0 = (uint32_t)base + threadIdx.x;
-  const int64_t p = p0 + q0 / (uint32_t)nq;
-  const int r0 = (int)(q0 % (uint32_t)nq) * RB;
-  // the reducing variant keeps every thread until the block reduction;
-  // threads past the end compute site 0 and contribute nothing
-  const bool active = p < V;
-  if (!DOT && !active) return;
-  int c[4];
-  ordered_site(g, ord, active ? (uint32_t)p : 0u, c);
+  int c[4], base = 0, r0, lc[4];
+  bool active = true;
+  if constexpr (TILE) {
+    const uint32_t ls = threadIdx.x / (uint32_t)nq;
+    r0 = (int)(threadIdx.x - ls * (uint32_t)nq) * RB;
+    Geom gt = g;
+    gt.X /= tile.b[0]; gt.Y /= tile.b[1]; gt.Z /= tile.b[2]; gt.T /= tile.b[3];
+    ordered_site(gt, ord, (uint32_t)blk, c);
+    uint32_t q = ls;
+#pragma unroll
+    for (int m = 0; m < 4; m++) {
+      const uint32_t w = q / (uint32_t)tile.b[m];
+      lc[m] = (int)(q - w * (uint32_t)tile.b[m]);
+      c[m] = c[m] * tile.b[m] + lc[m];
+      q = w;
+    }
+  } else {
+    // the block's first element is split once, in 32 bits where it can be;
+    // V < 2^31 (the FP64 links alone take 576 bytes a site)
+    const int64_t p0 = nblocks < (1 << 23) ? (int64_t)((uint32_t)blk * 256u / (uint32_t)nq) : blk * 256 / nq;
+    base = (int)(blk * 256 - p0 * nq);
+    const uint32_t q0 = (uint32_t)base + threadIdx.x;
+    const int64_t p = p0 + q0 / (uint32_t)nq;
+    r0 = (int)(q0 % (uint32_t)nq) * RB;
+    // the reducing variant keeps every thread until the block reduction;
+    // threads past the end compute site 0 and contribute nothing
+    active = p < V;
+    if (!DOT && !active) return;
+    ordered_site(g, ord, active ? (uint32_t)p : 0u, c);
+  }
   const uint32_t sy = g.X, sz = sy * (uint32_t)g.Y, st = sz * (uint32_t)g.Z;
   const uint32_t s = c[0] + sy * c[1] + sz * c[2] + st * c[3];
   constexpr uint32_t kSB = sizeof(typename P::S);
   // byte offset of this thread's first element in a plane
   const O es = ((O)s * (O)nrhs + (O)r0) * kSB;
 
+  // tile form: the tile's spinors, [12][site][rhs] in LDS
+  extern __shared__ __align__(16) unsigned char tile_smem[];
+  typename P::S* const own = reinterpret_cast<typename P::S*>(tile_smem);
+  const int ln = TILE ? tile.sites * nrhs : 0, le = (int)threadIdx.x * RB;
+  if constexpr (TILE) {
+    RawV<P, RB> v[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) v[k] = raw_ld<P, RB>(at_byte(in + k * N, es), 0);
+#pragma unroll
+    for (int k = 0; k < 12; k++) *reinterpret_cast<RawV<P, RB>*>(own + k * ln + le) = v[k];
+    __syncthreads();
+  }
   cx<R> acc[12][RB];
 #pragma unroll
   for (int k = 0; k < 12; k++)
@@ -419,13 +521,35 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
     const R sg = fwd ? (R)-1 : (R)1;  // half spinor h = u + sg * A_mu l
     const O e = ((O)sn * (O)nrhs + (O)r0) * kSB;
     cx<R> h[2][3][RB];
+    RawV<P, RB> ps[TILE ? 12 : 1];
+    if constexpr (TILE) {
+      // neighbours inside the tile from LDS, the others from memory
+      const int lm = mu == 0 ? lc[0] : mu == 1 ? lc[1] : mu == 2 ? lc[2] : lc[3];
+      const int bm = mu == 0 ? tile.b[0] : mu == 1 ? tile.b[1] : mu == 2 ? tile.b[2] : tile.b[3];
+      const int dm = (mu == 0 ? 1 : mu == 1 ? tile.b[0] : mu == 2 ? tile.b[0] * tile.b[1] : tile.b[0] * tile.b[1] * tile.b[2]) * nrhs;
+      const bool edge = fwd ? lm == bm - 1 : lm == 0;
+      const int l2 = edge ? le + (bm == ex ? (fwd ? -(bm - 1) * dm : (bm - 1) * dm) : 0) : fwd ? le + dm : le - dm;
+#pragma unroll
+      for (int k = 0; k < 12; k++) ps[k] = *reinterpret_cast<const RawV<P, RB>*>(own + k * ln + l2);
+      if (edge && bm != ex) {
+#pragma unroll
+        for (int k = 0; k < 12; k++) ps[k] = raw_ld<P, RB>(at_byte(in + k * N, e), 0);
+      }
+    }
 #pragma unroll
     for (int a = 0; a < 3; a++) {
       cx<R> u0[RB], u1[RB], l0[RB], l1[RB];
-      P::template ldv<RB>(at_byte(in + (0 * 3 + a) * N, e), 0, u0);
-      P::template ldv<RB>(at_byte(in + (1 * 3 + a) * N, e), 0, u1);
-      P::template ldv<RB>(at_byte(in + (2 * 3 + a) * N, e), 0, l0);
-      P::template ldv<RB>(at_byte(in + (3 * 3 + a) * N, e), 0, l1);
+      if constexpr (TILE) {
+        raw_cvt<P, RB>(ps[a], u0);
+        raw_cvt<P, RB>(ps[3 + a], u1);
+        raw_cvt<P, RB>(ps[6 + a], l0);
+        raw_cvt<P, RB>(ps[9 + a], l1);
+      } else {
+        P::template ldv<RB>(at_byte(in + (0 * 3 + a) * N, e), 0, u0);
+        P::template ldv<RB>(at_byte(in + (1 * 3 + a) * N, e), 0, u1);
+        P::template ldv<RB>(at_byte(in + (2 * 3 + a) * N, e), 0, l0);
+        P::template ldv<RB>(at_byte(in + (3 * 3 + a) * N, e), 0, l1);
+      }
 #pragma unroll
       for (int j = 0; j < RB; j++) {
         cx<R> a0, a1;
@@ -487,7 +611,12 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
   for (int chi = 0; chi < 2; chi++) {
     cx<R> pv[6][RB];
 #pragma unroll
-    for (int k = 0; k < 6; k++) P::template ldv<RB>(at_byte(in + (6 * chi + k) * N, es), 0, pv[k]);
+    for (int k = 0; k < 6; k++) {
+      if constexpr (TILE)
+        raw_cvt<P, RB>(*reinterpret_cast<const RawV<P, RB>*>(own + (6 * chi + k) * ln + le), pv[k]);
+      else
+        P::template ldv<RB>(at_byte(in + (6 * chi + k) * N, es), 0, pv[k]);
+    }
     cx<R> xv[6][RB];
     if (MR) {
 #pragma unroll
@@ -542,8 +671,26 @@ __global__ __launch_bounds__(256) void k_dslash(typename P::S* __restrict__ out,
       dqq[j] = (double)sqq[j];
     }
   } else if (active) {
+    // two loops: the compiler would join an either-or store and lose the hint
+    if (ord.stream) {
+      asm volatile("" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < 12; k++) P::template stv<RB>(at_byte(out + k * N, es), 0, acc[k]);
+      for (int k = 0; k < 12; k++) {
+        typename P::S e[RB];
+        P::template stv<RB>(e, 0, acc[k]);
+        RawV<P, RB> w;
+        __builtin_memcpy(&w, e, sizeof(w));
+        __builtin_nontemporal_store(w, reinterpret_cast<RawV<P, RB>*>(at_byte(out + k * N, es)));
+      }
+      asm volatile("" ::: "memory");
+    } else {
+#pragma unroll
+      for (int k = 0; k < 12; k++) P::template stv<RB>(at_byte(out + k * N, es), 0, acc[k]);
+    }
+  }
+  if (DOT && TILE) {
+    tile_dot_store<RB>(dqr, dqq, nrhs, tile.sites, nblocks, tile_smem, dpart);
+    return;
   }
   if (DOT) dot_block_store<RB>(dqr, dqq, active, base, nrhs, nblocks, dpart);
 }
@@ -1227,6 +1374,14 @@ int64_t FineOp::nblocks(mgm_prec p, int nrhs, bool dot) const {
   return (g.V * (nrhs / rb_of(p, nrhs, dot)) + 255) / 256;
 }
 
+// Results longer than the 256 MB last-level cache are not kept: their stores leave its
+// lines, and L2's, to the input (FP32 at 12 rhs on 24^3 x 48 699 us to 682, FP64 at 20 rhs on
+// 16^3 x 32 533 to 516).  Shorter ones stay for the kernel that reads them next (the
+// 16^4 solve takes 1 % longer without).
+static bool streams(const Geom& g, mgm_prec p, int nrhs) {
+  return 12.0 * g.V * nrhs * (double)prec_bytes(p) > 256e6;
+}
+
 // Rows of 8 planes (4 in FP64, whose sites are twice as long) of 4 time slices, so that neighbours in z and t are read
 // while their lines are still in the XCD's L2 (FP32, 20 rhs on 32^4: 2.13 ms against
 // 2.38 lexicographic, 12 rhs on 24^3 x 48: 0.84 against 0.90; FP64, 4 rhs on 32^4:
@@ -1234,8 +1389,8 @@ int64_t FineOp::nblocks(mgm_prec p, int nrhs, bool dot) const {
 // lexicographically: their index arithmetic is shorter, which shows in launches
 // of 20 us.
 static SiteOrder site_order(const Geom& g, mgm_prec p, int nrhs) {
-  if (12.0 * g.V * nrhs * (double)prec_bytes(p) <= 32e6) return SiteOrder{0, 0, 0};
-  return SiteOrder{1, std::min(g.Z, p == MGM_PREC_F64 ? 4 : 8), std::min(g.T, 4)};
+  if (12.0 * g.V * nrhs * (double)prec_bytes(p) <= 32e6) return SiteOrder{0, 0, 0, false};
+  return SiteOrder{1, std::min(g.Z, p == MGM_PREC_F64 ? 4 : 8), std::min(g.T, 4), streams(g, p, nrhs)};
 }
 
 // Extra arrays of the smoother-step mode (all null otherwise).
@@ -1245,15 +1400,109 @@ struct MrArgs {
   const double* qq = nullptr;
 };
 
+// A tile of the lattice and its rhs per thread.  Blocks of 103 to 256 threads (FP64 dots
+// with more than 256 in any box of a fitting count: 577 to 768, which fill a CU as
+// well; 257 to 576 leave a third of its wave slots empty: FP64 at 12 rhs on 16^4
+// 121 us at 192 threads, 153 at 384, 119 at 768), four fifths of their lanes used.  Of these the
+// box with the fewest lines read per site: the centre and the hops out of the box,
+// rounded up to whole 128-byte lines of an x-run, and the field groups (9 / nrhs
+// spinors' worth) by the same measure.
+// Taken where that is at most 6 of 9 spinors (measured, 16^4: FP64 5.0 at 16 rhs 165 us
+// to 208 untiled, 6.0 at 32 rhs 361 to 415; FP32 4.5 at 16 rhs 84 to 123, 6.7 at 50 rhs 320 to
+// 326, 7.7 at 25 rhs 165 to 151, 6.5 at 1 rhs 18.6 to 18.4), every CU gets a block and the
+// fullest at most 5/4 of the mean (FP32 at 4 rhs on 12 x 10 x 14 x 18, 336 blocks: 26.1 us to 24.6),
+// and a plane fits 32-bit offsets.  Not in FP16, whose spinors leave more of the
+// time to arithmetic (4 rhs on 24^3 x 48: 205 us to 193; 50 rhs on 16^4: 253 to 188).
+struct TilePlan {
+  Tile t{};
+  int rb = 0;
+};
+static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan* plan) {
+  const Geom& g = op.g;
+  if (p != MGM_PREC_F64 && p != MGM_PREC_F32) return false;
+  const int sb = (int)prec_bytes(p);
+  if ((double)g.V * nrhs * sb > 4294967295.0) return false;
+  const int rb = p == MGM_PREC_F32 && !dot && nrhs % 2 == 0 ? 2 : 1;
+  const int nq = nrhs / rb;
+  if (nq > 256 || g.V / op.ctx->cu_count * nq < 103) return false;
+  int div[4][9], nd[4];
+  const int ext[4] = {g.X, g.Y, g.Z, g.T};
+  for (int m = 0; m < 4; m++) {
+    nd[m] = 0;
+    for (int d = 1; d <= 8 && d <= ext[m]; d++)
+      if (ext[m] % d == 0) div[m][nd[m]++] = d;
+    if (m == 0 && ext[m] % 16 == 0) div[m][nd[m]++] = 16;
+  }
+  auto search = [&](int lo, int hi) {
+    double best = 1e9;
+    for (int a = 0; a < nd[0]; a++)
+      for (int b = nd[1] - 1; b >= 0; b--)  // of equals the longer in y
+        for (int c = 0; c < nd[2]; c++) {
+          const int s3 = div[0][a] * div[1][b] * div[2][c];
+          int d = nd[3] - 1;  // the longest that fits
+          while (d >= 0 && s3 * div[3][d] * nq > hi) d--;
+          if (d < 0) continue;
+          const int bx[4] = {div[0][a], div[1][b], div[2][c], div[3][d]};
+          const int sites = s3 * bx[3], th = sites * nq;
+          if (th < lo || 5 * th < 4 * ((th + 63) / 64 * 64)) continue;
+          if (dot && sites * nrhs < 256) continue;  // bounds the partial sums
+          const int64_t cus = op.ctx->cu_count, nb = g.V / sites;
+          if (nb < cus || 4 * ((nb + cus - 1) / cus * cus) > 5 * nb) continue;
+          double reads = 1;
+          for (int m = 0; m < 4; m++)
+            if (bx[m] != ext[m]) reads += 2.0 / bx[m];
+          const int run = bx[0] * nrhs * sb;
+          const double lines = reads * ((run + 127) / 128 * 128) / run;
+          const double cost = lines + 9.0 / nrhs * std::max(1.0, 8.0 / bx[0]);
+          if (lines <= 6.0 && cost < best) {
+            best = cost;
+            plan->t = Tile{{bx[0], bx[1], bx[2], bx[3]}, sites};
+            plan->rb = rb;
+          }
+        }
+    return best < 1e9;
+  };
+  if (search(103, 256)) return true;
+  return dot && p == MGM_PREC_F64 && (size_t)12 * kTileThreads * sb <= op.ctx->max_lds && search(577, kTileThreads);
+}
+
+template <class P, bool DOT, int RB>
+static int64_t launch_tile_p(const FineOp& op, const typename P::S* U, const typename P::RS* C, const void* x, void* y,
+                             int nrhs, double2* dpart, const Tile& t) {
+  using S = typename P::S;
+  const Geom& g = op.g;
+  const int64_t nb = g.V / t.sites;
+  const size_t lds = (size_t)12 * t.sites * nrhs * sizeof(S);
+  auto* k = k_dslash<P, DOT, false, RB, uint32_t, true>;
+  if (lds > 65536)
+    MGM_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  // past the L2s: two layers of tiles in t, whole xy planes of them (FP32 at 12 rhs on
+  // 24^3 x 48 711 us to 699, FP64 at 20 rhs on 16^3 x 32 525 to 497)
+  SiteOrder ord{};
+  if (12.0 * g.V * nrhs * sizeof(S) > 32e6) ord = SiteOrder{g.Y / t.b[1], 1, 2, streams(g, P::prec, nrhs)};
+  hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(t.sites * nrhs / RB), lds, op.ctx->stream, (S*)y, (const S*)x, U, C,
+                     g, nrhs, nb, ord, t, dpart, (S*)nullptr, (const double2*)nullptr, (const double*)nullptr);
+  MGM_LAUNCH_CHECK();
+  return nb;
+}
+template <bool DOT>
+static int64_t launch_tile(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart,
+                           const TilePlan& pl) {
+  if (p == MGM_PREC_F64) return launch_tile_p<F64, DOT, 1>(op, op.U64, op.C64, x, y, nrhs, dpart, pl.t);
+  if constexpr (!DOT)
+    if (pl.rb == 2) return launch_tile_p<F32, DOT, 2>(op, op.U32, op.C32, x, y, nrhs, dpart, pl.t);
+  return launch_tile_p<F32, DOT, 1>(op, op.U32, op.C32, x, y, nrhs, dpart, pl.t);
+}
+
 template <class P, bool DOT, bool MR, int RB>
 static int64_t launch_site_p(const FineOp& op, const typename P::S* U, const typename P::RS* C, const void* x, void* y,
                           int nrhs, double2* dpart, SiteOrder ord, const MrArgs& mr) {
   using S = typename P::S;
   const int64_t nb = (op.g.V * (nrhs / RB) + 255) / 256;
-  auto* k = (double)op.g.V * nrhs * sizeof(S) <= 4294967295.0 ? k_dslash<P, DOT, MR, RB, uint32_t>
-                                                             : k_dslash<P, DOT, MR, RB, int64_t>;
+  auto* k = (double)op.g.V * nrhs * sizeof(S) <= 4294967295.0 ? k_dslash<P, DOT, MR, RB, uint32_t, false>
+                                                             : k_dslash<P, DOT, MR, RB, int64_t, false>;
   hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(256), 0, op.ctx->stream, (S*)y,
-                     (const S*)x, U, C, op.g, nrhs, nb, ord, dpart, (S*)mr.x, mr.qr, mr.qq);
+                     (const S*)x, U, C, op.g, nrhs, nb, ord, Tile{}, dpart, (S*)mr.x, mr.qr, mr.qq);
   MGM_LAUNCH_CHECK();
   return nb;
 }
@@ -1413,7 +1662,7 @@ static int64_t launch_march(const FineOp& op, mgm_prec p, const void* x, void* y
 // then every plane-marching shape that applies.  Untuned, FP16 takes the form
 // with the smallest estimated time (the first marching shape that applies left
 // 224 of 256 CUs idle on 16^4: 166 us against 31 at 4 rhs), FP32 and FP64
-// variant 0.  Returns the block count of the variant that ran.
+// the tile form (the last variant) where there is a plan, else variant 0.  Returns the block count of the variant that ran.
 template <bool DOT>
 static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart) {
   const int rb0 = rb_of(p, nrhs, DOT);
@@ -1424,15 +1673,23 @@ static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* 
                           std::to_string(op.g.V) + "/" + std::to_string(nrhs);
   int64_t nb = 0;
   int dflt = 0;
+  const int nold = nsite + (int)shapes.size();
+  TilePlan tile;
+  const bool tiled = tile_plan(op, p, nrhs, DOT, &tile);
+  if (tiled) dflt = nold;
   if (p == MGM_PREC_F16) {
     const int i = best_shape(op, p, nrhs, shapes, DOT, false);
     if (i >= 0) dflt = nsite + i;
   }
   op.ctx->choose(
-      key, nsite + (int)shapes.size(),
+      key, nold,
       [&](int v) {
-    MGM_CHECK(v >= 0 && v < nsite + (int)shapes.size(), MGM_ERR_INVALID_ARG,
+    MGM_CHECK(v >= 0 && v < nold + (tiled ? 1 : 0), MGM_ERR_INVALID_ARG,
               "dslash launch variant out of range for this shape");
+    if (v == nold) {
+      nb = launch_tile<DOT>(op, p, x, y, nrhs, dpart, tile);
+      return;
+    }
     if (v >= nsite) {
       nb = launch_march<DOT, false>(op, p, x, y, nrhs, dpart, shapes[v - nsite]);
       return;
@@ -1444,7 +1701,7 @@ static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* 
     else
       nb = launch_rb<DOT, 1>(op, p, x, y, nrhs, dpart, ord);
       },
-      dflt);
+      dflt, tiled ? 1 : 0);
   return nb;
 }
 
