@@ -429,8 +429,7 @@ struct Tile {
 // in LDS, so hops inside the box (4 of 8 in a box of 4 x 2 x 2 x 4) and the centre
 // do not read L1 again.  The box is rarely larger than 32 sites: blocks of three or four
 // waves fill a CU's wave slots and do not wait for each other.  FP64 at 12 rhs on
-// 16^4 161 us to 122, at 4 rhs 90 to 51, at 20 rhs on 16^3 x 32 535 to 497; FP32 at 12 rhs
-// on 24^3 x 48 808 to 699 (38 million L1 lines instead of 66), then bound by reads past
+// 16^4 161 us to 143, at 4 rhs 66 to 48; FP32 at 12 rhs on 24^3 x 48 699 to 614 (38 million L1 lines instead of 66), then bound by reads past
 // L2: the boxes an XCD has in flight exceed its 4 MB, 25 million lines come from
 // beyond, 9 million would do.
 // Same sums in the same order as the untiled form.
@@ -503,13 +502,24 @@ __global__ __launch_bounds__(TILE ? kTileThreads : 256) void k_dslash(typename P
   for (int k = 0; k < 12; k++)
 #pragma unroll
     for (int j = 0; j < RB; j++) acc[k][j] = {0, 0};
-  // The eight hops run as a loop that is not unrolled, so only one
-  // neighbour's spinor and link are live at a time (registers stay low and
-  // occupancy high enough to cover HBM latency).
+  // One hop's spinor and link are live at a time (registers stay low and occupancy
+  // high enough to cover memory latency), but the directions are constants: with the
+  // loop over all hops rolled, the spin projections were moves and sign flips
+  // chosen at run time (FP16 step, 12 rhs on 16^4, 80 us to 64; FP32, 12 rhs on 24^3 x 48, 682
+  // to 612; FP16 56 to 43).  FP64 and FP32 unroll the sense too, each hop behind a
+  // scalar branch that is always taken and keeps its loads from moving up (one FP64
+  // rhs on 8^4 10.6 us to 9.3; FP16 step 64 to 70, so not there).
+  constexpr int kDirs = std::is_same<P, F16>::value ? 1 : 2;  // senses per trip
+  int one;
+  asm volatile("s_mov_b32 %0, 1" : "=s"(one));
+#pragma unroll
+  for (int mu = 0; mu < 4; mu++)
 #pragma unroll 1
-  for (int hop = 0; hop < 8; hop++) {
-    const int mu = hop >> 1;
-    const bool fwd = (hop & 1) == 0;
+  for (int s0 = 0; s0 < 2; s0 += kDirs)
+#pragma unroll
+  for (int s1 = 0; s1 < kDirs; s1++) {
+    const bool fwd = s0 + s1 == 0;
+    if (kDirs == 2 && one == 0) continue;
     const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
     const int ex = mu == 0 ? g.X : mu == 1 ? g.Y : mu == 2 ? g.Z : g.T;
     const uint32_t sd = mu == 0 ? 1u : mu == 1 ? sy : mu == 2 ? sz : st;
@@ -1155,11 +1165,9 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
     S* const cur = pl + (i & 1) * plane_elems;  // plane z
     S* const nxt = pl + ((i & 1) ^ 1) * plane_elems;  // plane z + 1, staged during this step
     __syncthreads();  // plane z staged; every read of the other buffer done
-    // x and y hops from LDS
-#pragma unroll 1
-    for (int hop = 0; hop < 4; hop++) {
-      const int mu = hop >> 1;
-      const bool fwd = (hop & 1) == 0;
+    // x and y hops from LDS (the direction a constant: FP16 step, 4 rhs on
+    // 32^3 x 64, 622 us to 607)
+    auto plane_hop = [&](const int mu, const bool fwd) __attribute__((always_inline)) {
       int lrow, lcol;
       uint32_t ls;  // site owning the link
       if (mu == 0) {
@@ -1177,7 +1185,11 @@ __global__ __launch_bounds__(MAXT) void k_dslash_march(typename P::S* __restrict
       for (int k = 0; k < 12; k++) ps[k] = cur[lidx(k, lrow, lcol)];
       hop_raw<P, PK>(ps, mu, fwd, ru, upb, ls, gg);
       hop_add<P>(mu, fwd, (R)-0.5, gg, acc);
-    }
+    };
+#pragma unroll
+    for (int mu = 0; mu < 2; mu++)
+#pragma unroll 1
+      for (int sense = 0; sense < 2; sense++) plane_hop(mu, sense == 0);
     if (!kTEarly) t_hops(z, acc);
     // next plane (kept raw for staging); its loads overlap the clover term
     S nx[12];
@@ -1400,19 +1412,20 @@ struct MrArgs {
   const double* qq = nullptr;
 };
 
-// A tile of the lattice and its rhs per thread.  Blocks of 103 to 256 threads (FP64 dots
-// with more than 256 in any box of a fitting count: 577 to 768, which fill a CU as
-// well; 257 to 576 leave a third of its wave slots empty: FP64 at 12 rhs on 16^4
-// 121 us at 192 threads, 153 at 384, 119 at 768), four fifths of their lanes used.  Of these the
+// A tile of the lattice and its rhs per thread.  Blocks of 103 to 256 threads, four
+// fifths of their lanes used; in FP64, where no such box is taken, 577 to 768, which fill a
+// CU as well (257 to 576 leave a third of its wave slots empty: FP64 at 12 rhs on 16^4
+// 121 us at 192 threads, 153 at 384, 119 at 768).  Of these the
 // box with the fewest lines read per site: the centre and the hops out of the box,
 // rounded up to whole 128-byte lines of an x-run, and the field groups (9 / nrhs
 // spinors' worth) by the same measure.
-// Taken where that is at most 6 of 9 spinors (measured, 16^4: FP64 5.0 at 16 rhs 165 us
-// to 208 untiled, 6.0 at 32 rhs 361 to 415; FP32 4.5 at 16 rhs 84 to 123, 6.7 at 50 rhs 320 to
-// 326, 7.7 at 25 rhs 165 to 151, 6.5 at 1 rhs 18.6 to 18.4), every CU gets a block and the
-// fullest at most 5/4 of the mean (FP32 at 4 rhs on 12 x 10 x 14 x 18, 336 blocks: 26.1 us to 24.6),
-// and a plane fits 32-bit offsets.  Not in FP16, whose spinors leave more of the
-// time to arithmetic (4 rhs on 24^3 x 48: 205 us to 193; 50 rhs on 16^4: 253 to 188).
+// Taken where the first is below 6 of 9 spinors (against the untiled form, 16^4: FP64 2.9 at
+// 1 rhs 26.6 us to 20.8, 4.0 at 4 rhs 66 to 48, 5.0 at 12 rhs 161 to 143, 6.0 at 32 rhs 384 to 392;
+// FP32 4.5 at 12 rhs 78 to 65, 7.7 at 25 rhs 151 to 165), every CU gets a block and
+// the fullest at most 5/4 of the mean (FP32 at 4 rhs on 12 x 10 x 14 x 18, 336 blocks: 24.6 us to
+// 26.1), and a plane fits 32-bit offsets.  In FP32 every CU gets two blocks' worth of threads
+// (1 rhs on 16^4 12.6 us to 14.0).  Not in FP16, whose spinors leave more of the
+// time to arithmetic (12 rhs on 16^4: 59 us to 60 at best, 50 rhs 188 to 253).
 struct TilePlan {
   Tile t{};
   int rb = 0;
@@ -1424,7 +1437,7 @@ static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan
   if ((double)g.V * nrhs * sb > 4294967295.0) return false;
   const int rb = p == MGM_PREC_F32 && !dot && nrhs % 2 == 0 ? 2 : 1;
   const int nq = nrhs / rb;
-  if (nq > 256 || g.V / op.ctx->cu_count * nq < 103) return false;
+  if (nq > 256 || g.V / op.ctx->cu_count * nq < (p == MGM_PREC_F32 ? 512 : 103)) return false;
   int div[4][9], nd[4];
   const int ext[4] = {g.X, g.Y, g.Z, g.T};
   for (int m = 0; m < 4; m++) {
@@ -1454,7 +1467,7 @@ static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan
           const int run = bx[0] * nrhs * sb;
           const double lines = reads * ((run + 127) / 128 * 128) / run;
           const double cost = lines + 9.0 / nrhs * std::max(1.0, 8.0 / bx[0]);
-          if (lines <= 6.0 && cost < best) {
+          if (lines < 6.0 && cost < best) {
             best = cost;
             plan->t = Tile{{bx[0], bx[1], bx[2], bx[3]}, sites};
             plan->rb = rb;
@@ -1463,7 +1476,7 @@ static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan
     return best < 1e9;
   };
   if (search(103, 256)) return true;
-  return dot && p == MGM_PREC_F64 && (size_t)12 * kTileThreads * sb <= op.ctx->max_lds && search(577, kTileThreads);
+  return p == MGM_PREC_F64 && (size_t)12 * kTileThreads * sb <= op.ctx->max_lds && search(577, kTileThreads);
 }
 
 template <class P, bool DOT, int RB>
@@ -1557,37 +1570,39 @@ static bool march_ok(const FineOp& op, mgm_prec p, int nrhs, const MarchShape& m
 // Estimated microseconds of the FP16 forms, by which the untuned default is
 // chosen and the smoother forms its column groups.  Marching: a CU holds 1024
 // threads of these kernels (128 VGPRs) or as many blocks as its LDS; a plane of
-// a resident set of th threads takes 7 us of latency plus 12.7 ns a thread
-// (20 us for a full CU at 8 rhs per block on 32^3 x 64), a block zs + 1 planes.
+// a resident set of th threads takes 6.5 us of latency plus 11.5 ns a thread in
+// the step (18 us for a full CU at 8 rhs per block on 32^3 x 64), four fifths of
+// that in the dslash; a block takes zs + 1 planes.
 // Rows of fewer than 4 rhs, and blocks that hold a small part of a site's rhs,
 // waste part of each cache line: measured 1.15x at 2 and 1.4x at 1 rhs per block,
 // 1.06x to 2.4x when a block holds one half to one tenth of them.
-static double march_us(const FineOp& op, mgm_prec p, int nrhs, const MarchShape& m, bool dot) {
+static double march_us(const FineOp& op, mgm_prec p, int nrhs, const MarchShape& m, bool dot, bool step) {
   const Geom& g = op.g;
   const int64_t blocks = (int64_t)(nrhs / m.nbr) * g.T * (g.Y / m.ty) * (g.Z / m.zs);
   const int th = g.X * m.ty * m.nbr;
   const int64_t cus = op.ctx->cu_count;
   const int64_t res = std::max<int64_t>(
       1, std::min<int64_t>(1024 / th, (int64_t)(op.ctx->max_lds / march_lds(g, p, m, dot))));
-  auto plane = [&](int64_t blocks_per_cu) { return blocks_per_cu == 0 ? 0.0 : 7.0 + 12.7e-3 * (double)(blocks_per_cu * th); };
+  auto plane = [&](int64_t blocks_per_cu) { return blocks_per_cu == 0 ? 0.0 : 6.5 + 11.5e-3 * (double)(blocks_per_cu * th); };
   const int64_t full = blocks / (cus * res), tail = (blocks - full * cus * res + cus - 1) / cus;
   const double ratio = (double)nrhs / m.nbr;
   const double line = (m.nbr == 1 ? 1.4 : m.nbr == 2 ? 1.15 : 1.0) * (1.0 + 0.015 * ratio * ratio);
-  return ((double)full * plane(res) + plane(tail)) * (m.zs + 1) * line;
+  return ((double)full * plane(res) + plane(tail)) * (m.zs + 1) * line * (step ? 1.0 : 0.8);
 }
-// Site-parallel: measured 135 ps per site and rhs for the step and 115 ps for
-// the dslash (2 rhs per thread, 4 to 8 rhs, 16^4 to 32^3 x 64), and 12 us where a
-// launch does not fill the chip.
-static double site_us(const FineOp& op, int nrhs, bool step) {
-  return 12.0 + (step ? 135e-6 : 115e-6) * (double)op.g.V * nrhs;
+// Site-parallel, one rhs per thread: measured per site and rhs 78 ps for the step, 58
+// with dots and 52 without, 36 ps a site for links and clover, and 8 us for a launch
+// (1 to 25 rhs, 16^4 to 32^3 x 64; within 15 %).  The faster form by these and the marching
+// estimates is the faster measured one at 22 of 22 such sizes.
+static double site_us(const FineOp& op, int nrhs, bool dot, bool step) {
+  return 8.0 + (double)op.g.V * ((step ? 78e-6 : dot ? 58e-6 : 52e-6) * nrhs + 36e-6);
 }
 // index of the fastest estimated shape, or -1 for the site-parallel kernel
 static int best_shape(const FineOp& op, mgm_prec p, int nrhs, const std::vector<MarchShape>& shapes, bool dot,
                       bool step, double* us = nullptr) {
   int best = -1;
-  double t = site_us(op, nrhs, step);
+  double t = site_us(op, nrhs, dot, step);
   for (size_t i = 0; i < shapes.size(); i++) {
-    const double ti = march_us(op, p, nrhs, shapes[i], dot);
+    const double ti = march_us(op, p, nrhs, shapes[i], dot, step);
     if (ti < t) {
       t = ti;
       best = (int)i;
@@ -1661,7 +1676,7 @@ static int64_t launch_march(const FineOp& op, mgm_prec p, const void* x, void* y
 // with an even rhs count also try the other rhs-per-thread count (2, 3);
 // then every plane-marching shape that applies.  Untuned, FP16 takes the form
 // with the smallest estimated time (the first marching shape that applies left
-// 224 of 256 CUs idle on 16^4: 166 us against 31 at 4 rhs), FP32 and FP64
+// 224 of 256 CUs idle on 16^4: 146 us against 19 at 4 rhs), FP32 and FP64
 // the tile form (the last variant) where there is a plan, else variant 0.  Returns the block count of the variant that ran.
 template <bool DOT>
 static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart) {
@@ -1672,7 +1687,11 @@ static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* 
   const std::string key = std::string(DOT ? "dslash_dot/" : "dslash/") + std::to_string((int)p) + "/" +
                           std::to_string(op.g.V) + "/" + std::to_string(nrhs);
   int64_t nb = 0;
-  int dflt = 0;
+  // One rhs per thread (variant 2 where 0 has two) in FP16, whose form with two is
+  // slower or the same (4 rhs on 8^4 13.2 us to 8.8, 12 on 16^4 44.9 to 42.9, 12 on 24^3 x 48
+  // 424 to 422), and in FP32 where it does not give every SIMD a wave (12 rhs on
+  // 8^4 11.5 us to 9.5; 50 rhs 21.8 to 27.8).
+  int dflt = alt && (p == MGM_PREC_F16 || op.g.V * nrhs < (int64_t)256 * op.ctx->cu_count) ? 2 : 0;
   const int nold = nsite + (int)shapes.size();
   TilePlan tile;
   const bool tiled = tile_plan(op, p, nrhs, DOT, &tile);
@@ -1748,11 +1767,11 @@ int64_t FineOp::apply_step(mgm_prec p, const void* r, void* r_next, void* x, con
   // variants: every shape with FP32 arithmetic on converted values, then
   // every shape with packed FP16 arithmetic
   const int ns = (int)shapes.size();
-  // then the site-parallel form, with FP32 arithmetic: one rhs per thread, and
-  // two (the default of the two where the count is even)
+  // then the site-parallel form, with FP32 arithmetic: one rhs per thread (the
+  // default of the two), and two
   const int nsite = nrhs % 2 ? 1 : 2;
   int dflt = best_shape(*this, p, nrhs, shapes, true, true);
-  if (dflt < 0) dflt = 2 * ns + nsite - 1;
+  if (dflt < 0) dflt = 2 * ns;
   ctx->choose(
       key, 2 * ns,
       [&](int v) {
