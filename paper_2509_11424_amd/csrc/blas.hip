@@ -28,8 +28,10 @@ __device__ __forceinline__ void std_(void* p, int64_t i, cx<double> v) {
 // rhs index of a grid-stride loop, advanced without 64-bit division
 struct RhsIter {
   int r, step, nrhs;
+  // i0 < stride, the thread count of the launch (below 2^31: 32-bit remainders, as the
+  // 64-bit ones cost more than the element)
   __device__ RhsIter(int64_t i0, int64_t stride, int nr)
-      : r((int)(i0 % nr)), step((int)(stride % nr)), nrhs(nr) {}
+      : r((int)((uint32_t)i0 % (uint32_t)nr)), step((int)((uint32_t)stride % (uint32_t)nr)), nrhs(nr) {}
   __device__ void next() {
     r += step;
     if (r >= nrhs) r -= nrhs;
@@ -42,7 +44,8 @@ struct RowRhsIter {
   int64_t row, step_row;
   int r, step_r, nrhs;
   __device__ RowRhsIter(int64_t i0, int64_t stride, int nr)
-      : row(i0 / nr), step_row(stride / nr), r((int)(i0 % nr)), step_r((int)(stride % nr)), nrhs(nr) {}
+      : row((uint32_t)i0 / (uint32_t)nr), step_row((uint32_t)stride / (uint32_t)nr),
+        r((int)((uint32_t)i0 % (uint32_t)nr)), step_r((int)((uint32_t)stride % (uint32_t)nr)), nrhs(nr) {}
   __device__ void next() {
     row += step_row;
     r += step_r;
@@ -347,63 +350,121 @@ static RedPlan red_plan(int64_t n, int nrhs) {
   return p;
 }
 
-// Block reduction of K complex values per thread into partial[blk][K][nrhs].
+// Block reduction of K complex values per thread into partial[blk][K][nrhs].  G
+// threads per column each sum every G-th of its 256 / nrhs entries, and one adds the G
+// sums (about the square root of the count each: one thread alone took 256 dependent
+// reads at one rhs).
 template <int K>
 __device__ __forceinline__ void block_store(double2 (&v)[K], double2* partial, int nrhs) {
   __shared__ double2 sh[256];
   const int t = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * blockDim.x;
+  const int base = (int)(blockIdx.x * 256u % (uint32_t)nrhs);  // column of thread 0
+  int G = 1;
+  while (G * G * nrhs < 256 && 2 * G * nrhs <= 256) G *= 2;
+  const int g = t / nrhs, r = t - g * nrhs;
 #pragma unroll
   for (int k = 0; k < K; k++) {
     sh[t] = v[k];
     __syncthreads();
-    if (t < nrhs) {
-      int t0 = (int)(((t - base % nrhs) % nrhs + nrhs) % nrhs);
-      double sr = 0, si = 0;
-      for (int u = t0; u < (int)blockDim.x; u += nrhs) {
+    double sr = 0, si = 0;
+    if (g < G) {
+      for (int u = (r < base ? r - base + nrhs : r - base) + g * nrhs; u < 256; u += G * nrhs) {
         sr += sh[u].x;
         si += sh[u].y;
       }
-      partial[((int64_t)blockIdx.x * K + k) * nrhs + t] = make_double2(sr, si);
     }
     __syncthreads();
+    if (G > 1) {
+      sh[t] = make_double2(sr, si);
+      __syncthreads();
+      if (g == 0)
+        for (int q = 1; q < G; q++) {
+          sr += sh[r + q * nrhs].x;
+          si += sh[r + q * nrhs].y;
+        }
+      __syncthreads();
+    }
+    if (g == 0) partial[((int64_t)blockIdx.x * K + k) * nrhs + r] = make_double2(sr, si);
   }
 }
 
-// Second stage of every reduction: one 64-lane wave per output entry; lane j
-// sums block partials j, j+64, ... and a fixed shuffle tree adds the lanes.
-__device__ __forceinline__ double2 wave_sum_partials(const double2* partial, int nblk, int stride, int i) {
-  double a = 0, b = 0;
-  for (int k = threadIdx.x; k < nblk; k += 64) {
-    double2 v = partial[(int64_t)k * stride + i];
-    a += v.x;
-    b += v.y;
+// Second stage of every reduction: a block of 256 threads sums OB adjacent output
+// entries, thread t the partials t / OB, t / OB + 256 / OB, ... of entry t % OB, four
+// loads in flight; a fixed tree adds the threads.  Bound by the latency of its loads
+// and, with many entries, by their lines (OB = 4 reads 64 bytes of each): 1024
+// partials of 64 entries take 4.4 us, 7.4 in single waves of 16 loads.
+template <int OB>
+__device__ __forceinline__ double2 sum_partials(const double2* partial, int nblk, int stride, int i0, int cnt) {
+  constexpr int KT = 256 / OB;
+  __shared__ double2 sh[4][OB];
+  const int t = threadIdx.x, o = t % OB, w = t / 64;
+  const int i = i0 + o < cnt ? i0 + o : cnt - 1;
+  double2 a = make_double2(0, 0);
+  for (int k0 = t / OB; k0 < nblk; k0 += 4 * KT) {
+    double2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int k = k0 + u * KT;
+      v[u] = partial[(int64_t)(k < nblk ? k : k0) * stride + i];
+      if (k >= nblk) v[u] = make_double2(0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      a.x += v[u].x;
+      a.y += v[u].y;
+    }
   }
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    a += __shfl_down(a, off, 64);
-    b += __shfl_down(b, off, 64);
+  for (int off = 32; off >= OB; off >>= 1) {
+    a.x += __shfl_down(a.x, off, 64);
+    a.y += __shfl_down(a.y, off, 64);
   }
-  return make_double2(a, b);
+  if (t % 64 < OB) sh[w][o] = a;
+  __syncthreads();
+  a = sh[0][o];
+#pragma unroll
+  for (int u = 1; u < 4; u++) {
+    a.x += sh[u][o].x;
+    a.y += sh[u][o].y;
+  }
+  return a;  // of entry i0 + t % OB, valid in threads below OB
 }
+// entries per block: four where the entries alone fill the chip (512 entries of
+// 1024 partials 10.9 us in single waves)
+static int finalize_ob(int cnt) { return cnt >= 256 ? 4 : 1; }
 
-// out[out_off + i] = sum_b partial[b][K][nrhs] entry i, for i < cnt (grid = cnt)
-__global__ void k_finalize_c(const double2* partial, int nblk, int K, int nrhs, int cnt, double2* out,
-                             int64_t out_off) {
-  const int i = blockIdx.x;
-  double2 v = wave_sum_partials(partial, nblk, K * nrhs, i);
-  if (threadIdx.x == 0) out[out_off + i] = v;
+// out[out_off + i] = sum_b partial[b][stride] entry i, for i < cnt
+template <int OB>
+__global__ __launch_bounds__(256) void k_finalize_c(const double2* partial, int nblk, int stride, int cnt,
+                                                    double2* out, int64_t out_off) {
+  const int i0 = blockIdx.x * OB;
+  const double2 v = sum_partials<OB>(partial, nblk, stride, i0, cnt);
+  if (threadIdx.x < OB && i0 + (int)threadIdx.x < cnt) out[out_off + i0 + threadIdx.x] = v;
 }
-// real parts, i < K * nrhs (grid = K * nrhs)
-__global__ void k_finalize_r(const double2* partial, int nblk, int K, int nrhs, double* out) {
-  const int i = blockIdx.x;
-  double2 v = wave_sum_partials(partial, nblk, K * nrhs, i);
-  if (threadIdx.x == 0) out[i] = v.x;
+// real parts
+template <int OB>
+__global__ __launch_bounds__(256) void k_finalize_r(const double2* partial, int nblk, int stride, int cnt,
+                                                    double* out) {
+  const int i0 = blockIdx.x * OB;
+  const double2 v = sum_partials<OB>(partial, nblk, stride, i0, cnt);
+  if (threadIdx.x < OB && i0 + (int)threadIdx.x < cnt) out[i0 + threadIdx.x] = v.x;
+}
+static void finalize_c(Context* c, const double2* partial, int nblk, int cnt, double2* out, int64_t out_off) {
+  if (finalize_ob(cnt) == 4)
+    hipLaunchKernelGGL(k_finalize_c<4>, dim3((cnt + 3) / 4), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out, out_off);
+  else
+    hipLaunchKernelGGL(k_finalize_c<1>, dim3(cnt), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out, out_off);
+}
+static void finalize_r(Context* c, const double2* partial, int nblk, int cnt, double* out) {
+  if (finalize_ob(cnt) == 4)
+    hipLaunchKernelGGL(k_finalize_r<4>, dim3((cnt + 3) / 4), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out);
+  else
+    hipLaunchKernelGGL(k_finalize_r<1>, dim3(cnt), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out);
 }
 // q^H rho (slot 0) and |q|^2 (slot 1) -> separate outputs (grid = 2 * nrhs)
-__global__ void k_finalize_dn(const double2* partial, int nblk, int nrhs, double2* qr, double* qq) {
+__global__ __launch_bounds__(256) void k_finalize_dn(const double2* partial, int nblk, int nrhs, double2* qr, double* qq) {
   const int i = blockIdx.x;
-  double2 v = wave_sum_partials(partial, nblk, 2 * nrhs, i);
+  const double2 v = sum_partials<1>(partial, nblk, 2 * nrhs, i, 2 * nrhs);
   if (threadIdx.x == 0) {
     if (i < nrhs)
       qr[i] = v;
@@ -418,11 +479,11 @@ static void need(Scratch& s, size_t entries) {
 
 template <class P>
 __global__ void k_dot(const void* x, const void* y, int nrhs, RedPlan pl, double2* partial) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[1] = {make_double2(0, 0)};
   if (g < pl.J * nrhs) {
-    int r = (int)(g % nrhs);
-    int64_t j = g / nrhs;
+    int r = (int)(g % (uint32_t)nrhs);
+    int64_t j = g / (uint32_t)nrhs;
     cx<double> a = {0, 0};
     for (int64_t m = j; m < pl.m; m += pl.J) {
       int64_t e = m * nrhs + r;
@@ -439,18 +500,17 @@ void b_dot(Context* c, Scratch& s, Vec x, Vec y, double2* out) {
   need(s, (size_t)pl.blocks * x.nrhs);
   DISPATCH_PREC(x.prec, P, hipLaunchKernelGGL(k_dot<P>, dim3(pl.blocks), dim3(256), 0, c->stream, x.p, y.p,
                                               x.nrhs, pl, s.partial));
-  hipLaunchKernelGGL(k_finalize_c, dim3(x.nrhs), dim3(64), 0, c->stream, s.partial,
-                     (int)pl.blocks, 1, x.nrhs, x.nrhs, out, (int64_t)0);
+  finalize_c(c, s.partial, (int)pl.blocks, x.nrhs, out, 0);
   MGM_LAUNCH_CHECK();
 }
 
 template <class P>
 __global__ void k_norm2(const void* x, int nrhs, RedPlan pl, double2* partial) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[1] = {make_double2(0, 0)};
   if (g < pl.J * nrhs) {
-    int r = (int)(g % nrhs);
-    int64_t j = g / nrhs;
+    int r = (int)(g % (uint32_t)nrhs);
+    int64_t j = g / (uint32_t)nrhs;
     double a = 0;
     for (int64_t m = j; m < pl.m; m += pl.J) a += norm2(ldd<P>(x, m * nrhs + r));
     v[0] = make_double2(a, 0);
@@ -463,19 +523,18 @@ void b_norm2(Context* c, Scratch& s, Vec x, double* out) {
   need(s, (size_t)pl.blocks * x.nrhs);
   DISPATCH_PREC(x.prec, P, hipLaunchKernelGGL(k_norm2<P>, dim3(pl.blocks), dim3(256), 0, c->stream, x.p,
                                               x.nrhs, pl, s.partial));
-  hipLaunchKernelGGL(k_finalize_r, dim3(x.nrhs), dim3(64), 0, c->stream, s.partial,
-                     (int)pl.blocks, 1, x.nrhs, out);
+  finalize_r(c, s.partial, (int)pl.blocks, x.nrhs, out);
   MGM_LAUNCH_CHECK();
 }
 
 // r = b - r with the norms of the stored r
 template <class P>
 __global__ void k_rsub_norm2(const void* b, void* r, int nrhs, RedPlan pl, double2* partial) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[1] = {make_double2(0, 0)};
   if (g < pl.J * nrhs) {
-    int rr = (int)(g % nrhs);
-    int64_t j = g / nrhs;
+    int rr = (int)(g % (uint32_t)nrhs);
+    int64_t j = g / (uint32_t)nrhs;
     double a = 0;
     for (int64_t m = j; m < pl.m; m += pl.J) {
       const int64_t e = m * nrhs + rr;
@@ -494,18 +553,17 @@ void b_rsub_norm2(Context* c, Scratch& s, Vec b, Vec r, double* out) {
   need(s, (size_t)pl.blocks * r.nrhs);
   DISPATCH_PREC(r.prec, P, hipLaunchKernelGGL(k_rsub_norm2<P>, dim3(pl.blocks), dim3(256), 0, c->stream, b.p,
                                               r.p, r.nrhs, pl, s.partial));
-  hipLaunchKernelGGL(k_finalize_r, dim3(r.nrhs), dim3(64), 0, c->stream, s.partial,
-                     (int)pl.blocks, 1, r.nrhs, out);
+  finalize_r(c, s.partial, (int)pl.blocks, r.nrhs, out);
   MGM_LAUNCH_CHECK();
 }
 
 template <class P>
 __global__ void k_dot_norm(const void* q, const void* rho, int nrhs, RedPlan pl, double2* partial) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[2] = {make_double2(0, 0), make_double2(0, 0)};
   if (g < pl.J * nrhs) {
-    int r = (int)(g % nrhs);
-    int64_t j = g / nrhs;
+    int r = (int)(g % (uint32_t)nrhs);
+    int64_t j = g / (uint32_t)nrhs;
     cx<double> a = {0, 0};
     double d = 0;
     for (int64_t m = j; m < pl.m; m += pl.J) {
@@ -526,7 +584,7 @@ void b_dot_norm(Context* c, Scratch& s, Vec q, Vec rho, double2* qr, double* qq)
   need(s, (size_t)pl.blocks * 2 * q.nrhs);
   DISPATCH_PREC(q.prec, P, hipLaunchKernelGGL(k_dot_norm<P>, dim3(pl.blocks), dim3(256), 0, c->stream, q.p,
                                               rho.p, q.nrhs, pl, s.partial));
-  hipLaunchKernelGGL(k_finalize_dn, dim3(2 * q.nrhs), dim3(64), 0, c->stream, s.partial,
+  hipLaunchKernelGGL(k_finalize_dn, dim3(2 * q.nrhs), dim3(256), 0, c->stream, s.partial,
                      (int)pl.blocks, q.nrhs, qr, qq);
   MGM_LAUNCH_CHECK();
 }
@@ -534,13 +592,13 @@ void b_dot_norm(Context* c, Scratch& s, Vec q, Vec rho, double2* qr, double* qq)
 template <class P, int KB>
 __global__ __launch_bounds__(256) void k_multidot(const void* base, int64_t stride, int k, const void* w, int nrhs,
                                                   RedPlan pl, double2* partial) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[KB];
 #pragma unroll
   for (int i = 0; i < KB; i++) v[i] = make_double2(0, 0);
   if (g < pl.J * nrhs) {
-    int r = (int)(g % nrhs);
-    int64_t j = g / nrhs;
+    int r = (int)(g % (uint32_t)nrhs);
+    int64_t j = g / (uint32_t)nrhs;
     cx<double> a[KB];
 #pragma unroll
     for (int i = 0; i < KB; i++) a[i] = {0, 0};
@@ -585,8 +643,7 @@ void b_multidot(Context* c, Scratch& s, Vec base, int64_t stride, int k, Vec w, 
     // block-reduction rounds follow the vectors in use
     DISPATCH_PREC(w.prec, P, launch_multidot<P>(c, (const typename P::S*)base.p + i0 * stride, stride, kk, w, pl,
                                                  s.partial));
-    hipLaunchKernelGGL(k_finalize_c, dim3(kk * w.nrhs), dim3(64), 0, c->stream, s.partial,
-                       (int)pl.blocks, kk, w.nrhs, kk * w.nrhs, out, (int64_t)i0 * w.nrhs);
+    finalize_c(c, s.partial, (int)pl.blocks, kk * w.nrhs, out, (int64_t)i0 * w.nrhs);
     MGM_LAUNCH_CHECK();
   }
 }
@@ -594,11 +651,11 @@ void b_multidot(Context* c, Scratch& s, Vec base, int64_t stride, int k, Vec w, 
 template <class P>
 __global__ void k_multiaxpy(const void* base, int64_t stride, int k, const double2* h, double sgn, void* w,
                             int nrhs, RedPlan pl, double2* partial, int want_norm, int overwrite) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[1] = {make_double2(0, 0)};
   if (g < pl.J * nrhs) {
-    int r = (int)(g % nrhs);
-    int64_t j = g / nrhs;
+    int r = (int)(g % (uint32_t)nrhs);
+    int64_t j = g / (uint32_t)nrhs;
     const typename P::S* B = (const typename P::S*)base;
     double nn = 0;
     for (int64_t m = j; m < pl.m; m += pl.J) {
@@ -629,8 +686,7 @@ void b_multiaxpy(Context* c, Scratch& s, Vec base, int64_t stride, int k, const 
                                               (const void*)base.p, stride, k, h, sgn, w.p, w.nrhs, pl,
                                               s.partial, n2 ? 1 : 0, overwrite ? 1 : 0));
   if (n2)
-    hipLaunchKernelGGL(k_finalize_r, dim3(w.nrhs), dim3(64), 0, c->stream, s.partial,
-                       (int)pl.blocks, 1, w.nrhs, n2);
+    finalize_r(c, s.partial, (int)pl.blocks, w.nrhs, n2);
   MGM_LAUNCH_CHECK();
 }
 
@@ -703,7 +759,7 @@ void b_finalize_dot_norm(Context* c, Scratch& s, const double2* part, int64_t nb
   need(s, (size_t)G * 2 * nrhs);
   hipLaunchKernelGGL(k_segment_sum, dim3(G, 2 * nrhs), dim3(256), 0, c->stream, part, nblk, 2 * nrhs,
                      s.partial);
-  hipLaunchKernelGGL(k_finalize_dn, dim3(2 * nrhs), dim3(64), 0, c->stream, s.partial, G, nrhs, qr, qq);
+  hipLaunchKernelGGL(k_finalize_dn, dim3(2 * nrhs), dim3(256), 0, c->stream, s.partial, G, nrhs, qr, qq);
   MGM_LAUNCH_CHECK();
 }
 
@@ -715,13 +771,13 @@ void b_finalize_dot_norm(Context* c, Scratch& s, const double2* part, int64_t nb
 template <class P, int K>
 __global__ __launch_bounds__(256) void k_multiaxpy_dot(const void* base, int64_t stride, const double2* h, void* w,
                                                        int nrhs, RedPlan pl, double2* partial) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
   double2 v[K];
 #pragma unroll
   for (int i = 0; i < K; i++) v[i] = make_double2(0, 0);
   if (g < pl.J * nrhs) {
-    const int r = (int)(g % nrhs);
-    const int64_t j = g / nrhs;
+    const int r = (int)(g % (uint32_t)nrhs);
+    const int64_t j = g / (uint32_t)nrhs;
     const typename P::S* B = (const typename P::S*)base;
     cx<double> hc[K], a[K];
 #pragma unroll
@@ -773,8 +829,7 @@ void b_multiaxpy_dot(Context* c, Scratch& s, Vec base, int64_t stride, int k, co
     MGM_GS_CASE(14) MGM_GS_CASE(15) MGM_GS_CASE(16)
   }
 #undef MGM_GS_CASE
-  hipLaunchKernelGGL(k_finalize_c, dim3(k * w.nrhs), dim3(64), 0, c->stream, s.partial, (int)pl.blocks, k,
-                     w.nrhs, k * w.nrhs, out, (int64_t)0);
+  finalize_c(c, s.partial, (int)pl.blocks, k * w.nrhs, out, 0);
   MGM_LAUNCH_CHECK();
 }
 
@@ -796,9 +851,9 @@ void k_gmres_start(Context* c, Givens& G, const double* r2, int nrhs) {
 // Complex Givens rotation with real cosine: for the pair (x, y),
 // x' = c x + conj(s) y, y' = -s x + c y.  Chosen to zero y for (a, b):
 // c = |a| / rho, s = b conj(a) / (|a| rho), rho = sqrt(|a|^2 + |b|^2).
-__global__ void kk_gmres_column(Givens G, int j, const double* w2, int nrhs, int reorth) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrhs) return;
+// New column j of the Hessenberg matrix of rhs r: earlier rotations, the new one, and the
+// residual estimate.  w2: squared norms of the unnormalised next basis vector.
+__device__ __forceinline__ void gmres_column(const Givens& G, int j, const double* w2, int nrhs, int reorth, int r) {
   const int m = G.m;
   cx<double> hcol[64];
   for (int i = 0; i <= j; i++) {
@@ -845,34 +900,63 @@ __global__ void kk_gmres_column(Givens G, int j, const double* w2, int nrhs, int
   G.g[(int64_t)(j + 1) * nrhs + r] = make_double2(g1.re, g1.im);
   G.est[r] = sqrt(norm2(g1));
 }
-void k_gmres_column(Context* c, Givens& G, int j, const double* w2, int nrhs, bool reorth) {
+// x /= |x| per rhs (norms n2), and the Hessenberg column: the first ncol blocks
+// form the column, which needs the same norms and nothing of the others (on its
+// own, a launch of 4.5 us after each of 2.5).
+template <class P>
+__global__ __launch_bounds__(256) void k_normalize_column(void* x, const double* n2, int64_t n, int nrhs, Givens G,
+                                                          int j, int reorth, int ncol) {
+  if ((int)blockIdx.x < ncol) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < nrhs) gmres_column(G, j, n2, nrhs, reorth, r);
+    return;
+  }
+  const int64_t stride = (int64_t)(gridDim.x - ncol) * blockDim.x;
+  int64_t i = (int64_t)(blockIdx.x - ncol) * blockDim.x + threadIdx.x;
+  for (RhsIter it(i, stride, nrhs); i < n; i += stride, it.next()) {
+    const double b = sqrt(n2[it.r]);
+    std_<P>(x, i, (b > 0.0 ? 1.0 / b : 0.0) * ldd<P>(x, i));
+  }
+}
+void b_normalize_column(Context* c, Vec x, const double* n2, Givens& G, int j, bool reorth) {
+  plain_layout(x);
   MGM_CHECK(G.m <= 63, MGM_ERR_INVALID_ARG, "restart too long");
-  hipLaunchKernelGGL(kk_gmres_column, dim3(nblocks_for(nrhs, 64)), dim3(64), 0, c->stream, G, j, w2, nrhs,
-                     reorth ? 1 : 0);
+  const int64_t n = x.n();
+  const int ncol = (int)nblocks_for(x.nrhs, 256);
+  DISPATCH_PREC(x.prec, P, hipLaunchKernelGGL(k_normalize_column<P>, dim3(ncol + (n > 0 ? ew_blocks(n) : 0)),
+                                              dim3(256), 0, c->stream, x.p, n2, n, x.nrhs, G, j, reorth ? 1 : 0,
+                                              ncol));
   MGM_LAUNCH_CHECK();
 }
 
-__global__ void kk_gmres_solve(Givens G, int k, int nrhs) {
+// y_i is kept in LDS too: read back from memory, every product waited for the
+// store of the one before
+__global__ __launch_bounds__(64) void kk_gmres_solve(Givens G, int k, int nrhs) {
+  extern __shared__ __align__(16) double2 sy[];  // [k][64]
   int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= nrhs) return;
   const int m = G.m;
   for (int i = k - 1; i >= 0; i--) {
     double2 gi = G.g[(int64_t)i * nrhs + r];
     cx<double> acc = {gi.x, gi.y};
+#pragma unroll 4
     for (int jj = i + 1; jj < k; jj++) {
       double2 Rij = G.R[((int64_t)jj * m + i) * nrhs + r];
-      double2 yj = G.y[(int64_t)jj * nrhs + r];
+      double2 yj = sy[jj * 64 + threadIdx.x];
       acc = acc - cx<double>{Rij.x, Rij.y} * cx<double>{yj.x, yj.y};
     }
     double2 Rii = G.R[((int64_t)i * m + i) * nrhs + r];
     double d = Rii.x * Rii.x + Rii.y * Rii.y;
     cx<double> yi = {0, 0};
     if (d > 0.0) yi = (1.0 / d) * cmulc(cx<double>{Rii.x, Rii.y}, acc);  // acc / Rii
+    sy[i * 64 + threadIdx.x] = make_double2(yi.re, yi.im);
     G.y[(int64_t)i * nrhs + r] = make_double2(yi.re, yi.im);
   }
 }
 void k_gmres_solve(Context* c, Givens& G, int k, int nrhs) {
-  hipLaunchKernelGGL(kk_gmres_solve, dim3(nblocks_for(nrhs, 64)), dim3(64), 0, c->stream, G, k, nrhs);
+  MGM_CHECK(k <= 63, MGM_ERR_INVALID_ARG, "restart too long");  // LDS below 64 KB
+  hipLaunchKernelGGL(kk_gmres_solve, dim3(nblocks_for(nrhs, 64)), dim3(64), (size_t)k * 64 * sizeof(double2), c->stream,
+                     G, k, nrhs);
   MGM_LAUNCH_CHECK();
 }
 

@@ -340,8 +340,7 @@ static int arnoldi(Hier& H, int l, mgm_prec p, int nrhs, int kmax, bool precond,
       }
       b_multiaxpy(c, H.scratch, base, stride, j + 1, G.h2, -1.0, Wv, w.n2a);
     }
-    b_normalize(c, Wv, w.n2a, nullptr);
-    k_gmres_column(c, G, j, w.n2a, nrhs, reorth);
+    b_normalize_column(c, Wv, w.n2a, G, j, reorth);
     k = j + 1;
     if (stop) {
       MGM_HIP(hipMemcpyAsync(pin + (j & 1) * nrhs, G.est, sizeof(double) * nrhs, hipMemcpyDeviceToHost,
