@@ -114,7 +114,7 @@ def coarse_mfma_evidence():
         return None
     try:
         sites, d = int(kv["sites"]), int(kv["dof"])
-        out = {"kernel": "k_coarse_mfma_bf16 (level-1 coarse stencil, %d sites, %d dof)" % (sites, d),
+        out = {"kernel": "k_coarse_staged_bf16 (level-1 coarse stencil, %d sites, %d dof)" % (sites, d),
                "record": os.path.relpath(COARSE_MFMA_FILE, ROOT), "peak_tflops": BF16_MFMA_PEAK_TFLOPS,
                "sources_match": kv.get("kernel_sources_sha256") == kernel_sources_hash(COARSE_SOURCES)}
         fs, ws = float(kv["fetch_scale"]), float(kv["write_scale"])

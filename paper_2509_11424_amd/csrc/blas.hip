@@ -5,6 +5,8 @@
 #include "blas.h"
 #include "group.h"
 
+#include <type_traits>
+
 namespace mgm {
 
 #define DISPATCH_PREC(pr, TAG, ...)                                     \
@@ -23,6 +25,46 @@ __device__ __forceinline__ cx<double> ldd(const void* p, int64_t i) {
 template <class P>
 __device__ __forceinline__ void std_(void* p, int64_t i, cx<double> v) {
   P::st((typename P::S*)p, i, cx<typename P::R>{(typename P::R)v.re, (typename P::R)v.im});
+}
+
+// W consecutive elements (columns of one row) at i, a multiple of W
+template <class P, int W>
+struct alignas(W * sizeof(typename P::S) < 16 ? W * sizeof(typename P::S) : 16) PackW {
+  typename P::S v[W];
+};
+template <class P, int W>
+__device__ __forceinline__ void ldw(const void* p, int64_t i, cx<double> (&v)[W]) {
+  const PackW<P, W> t = *reinterpret_cast<const PackW<P, W>*>((const typename P::S*)p + i);
+#pragma unroll
+  for (int j = 0; j < W; j++) v[j] = ldd<P>(t.v, j);
+}
+template <class P, int W>
+__device__ __forceinline__ void stw(void* p, int64_t i, const cx<double> (&v)[W]) {
+  PackW<P, W> t;
+#pragma unroll
+  for (int j = 0; j < W; j++) std_<P>(t.v, j, v[j]);
+  *reinterpret_cast<PackW<P, W>*>((typename P::S*)p + i) = t;
+}
+// Elements per thread of the element-wise kernels: 16 bytes of the narrower of their
+// formats, as far as that divides the column counts (rhs and groups) and the
+// arrays are aligned.  One element a thread read 256 bytes a wave in FP16.
+template <class PA, class PB>
+static int pack_width(int nrhs, int ga, int gb, const void* a, const void* b, const void* c) {
+  constexpr size_t narrow = sizeof(typename PA::S) < sizeof(typename PB::S) ? sizeof(typename PA::S) : sizeof(typename PB::S);
+  int w = (int)(16 / narrow);
+  if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) % 16) return 1;
+  while (w > 1 && (nrhs % w || ga % w || gb % w)) w /= 2;
+  return w;
+}
+// launch(std::integral_constant<int, W>) for the W above (at most 16 / the narrower)
+template <class PA, class PB, class F>
+static void with_width(int w, F launch) {
+  constexpr size_t narrow = sizeof(typename PA::S) < sizeof(typename PB::S) ? sizeof(typename PA::S) : sizeof(typename PB::S);
+  if constexpr (narrow <= 4)
+    if (w == 4) return launch(std::integral_constant<int, 4>());
+  if constexpr (narrow <= 8)
+    if (w == 2) return launch(std::integral_constant<int, 2>());
+  launch(std::integral_constant<int, 1>());
 }
 
 // rhs index of a grid-stride loop, advanced without 64-bit division
@@ -101,18 +143,21 @@ void b_copy(Context* c, Vec dst, Vec src) {
 
 // The scaled conversions take the column-group size of each operand (gd for
 // the destination, gs for the source; nrhs for a plain operand).
-template <class PD, class PS>
-__global__ void k_copy_scaled(void* dst, const void* src, int64_t n, int nrhs, const double* s, int gd, int gs) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+// W columns of a row per thread; n, nrhs, gd and gs are counted in columns.
+template <class PD, class PS, int W>
+__global__ __launch_bounds__(256) void k_copy_scaled(void* dst, const void* src, int64_t n, int nrhs, const double* s,
+                                                     int gd, int gs) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nw = n / W, rows = n / nrhs;
+  const bool plain = gd == nrhs && gs == nrhs;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gd == nrhs && gs == nrhs) {
-    for (RhsIter it(i, stride, nrhs); i < n; i += stride, it.next()) std_<PD>(dst, i, s[it.r] * ldd<PS>(src, i));
-    return;
+  for (RowRhsIter it(i, stride, nrhs / W); i < nw; i += stride, it.next()) {
+    const int r = it.r * W;
+    cx<double> v[W];
+    ldw<PS, W>(src, plain ? i * W : grouped_index(it.row, r, nrhs, gs, rows), v);
+#pragma unroll
+    for (int j = 0; j < W; j++) v[j] = s[r + j] * v[j];
+    stw<PD, W>(dst, plain ? i * W : grouped_index(it.row, r, nrhs, gd, rows), v);
   }
-  const int64_t rows = n / nrhs;
-  for (RowRhsIter it(i, stride, nrhs); i < n; i += stride, it.next())
-    std_<PD>(dst, grouped_index(it.row, it.r, nrhs, gd, rows),
-             s[it.r] * ldd<PS>(src, grouped_index(it.row, it.r, nrhs, gs, rows)));
 }
 static void check_groups(const Vec& v) {
   MGM_CHECK(v.group == 0 || (v.group > 0 && v.nrhs % v.group == 0), MGM_ERR_INVALID_ARG,
@@ -125,23 +170,27 @@ void b_copy_scaled(Context* c, Vec dst, Vec src, const double* s) {
   check_groups(src);
   if (n == 0) return;
   DISPATCH_PREC(dst.prec, PD, DISPATCH_PREC(src.prec, PS,
-      hipLaunchKernelGGL((k_copy_scaled<PD, PS>), dim3(ew_blocks(n)), dim3(256), 0, c->stream, dst.p, src.p, n,
-                         src.nrhs, s, dst.gs(), src.gs())));
+      with_width<PD, PS>(pack_width<PD, PS>(src.nrhs, dst.gs(), src.gs(), dst.p, src.p, nullptr), [&](auto w) {
+        hipLaunchKernelGGL((k_copy_scaled<PD, PS, decltype(w)::value>), dim3(ew_blocks(n / decltype(w)::value)),
+                           dim3(256), 0, c->stream, dst.p, src.p, n, src.nrhs, s, dst.gs(), src.gs());
+      })));
   MGM_LAUNCH_CHECK();
 }
 
-template <class PD, class PS>
-__global__ void k_sub_scaled(void* dst, const void* a, const void* b, int64_t n, int nrhs, const double* s, int gd) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+template <class PD, class PS, int W>
+__global__ __launch_bounds__(256) void k_sub_scaled(void* dst, const void* a, const void* b, int64_t n, int nrhs,
+                                                    const double* s, int gd) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nw = n / W, rows = n / nrhs;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gd == nrhs) {
-    for (RhsIter it(i, stride, nrhs); i < n; i += stride, it.next())
-      std_<PD>(dst, i, s[it.r] * (ldd<PS>(a, i) - ldd<PS>(b, i)));
-    return;
+  for (RowRhsIter it(i, stride, nrhs / W); i < nw; i += stride, it.next()) {
+    const int r = it.r * W;
+    cx<double> x[W], y[W];
+    ldw<PS, W>(a, i * W, x);
+    ldw<PS, W>(b, i * W, y);
+#pragma unroll
+    for (int j = 0; j < W; j++) x[j] = s[r + j] * (x[j] - y[j]);
+    stw<PD, W>(dst, gd == nrhs ? i * W : grouped_index(it.row, r, nrhs, gd, rows), x);
   }
-  const int64_t rows = n / nrhs;
-  for (RowRhsIter it(i, stride, nrhs); i < n; i += stride, it.next())
-    std_<PD>(dst, grouped_index(it.row, it.r, nrhs, gd, rows), s[it.r] * (ldd<PS>(a, i) - ldd<PS>(b, i)));
 }
 void b_sub_scaled(Context* c, Vec dst, Vec a, Vec b, const double* s) {
   int64_t n = a.n();
@@ -151,23 +200,27 @@ void b_sub_scaled(Context* c, Vec dst, Vec a, Vec b, const double* s) {
   check_groups(dst);
   if (n == 0) return;
   DISPATCH_PREC(dst.prec, PD, DISPATCH_PREC(a.prec, PS,
-      hipLaunchKernelGGL((k_sub_scaled<PD, PS>), dim3(ew_blocks(n)), dim3(256), 0, c->stream, dst.p, a.p, b.p,
-                         n, a.nrhs, s, dst.gs())));
+      with_width<PD, PS>(pack_width<PD, PS>(a.nrhs, dst.gs(), a.nrhs, dst.p, a.p, b.p), [&](auto w) {
+        hipLaunchKernelGGL((k_sub_scaled<PD, PS, decltype(w)::value>), dim3(ew_blocks(n / decltype(w)::value)),
+                           dim3(256), 0, c->stream, dst.p, a.p, b.p, n, a.nrhs, s, dst.gs());
+      })));
   MGM_LAUNCH_CHECK();
 }
 
-template <class PD, class PS>
-__global__ void k_add_scaled(void* dst, const void* src, int64_t n, int nrhs, const double* s, int gs) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+template <class PD, class PS, int W>
+__global__ __launch_bounds__(256) void k_add_scaled(void* dst, const void* src, int64_t n, int nrhs, const double* s,
+                                                    int gs) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nw = n / W, rows = n / nrhs;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gs == nrhs) {
-    for (RhsIter it(i, stride, nrhs); i < n; i += stride, it.next())
-      std_<PD>(dst, i, ldd<PD>(dst, i) + s[it.r] * ldd<PS>(src, i));
-    return;
+  for (RowRhsIter it(i, stride, nrhs / W); i < nw; i += stride, it.next()) {
+    const int r = it.r * W;
+    cx<double> x[W], y[W];
+    ldw<PD, W>(dst, i * W, x);
+    ldw<PS, W>(src, gs == nrhs ? i * W : grouped_index(it.row, r, nrhs, gs, rows), y);
+#pragma unroll
+    for (int j = 0; j < W; j++) x[j] = x[j] + s[r + j] * y[j];
+    stw<PD, W>(dst, i * W, x);
   }
-  const int64_t rows = n / nrhs;
-  for (RowRhsIter it(i, stride, nrhs); i < n; i += stride, it.next())
-    std_<PD>(dst, i, ldd<PD>(dst, i) + s[it.r] * ldd<PS>(src, grouped_index(it.row, it.r, nrhs, gs, rows)));
 }
 void b_add_scaled(Context* c, Vec dst, Vec src, const double* s) {
   int64_t n = src.n();
@@ -176,8 +229,10 @@ void b_add_scaled(Context* c, Vec dst, Vec src, const double* s) {
   check_groups(src);
   if (n == 0) return;
   DISPATCH_PREC(dst.prec, PD, DISPATCH_PREC(src.prec, PS,
-      hipLaunchKernelGGL((k_add_scaled<PD, PS>), dim3(ew_blocks(n)), dim3(256), 0, c->stream, dst.p, src.p, n,
-                         src.nrhs, s, src.gs())));
+      with_width<PD, PS>(pack_width<PD, PS>(src.nrhs, src.nrhs, src.gs(), dst.p, src.p, nullptr), [&](auto w) {
+        hipLaunchKernelGGL((k_add_scaled<PD, PS, decltype(w)::value>), dim3(ew_blocks(n / decltype(w)::value)),
+                           dim3(256), 0, c->stream, dst.p, src.p, n, src.nrhs, s, src.gs());
+      })));
   MGM_LAUNCH_CHECK();
 }
 
@@ -290,7 +345,7 @@ void b_scale_rhs(Context* c, Vec x, const double* m) {
   MGM_LAUNCH_CHECK();
 }
 
-template <class P>
+template <class P, int W>
 __global__ __launch_bounds__(256) void k_mr_update(const double2* qr, const double* qq, const void* rho_in,
                                                    void* rho, const void* q, void* y, int64_t n, int nrhs,
                                                    int y_zero) {
@@ -300,17 +355,22 @@ __global__ __launch_bounds__(256) void k_mr_update(const double2* qr, const doub
     sa[r] = d > 0.0 ? make_double2(qr[r].x / d, qr[r].y / d) : make_double2(0.0, 0.0);
   }
   __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, nw = n / W;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (RhsIter it(i, stride, nrhs); i < n; i += stride, it.next()) {
-    const cx<double> al = {sa[it.r].x, sa[it.r].y};
-    cx<double> rv = ldd<P>(rho_in, i);
-    cx<double> yv = y_zero ? cx<double>{0, 0} : ldd<P>(y, i);
-    fma_(yv, al, rv);
-    cx<double> qv = ldd<P>(q, i);
-    rv = rv - al * qv;
-    std_<P>(y, i, yv);
-    std_<P>(rho, i, rv);
+  for (RhsIter it(i, stride, nrhs / W); i < nw; i += stride, it.next()) {
+    cx<double> rv[W], yv[W], qv[W];
+    ldw<P, W>(rho_in, i * W, rv);
+    ldw<P, W>(q, i * W, qv);
+    if (!y_zero) ldw<P, W>(y, i * W, yv);
+#pragma unroll
+    for (int j = 0; j < W; j++) {
+      const cx<double> al = {sa[it.r * W + j].x, sa[it.r * W + j].y};
+      if (y_zero) yv[j] = {0, 0};
+      fma_(yv[j], al, rv[j]);
+      rv[j] = rv[j] - al * qv[j];
+    }
+    stw<P, W>(y, i * W, yv);
+    stw<P, W>(rho, i * W, rv);
   }
 }
 void b_mr_update(Context* c, const double2* qr, const double* qq, Vec rho, Vec q, Vec y, const Vec* rho_in,
@@ -325,8 +385,11 @@ void b_mr_update(Context* c, const double2* qr, const double* qq, Vec rho, Vec q
   MGM_CHECK(rho_in == nullptr || (rho_in->n() == n && rho_in->prec == rho.prec), MGM_ERR_INVALID_ARG,
             "mr update: shape mismatch");
   const void* src = rho_in ? rho_in->p : rho.p;
-  DISPATCH_PREC(rho.prec, P, hipLaunchKernelGGL(k_mr_update<P>, dim3(ew_blocks(n)), dim3(256), 0, c->stream,
-                                                qr, qq, src, rho.p, q.p, y.p, n, rho.nrhs, y_zero ? 1 : 0));
+  DISPATCH_PREC(rho.prec, P,
+      with_width<P, P>((uintptr_t)src % 16 ? 1 : pack_width<P, P>(rho.nrhs, rho.nrhs, rho.nrhs, rho.p, q.p, y.p), [&](auto w) {
+        hipLaunchKernelGGL((k_mr_update<P, decltype(w)::value>), dim3(ew_blocks(n / decltype(w)::value)), dim3(256), 0,
+                           c->stream, qr, qq, src, rho.p, q.p, y.p, n, rho.nrhs, y_zero ? 1 : 0);
+      }));
   MGM_LAUNCH_CHECK();
 }
 

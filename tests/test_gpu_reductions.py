@@ -34,3 +34,23 @@ def test_solver_norms(nrhs, kind):
     nr = from_gpu(r).reshape(nrhs, -1)
     nb = from_gpu(b).reshape(nrhs, -1)
     assert np.all(np.linalg.norm(nr, axis=1) <= 2e-10 * np.linalg.norm(nb, axis=1))
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 6, 8, 12])
+def test_mixed_solver_column_counts(nrhs):
+    """Scaled conversions and MR updates at 1, 2 and 4 columns per thread: the FP64 outer
+    residual meets the tolerance whatever the inner precision, if no column is lost."""
+    import torch
+    import paper_2509_11424_amd as m
+    dims = (8, 8, 8, 8)
+    U = gauge_field(dims, 0.4, 93)
+    op = m.Operator(m.Context(0), U, 0.3, 1.0)
+    h = m.Hierarchy(op, [(2, 2, 2, 2)], [8], seed=5, max_nrhs=nrhs, restart=12, mixed=2)
+    b = to_gpu(random_spinor(dims, 94, batch=nrhs).reshape(nrhs, -1, 12))
+    x, st = h.solve(0, b, m.solve_desc(tol=1e-10, kind="mg_mixed", smooth=4))
+    r = b - op.apply(x)
+    torch.cuda.synchronize()
+    nr = from_gpu(r).reshape(nrhs, -1)
+    nb = from_gpu(b).reshape(nrhs, -1)
+    assert st["fallbacks"] == 0
+    assert np.all(np.linalg.norm(nr, axis=1) <= 2e-10 * np.linalg.norm(nb, axis=1))
