@@ -1418,10 +1418,12 @@ struct MrArgs {
 // 121 us at 192 threads, 153 at 384, 119 at 768).  Of these the
 // box with the fewest lines read per site: the centre and the hops out of the box,
 // rounded up to whole 128-byte lines of an x-run, and the field groups (9 / nrhs
-// spinors' worth) by the same measure.
+// spinors' worth) by the same measure, with the part lines at the ends of a run (1 rhs on
+// 32^3 x 64: 16 x 2 x 2 x 4 800 us, 8 x 4 x 4 x 2 923).
 // Taken where the first is below 6 of 9 spinors (against the untiled form, 16^4: FP64 2.9 at
 // 1 rhs 26.6 us to 20.8, 4.0 at 4 rhs 66 to 48, 5.0 at 12 rhs 161 to 143, 6.0 at 32 rhs 384 to 392;
-// FP32 4.5 at 12 rhs 78 to 65, 7.7 at 25 rhs 151 to 165), every CU gets a block and
+// FP32 4.5 at 12 rhs 78 to 65, 7.7 at 25 rhs 151 to 165), past 2 GB below 4.6 (32^3 x 64: FP64
+// 5.0 at 12 rhs 5.04 ms to 5.3, 4.0 at 4 rhs 1.96 to 1.67, FP32 4.5 at 12 rhs 2.26 to 2.16), every CU gets a block and
 // the fullest at most 5/4 of the mean (FP32 at 4 rhs on 12 x 10 x 14 x 18, 336 blocks: 24.6 us to
 // 26.1), and a plane fits 32-bit offsets.  In FP32 every CU gets two blocks' worth of threads
 // (1 rhs on 16^4 12.6 us to 14.0).  Not in FP16, whose spinors leave more of the
@@ -1446,6 +1448,7 @@ static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan
       if (ext[m] % d == 0) div[m][nd[m]++] = d;
     if (m == 0 && ext[m] % 16 == 0) div[m][nd[m]++] = 16;
   }
+  const double limit = 12.0 * g.V * nrhs * sb > 2e9 ? 4.6 : 6.0;
   auto search = [&](int lo, int hi) {
     double best = 1e9;
     for (int a = 0; a < nd[0]; a++)
@@ -1466,8 +1469,8 @@ static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan
             if (bx[m] != ext[m]) reads += 2.0 / bx[m];
           const int run = bx[0] * nrhs * sb;
           const double lines = reads * ((run + 127) / 128 * 128) / run;
-          const double cost = lines + 9.0 / nrhs * std::max(1.0, 8.0 / bx[0]);
-          if (lines < 6.0 && cost < best) {
+          const double cost = lines + 9.0 / nrhs * (std::max(1.0, 8.0 / bx[0]) + 2.0 / bx[0]);
+          if (lines < limit && cost < best) {
             best = cost;
             plan->t = Tile{{bx[0], bx[1], bx[2], bx[3]}, sites};
             plan->rb = rb;
@@ -1490,9 +1493,14 @@ static int64_t launch_tile_p(const FineOp& op, const typename P::S* U, const typ
   if (lds > 65536)
     MGM_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   // past the L2s: two layers of tiles in t, whole xy planes of them (FP32 at 12 rhs on
-  // 24^3 x 48 711 us to 699, FP64 at 20 rhs on 16^3 x 32 525 to 497)
+  // 24^3 x 48 711 us to 699, FP64 at 20 rhs on 16^3 x 32 525 to 497); planes of more tiles
+  // than an XCD has in flight in bands of 4 x 4 x 4 (FP32 at 12 rhs on 32^3 x 64 2.40 ms to
+  // 2.35)
   SiteOrder ord{};
-  if (12.0 * g.V * nrhs * sizeof(S) > 32e6) ord = SiteOrder{g.Y / t.b[1], 1, 2, streams(g, P::prec, nrhs)};
+  if (12.0 * g.V * nrhs * sizeof(S) > 32e6) {
+    ord = g.X / t.b[0] * (g.Y / t.b[1]) < 100 ? SiteOrder{g.Y / t.b[1], 1, 2} : SiteOrder{4, 4, 4};
+    ord.stream = streams(g, P::prec, nrhs);
+  }
   hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(t.sites * nrhs / RB), lds, op.ctx->stream, (S*)y, (const S*)x, U, C,
                      g, nrhs, nb, ord, t, dpart, (S*)nullptr, (const double2*)nullptr, (const double*)nullptr);
   MGM_LAUNCH_CHECK();
