@@ -111,14 +111,6 @@ __device__ __forceinline__ void clover_mul(const R (&c)[36], const cx<R>* x, cx<
       fmac_(y[j], cij, x[i]);
     }
 }
-template <class P>
-__device__ __forceinline__ void clover_block(const typename P::RS* __restrict__ C, int64_t V, int64_t s, int chi,
-                                             const cx<typename P::R>* x, cx<typename P::R>* y) {
-  typename P::R c[36];
-  clover_load<P>(C, V, (uint32_t)s, chi, c);
-  clover_mul(c, x, y);
-}
-
 // A_mu l (per colour) for the chiral basis, and A_mu^H g.
 template <typename R>
 __device__ __forceinline__ void A_times(int mu, cx<R> l0, cx<R> l1, cx<R>& o0, cx<R>& o1) {

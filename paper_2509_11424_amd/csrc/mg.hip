@@ -778,8 +778,20 @@ __device__ void wilson_block(const FineOp& op, int k, int64_t s, int64_t y, cons
                              const cx<double>* p, cx<double>* out) {
   const Geom& g = op.g;
   if (k == 0) {
-    clover_block<F64>(op.C64, g.V, s, 0, p, out);
-    clover_block<F64>(op.C64, g.V, s, 1, p + 6, out + 6);
+    // entry by entry: a whole block in registers spills here
+    for (int chi = 0; chi < 2; chi++) {
+      auto c = [&](int j) { return op.C64[clover_pos<F64>(g.V, 36 * chi + j, s)]; };
+      const cx<double>* x = p + 6 * chi;
+      cx<double>* y = out + 6 * chi;
+      for (int i = 0; i < 6; i++) y[i] = c(i) * x[i];
+      int q = 0;
+      for (int i = 1; i < 6; i++)
+        for (int j = 0; j < i; j++, q++) {
+          const cx<double> cij = {c(6 + 2 * q), c(7 + 2 * q)};
+          fma_(y[i], cij, x[j]);
+          fmac_(y[j], cij, x[i]);
+        }
+    }
     return;
   }
   const bool fwd = k <= 4;
