@@ -37,3 +37,28 @@ def test_tiles_match_the_untiled_form(dims, prec, nrhs):
     n = qqb.sqrt() * x.to(torch.complex128).abs().square().sum(dim=(0, 1)).sqrt()
     assert torch.all((qra - qrb).abs() <= 1e-13 * n)
     assert torch.all((qqa - qqb).abs() <= 1e-13 * qqb)
+
+
+@pytest.mark.parametrize("dims,prec,nrhs", [((16, 16, 16, 32), "f64", 12), ((32, 32, 8, 8), "f32", 12),
+                                           ((16, 16, 32, 32), "f32", 12), ((16, 16, 32, 32), "f16", 24)])
+def test_long_vectors_match_single_columns(dims, prec, nrhs):
+    """Results stored past the caches (over 256 MB) and boxes walked in bands, against
+    launches of one column, which take neither; the same sums, so the same bits in FP64 and
+    FP32.  FP16 marching and site-parallel forms may sum in another order: one ulp."""
+    import torch
+    import paper_2509_11424_amd as m
+    op = m.Operator(m.Context(0), gauge_field(dims, 0.6, 83), 0.03, 1.0)
+    g = torch.Generator(device="cuda:0").manual_seed(nrhs)
+    xr = torch.randn((12, op.V, nrhs, 2), generator=g, device="cuda:0", dtype=torch.float32)
+    x = {"f64": lambda: torch.view_as_complex(xr.double()), "f32": lambda: torch.view_as_complex(xr),
+         "f16": lambda: xr.to(torch.float16)}[prec]()
+    y = op.apply(x, prec=prec)
+    for r in (0, 1, nrhs - 1):
+        y1 = op.apply(x[:, :, r:r + 1].contiguous(), prec=prec)
+        torch.cuda.synchronize()
+        a, b = y[:, :, r], y1[:, :, 0]
+        if prec == "f16":
+            a, b = a.double(), b.double()
+            assert torch.all((a - b).abs() <= 2.0 ** -10 * b.abs() + 2.0 ** -14)
+        else:
+            assert torch.equal(a, b)
