@@ -94,11 +94,15 @@ mgm_status mgm_context_set_stream(mgm_context ctx, void* hip_stream);
  * order.  Off by default (variant 0). */
 mgm_status mgm_context_set_autotune(mgm_context ctx, int32_t enable);
 /* Text table of the tuned shapes ("key variant ms_v0 ms_v1 ..." per line),
- * NUL-terminated, truncated to `bytes`; *needed receives the full length. */
+ * NUL-terminated, truncated to `bytes`; *needed receives the full length.  Keys
+ * name the lattice by its volume; where the variants depend on the extents, a second
+ * lattice of one volume has a line of its own, its extents behind the first word
+ * ("dslash@XxYxZxT/..."). */
 mgm_status mgm_context_tune_report(mgm_context ctx, char* buf, size_t bytes, size_t* needed);
 /* Pins launch variant `variant` (>= 0) for shape `key` (a key of the tune
  * report, e.g. from an earlier run), as if the autotuner had chosen it; later
- * launches of that shape use it whether or not tuning is enabled.  A variant
+ * launches of that shape use it whether or not tuning is enabled, on every
+ * lattice of the volume unless the key names the extents.  A variant
  * beyond the shape's count makes those launches fail with INVALID_ARG.
  * Errors: INVALID_ARG (NULL key, negative variant). */
 mgm_status mgm_context_tune_set(mgm_context ctx, const char* key, int32_t variant);

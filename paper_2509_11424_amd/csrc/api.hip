@@ -45,13 +45,31 @@ void Context::prof_end(int kclass, double bytes, hipEvent_t a) {
   if (prof.pending.size() > 4096) prof_flush();
 }
 
-int Context::choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt, int more) {
-  auto it = tune.table.find(key);
-  if (it != tune.table.end()) {
-    MGM_CHECK(it->second.variant < nvar + more, MGM_ERR_INVALID_ARG,
-              "pinned launch variant " + std::to_string(it->second.variant) + " out of range for " + key);
-    run(it->second.variant);
-    return it->second.variant;
+// key of the same launch on one lattice: "kind@XxYxZxT/rest"
+static std::string on_lattice(const std::string& key, const std::string& lattice) {
+  const size_t k = std::min(key.find('/'), key.size());
+  return key.substr(0, k) + "@" + lattice + key.substr(k);
+}
+
+const Tuner::Entry* Tuner::find(const std::string& key, const std::string& lattice) const {
+  auto at = [&](const std::string& k) {
+    auto it = table.find(k);
+    return it == table.end() ? nullptr : &it->second;
+  };
+  const Entry* all = at(key);
+  if (all && !all->pinned() && all->lattice != lattice) all = nullptr;
+  const Entry* own = lattice.empty() ? nullptr : at(on_lattice(key, lattice));
+  return own && (own->pinned() || !all || !all->pinned()) ? own : all;
+}
+
+int Context::choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt, int more,
+                    const std::string& lattice) {
+  if (const Tuner::Entry* t = tune.find(key, lattice)) {
+    const int v = t->variant;
+    MGM_CHECK(v < nvar + more, MGM_ERR_INVALID_ARG,
+              "pinned launch variant " + std::to_string(v) + " out of range for " + key);
+    run(v);
+    return v;
   }
   if (!tune.enabled || capturing || nvar + more <= 1) {
     run(dflt);
@@ -60,6 +78,7 @@ int Context::choose(const std::string& key, int nvar, const std::function<void(i
   const bool prof_was_on = prof.on;
   prof.on = false;  // tuning launches stay out of the kernel-class statistics
   Tuner::Entry e;
+  e.lattice = lattice;
   e.ms.assign(nvar + more, 0.0f);
   hipEvent_t a = take_event(), b = take_event();
   for (int v = 0; v < nvar + more; v++) {
@@ -81,7 +100,8 @@ int Context::choose(const std::string& key, int nvar, const std::function<void(i
     if (e.ms[v] < e.ms[bv]) bv = v;
   e.variant = bv;
   e.ms.resize(nvar);  // the report lists the first nvar
-  tune.table[key] = e;
+  // the first lattice of a volume has the plain key
+  tune.table[tune.table.count(key) ? on_lattice(key, lattice) : key] = e;
   prof.pool.push_back(a);
   prof.pool.push_back(b);
   prof.on = prof_was_on;

@@ -278,8 +278,16 @@ struct Tuner {
   struct Entry {
     int variant = 0;
     std::vector<float> ms;  // timing of every variant
+    std::string lattice;    // extents it was measured on, where the variants depend on them
+    bool pinned() const { return ms.empty(); }
   };
   std::map<std::string, Entry> table;
+  // Entry for a launch on `lattice` ("" where the variants do not depend on the
+  // extents).  Keys name the volume only, and two lattices of one volume have different
+  // variants: a measured entry holds for its own lattice, the next one of the volume gets
+  // an entry of its own.  A pinned entry holds for every lattice and goes before a
+  // measured one.
+  const Entry* find(const std::string& key, const std::string& lattice) const;
 };
 
 struct Context {
@@ -303,8 +311,9 @@ struct Context {
   // `dflt` is the variant used while the autotuner is off.  `more` variants
   // follow the nvar listed ones: they are tuned and pinned like them, but the
   // times of the report are those of the listed ones, whose numbers saved
-  // tables hold
-  int choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt = 0, int more = 0);
+  // tables hold.  `lattice`: the extents, where the variants depend on them
+  int choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt = 0, int more = 0,
+             const std::string& lattice = "");
 };
 
 // RAII timer around one launch of kernel class kc (no-op when profiling is off).

@@ -1679,6 +1679,10 @@ static int64_t launch_march(const FineOp& op, mgm_prec p, const void* x, void* y
   return nb;
 }
 
+static std::string lattice_of(const Geom& g) {
+  return std::to_string(g.X) + "x" + std::to_string(g.Y) + "x" + std::to_string(g.Z) + "x" + std::to_string(g.T);
+}
+
 // Tuned launch shapes.  Site-parallel variants first: 0 (rb_of, banded walk),
 // 1 the lexicographic walk, and the non-reducing FP32/FP16 kernels
 // with an even rhs count also try the other rhs-per-thread count (2, 3);
@@ -1728,7 +1732,7 @@ static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* 
     else
       nb = launch_rb<DOT, 1>(op, p, x, y, nrhs, dpart, ord);
       },
-      dflt, tiled ? 1 : 0);
+      dflt, tiled ? 1 : 0, lattice_of(op.g));
   return nb;
 }
 
@@ -1791,7 +1795,7 @@ int64_t FineOp::apply_step(mgm_prec p, const void* r, void* r_next, void* x, con
         else
           nb = launch_march<true, true>(*this, p, r, r_next, nrhs, dpart, shapes[v % ns], mr, v >= ns);
       },
-      dflt, nsite);
+      dflt, nsite, lattice_of(g));
   return nb;
 }
 
