@@ -143,6 +143,16 @@ __device__ __forceinline__ void aggregate_rows(const TGeom& t, int64_t a, uint32
 }
 __host__ __device__ inline int row_words(int rows) { return (rows + 3) & ~3; }
 
+// the value of the lane beside this one (l ^ 1)
+__device__ __forceinline__ float lane_pair(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_pair(double v) {
+  const int2 a = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, a.x, 0xB1, 0xf, 0xf, true),
+                                              __builtin_amdgcn_update_dpp(0, a.y, 0xB1, 0xf, 0xf, true)));
+}
+
 // y_c[chi k][a][r] = sum_rows conj(P[a][chi][row][k]) x[chi half + j][site(loc)][r]
 // As real products: the test vectors are the A tiles, MT of them from
 // 16 MT blockIdx.z on, the 2 nr columns (re, im of each rhs side by side) the B
@@ -193,14 +203,17 @@ __global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restric
     xb[s] = x + (int64_t)chi * t.half * t.f.V * nrhs + (r < nrhs ? r : nrhs - 1);
   }
   const int quads = (rows + 3) >> 2;
+  // quadruples in flight: four where the registers hold them (1 rhs on 16^3 x 32 in 4^4
+  // aggregates, 28 test vectors, FP32 72 us with two, 62 with four)
+  constexpr int H = NT == 1 || std::is_same<R, float>::value ? 4 : 2;
   int nchain = 0;  // steps summed in acc
 #pragma unroll 1
-  for (int u0 = w; u0 < quads; u0 += 2 * wpa) {
-    typename PM::S praw[2][MT];
-    typename P::S xraw[2][NT];
-    bool in[2];
+  for (int u0 = w; u0 < quads; u0 += H * wpa) {
+    typename PM::S praw[H][MT];
+    typename P::S xraw[H][NT];
+    bool in[H];
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
       const int row = 4 * (u0 + h * wpa) + kq;
       in[h] = row < rows;
       const int rw = in[h] ? row : 0;
@@ -211,7 +224,7 @@ __global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restric
       for (int s = 0; s < NT; s++) xraw[h][s] = xb[s][off];
     }
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
       // conj(P) x: re = Pre xre + Pim xim, im = Pre xim - Pim xre
       R b1[NT], b2[NT];
 #pragma unroll
@@ -231,7 +244,7 @@ __global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restric
         for (int s = 0; s < NT; s++) acc[m][s] = MM::mfma(a2, b2[s], acc[m][s]);
       }
     }
-    if (++nchain == 2 || u0 + 2 * wpa >= quads) {
+    if (++nchain == 4 / H || u0 + H * wpa >= quads) {
 #pragma unroll
       for (int m = 0; m < MT; m++)
 #pragma unroll
@@ -406,8 +419,13 @@ __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__
 // As real products: rows of P are the A tiles, two tiles of 16 at a time per
 // wave, the 2 nr columns (re, im of each rhs side by side, nr rhs from
 // 8 NT blockIdx.y on) the B tiles, from an LDS copy of the aggregate's coarse
-// values.  VK consecutive test vectors per A load (VK divides N_tv).
-template <class P, class PM, class PX, int NT, int VK>
+// values.  VK consecutive test vectors per A load (4 VK divides N_tv where VK > 1).
+// ALL (four waves an aggregate): the entries of P of 32 test vectors (FP64: 16) are loaded
+// together, so that the lines of a row are read once before other waves replace
+// them in L1 (FP16 added, 20 rhs on 24^3 x 48 in 4^4 aggregates, 24 test vectors, 742 us to 688);
+// else in steps, with fewer registers (FP32, 32 rhs on 16^4 in 2^4 aggregates, 12 test vectors,
+// 75 us in steps, 82 with all).
+template <class P, class PM, class PX, int NT, int VK, bool ALL>
 __global__ __launch_bounds__(256) void k_prolong(const typename P::S* __restrict__ xc, const typename P::S* __restrict__ x,
                                                  typename P::S* __restrict__ y, const typename PM::S* __restrict__ Pm,
                                                  TGeom t, int nrhs, int mode, int wpa,
@@ -454,51 +472,75 @@ __global__ __launch_bounds__(256) void k_prolong(const typename P::S* __restrict
     sc[s] = mode == 3 ? (R)xs[rb[s]] : (R)1;
     xo[s] = mode == 3 ? grouped_index(0, rb[s], nrhs, xgs, 2 * half * Vf) : (int64_t)rb[s];
   }
-  const R* src = reinterpret_cast<const R*>(mode == 1 ? x : y);
+  const typename P::S* src = mode == 1 ? x : y;
   const int ntile = (rows + 15) >> 4;
 #pragma unroll 1
   for (int t0 = MT * w; t0 < ntile; t0 += MT * wpa) {
+    // The two lanes of a column hold re and im of four rows; each loads and stores whole
+    // entries of two of them (rows j = 2 e + part): half the memory instructions
+    // of a part each (FP32, 33 rhs on 16^4 in 2^4 aggregates, 28 test vectors, 190 us to 174)
     V4 acc[MT][NT];
-    int64_t frow[MT][4];
+    int64_t frow[MT][2];
 #pragma unroll
     for (int m = 0; m < MT; m++)
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int row = 16 * (t0 + m) + MM::row(kq, j), rw = row < rows ? row : rows - 1;
-        frow[m][j] = chi * half * Vf + tab[rw];
+      for (int e = 0; e < 2; e++) {
+        const int row = 16 * (t0 + m) + MM::row(kq, 2 * e + part), rw = row < rows ? row : rows - 1;
+        frow[m][e] = chi * half * Vf + tab[rw];
       }
-    if (mode == 3) {
-      typename PX::S raw[MT][4][NT];
-#pragma unroll
-      for (int m = 0; m < MT; m++)
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-          for (int s = 0; s < NT; s++) raw[m][j][s] = xq[frow[m][j] * xgs + xo[s]];
-#pragma unroll
-      for (int m = 0; m < MT; m++)
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-          for (int s = 0; s < NT; s++) {
-            const cx<typename PX::R> u = PX::ld(&raw[m][j][s], 0);
-            acc[m][s][j] = sc[s] * (R)(part ? u.im : u.re);
-          }
-    } else if (mode != 0) {
-#pragma unroll
-      for (int m = 0; m < MT; m++)
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-          for (int s = 0; s < NT; s++) {
-            const R v = src[2 * (frow[m][j] * nrhs + xo[s]) + part];
-            acc[m][s][j] = mode == 1 ? -v : v;
-          }
-    } else {
+    if (mode == 0) {
 #pragma unroll
       for (int m = 0; m < MT; m++)
 #pragma unroll
         for (int s = 0; s < NT; s++) acc[m][s] = (V4){0, 0, 0, 0};
+    } else {
+      cx<R> v[MT][2][NT];
+      if (mode == 3) {
+        typename PX::S raw[MT][2][NT];
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int e = 0; e < 2; e++)
+#pragma unroll
+            for (int s = 0; s < NT; s++) raw[m][e][s] = xq[frow[m][e] * xgs + xo[s]];
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int e = 0; e < 2; e++)
+#pragma unroll
+            for (int s = 0; s < NT; s++) {
+              const cx<typename PX::R> u = PX::ld(&raw[m][e][s], 0);
+              v[m][e][s] = {sc[s] * (R)u.re, sc[s] * (R)u.im};
+            }
+      } else {
+        typename P::S raw[MT][2][NT];
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int e = 0; e < 2; e++)
+#pragma unroll
+            for (int s = 0; s < NT; s++) raw[m][e][s] = src[frow[m][e] * nrhs + xo[s]];
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int e = 0; e < 2; e++)
+#pragma unroll
+            for (int s = 0; s < NT; s++) {
+              const cx<R> u = P::ld(&raw[m][e][s], 0);
+              v[m][e][s] = mode == 1 ? cx<R>{-u.re, -u.im} : u;
+            }
+      }
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int e = 0; e < 2; e++)
+#pragma unroll
+          for (int s = 0; s < NT; s++) {
+            const cx<R> u = v[m][e][s];
+            const R other = lane_pair(part ? u.re : u.im);
+            acc[m][s][2 * e] = part ? other : u.re;
+            acc[m][s][2 * e + 1] = part ? u.im : other;
+          }
     }
     // acc holds -x (mode 1), y (mode 2), xs x (mode 3) or 0; the sum over k is
     // added on top and the sign restored for mode 1
@@ -508,39 +550,57 @@ __global__ __launch_bounds__(256) void k_prolong(const typename P::S* __restrict
       const int row = 16 * (t0 + m) + n;
       pr[m] = pb + (row < rows ? row : rows - 1) * K;
     }
-#pragma unroll 2
-    for (int k0 = 0; k0 < K; k0 += 4 * VK) {
-      const int kl = k0 + VK * kq;           // this lane's first test vector
-      const bool in = VK > 1 || kl < K;      // VK > 1 only where 4 VK divides K
-      cx<R> pv[MT][VK];
+    constexpr int CK = !ALL ? 4 * VK : std::is_same<R, float>::value ? 32 : 16, U = CK / (4 * VK);
+    struct alignas(VK * sizeof(typename PM::S)) Entries {
+      typename PM::S v[VK];
+    };
+#pragma unroll(ALL ? 1 : 2)
+    for (int kc = 0; kc < K; kc += CK) {
+      Entries raw[MT][U];
 #pragma unroll
-      for (int m = 0; m < MT; m++) {
-        cx<typename PM::R> v[VK];
-        PM::template ldv<VK>(pr[m], in ? kl : 0, v);
+      for (int u = 0; u < U; u++) {
+        if (kc + 4 * VK * u >= K) break;
+        const int kl = kc + 4 * VK * u + VK * kq;  // this lane's first test vector
 #pragma unroll
-        for (int e = 0; e < VK; e++) pv[m][e] = in ? cx<R>{(R)v[e].re, (R)v[e].im} : cx<R>{0, 0};
+        for (int m = 0; m < MT; m++) raw[m][u] = *reinterpret_cast<const Entries*>(pr[m] + (kl < K ? kl : 0));
       }
 #pragma unroll
-      for (int e = 0; e < VK; e++)
+      for (int u = 0; u < U; u++) {
+        if (kc + 4 * VK * u >= K) break;
+        const int kl = kc + 4 * VK * u + VK * kq;
+        const bool in = VK > 1 || kl < K;  // VK > 1 only where 4 VK divides K
 #pragma unroll
-        for (int s = 0; s < NT; s++) {
-          const cx<R> c = sC[(kl + e) * NC + 8 * s + (n >> 1)];
-          const R b1 = part ? c.im : c.re, b2 = part ? c.re : -c.im;
+        for (int e = 0; e < VK; e++) {
+          cx<R> pv[MT];
 #pragma unroll
-          for (int m = 0; m < MT; m++) acc[m][s] = MM::mfma(pv[m][e].re, b1, acc[m][s]);
+          for (int m = 0; m < MT; m++) {
+            const cx<typename PM::R> v = PM::ld(raw[m][u].v, e);
+            pv[m] = in ? cx<R>{(R)v.re, (R)v.im} : cx<R>{0, 0};
+          }
 #pragma unroll
-          for (int m = 0; m < MT; m++) acc[m][s] = MM::mfma(pv[m][e].im, b2, acc[m][s]);
+          for (int s = 0; s < NT; s++) {
+            const cx<R> c = sC[(kl + e) * NC + 8 * s + (n >> 1)];
+            const R b1 = part ? c.im : c.re, b2 = part ? c.re : -c.im;
+#pragma unroll
+            for (int m = 0; m < MT; m++) acc[m][s] = MM::mfma(pv[m].re, b1, acc[m][s]);
+#pragma unroll
+            for (int m = 0; m < MT; m++) acc[m][s] = MM::mfma(pv[m].im, b2, acc[m][s]);
+          }
         }
+      }
     }
 #pragma unroll
     for (int m = 0; m < MT; m++)
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        if (16 * (t0 + m) + MM::row(kq, j) >= rows) continue;
+      for (int e = 0; e < 2; e++) {
+        const bool row_in = 16 * (t0 + m) + MM::row(kq, 2 * e + part) < rows;
 #pragma unroll
-        for (int s = 0; s < NT; s++)
-          if (r0 + 8 * s + (n >> 1) < nrhs)
-            reinterpret_cast<R*>(y)[2 * (frow[m][j] * nrhs + rb[s]) + part] = mode == 1 ? -acc[m][s][j] : acc[m][s][j];
+        for (int s = 0; s < NT; s++) {
+          const R a = acc[m][s][2 * e], b = acc[m][s][2 * e + 1], other = lane_pair(part ? a : b);
+          const cx<R> v = part ? cx<R>{other, b} : cx<R>{a, other};
+          if (row_in && r0 + 8 * s + (n >> 1) < nrhs)
+            P::st(y, frow[m][e] * nrhs + rb[s], mode == 1 ? cx<R>{-v.re, -v.im} : v);
+        }
       }
   }
 }
@@ -614,13 +674,17 @@ static void launch_prolong_vk(Context* c, const TGeom& t, const typename P::S* x
   while (NT > 1 && need(NT) > 65536) NT--;
   const size_t lds = need(NT);
   const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((ntile + NT - 1) / NT)), tb(256);
+  auto launch = [&](auto* k) {
+    hipLaunchKernelGGL(k, nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs);
+    MGM_LAUNCH_CHECK();
+  };
+  const bool all = wpa == 4;
   switch (NT) {
-    case 1: hipLaunchKernelGGL((k_prolong<P, PM, PX, 1, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
-    case 2: hipLaunchKernelGGL((k_prolong<P, PM, PX, 2, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
-    case 3: hipLaunchKernelGGL((k_prolong<P, PM, PX, 3, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
-    default: hipLaunchKernelGGL((k_prolong<P, PM, PX, 4, VK>), nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs); break;
+    case 1: launch(all ? k_prolong<P, PM, PX, 1, VK, true> : k_prolong<P, PM, PX, 1, VK, false>); break;
+    case 2: launch(all ? k_prolong<P, PM, PX, 2, VK, true> : k_prolong<P, PM, PX, 2, VK, false>); break;
+    case 3: launch(all ? k_prolong<P, PM, PX, 3, VK, true> : k_prolong<P, PM, PX, 3, VK, false>); break;
+    default: launch(all ? k_prolong<P, PM, PX, 4, VK, true> : k_prolong<P, PM, PX, 4, VK, false>); break;
   }
-  MGM_LAUNCH_CHECK();
 }
 template <class P, class PM, class PX>
 static void launch_prolong(Context* c, const TGeom& t, const typename P::S* xc, const typename P::S* x,
