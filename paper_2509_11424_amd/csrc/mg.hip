@@ -93,11 +93,13 @@ void mg_agg_map(Context* c, const TGeom& t, int64_t* out) {
 // chains of fused multiply-adds like the scalar ones (A[i][k]: lane i + 16 k,
 // B[k][n]: lane n + 16 k; D[i][n]: lane n + 16 q, register j, row 4 q + j in
 // FP32 and 4 j + q in FP64).  An aggregate and chirality is worked on by wpa
-// waves of a 256-thread workgroup: four, or one where the aggregate has too few
-// rows for four.  P streams from memory straight into the A operand, each entry
-// read once per launch and tile of right-hand sides; workgroups go to the XCDs
-// in contiguous ranges, so that aggregates that share lines of the fine
-// vector share an L2.  Aggregates 4^4, 24 test vectors, 20 rhs on 16^3 x 32, start
+// waves of a 256-thread workgroup, four or one (transfer_split).  P streams from
+// memory straight into the A operand; workgroups go to the XCDs in contiguous
+// ranges, so that aggregates that share lines of the fine vector share an L2, and
+// the tiles of one aggregate (right-hand sides, test vectors) follow each other there,
+// as they share P and the lines at the ends of their column ranges: FP32
+// prolongation of 33 rhs on 16^3 x 32 in 2^4 aggregates, 24 test vectors, 404 us with the
+// tiles in separate passes over the lattice, 330 side by side.  Aggregates 4^4, 24 test vectors, 20 rhs on 16^3 x 32, start
 // (scalar FMAs on LDS tiles) -> now: restriction FP64 329 -> 264 us, FP32 177 ->
 // 150, FP16 200 -> 51 (277 MB: at the rate of a copy); prolongation FP64 394 -> 269,
 // FP32 203 -> 153, FP16 added 289 -> 160 (530 MB, 104 us at that rate).
@@ -143,6 +145,22 @@ __device__ __forceinline__ void aggregate_rows(const TGeom& t, int64_t a, uint32
 }
 __host__ __device__ inline int row_words(int rows) { return (rows + 3) & ~3; }
 
+// Tiles of a launch: ny groups of rhs from group y0 on, nz of test vectors.
+struct Tiles {
+  int ny, nz, y0;
+};
+struct TileAt {
+  int64_t blk;
+  int y, z;
+};
+__device__ __forceinline__ TileAt tile_at(const Tiles& p) {
+  uint32_t q = (uint32_t)xcd_block(blockIdx.x, gridDim.x);
+  const uint32_t z = q % (uint32_t)p.nz;
+  q /= (uint32_t)p.nz;
+  const uint32_t y = q % (uint32_t)p.ny;
+  return {(int64_t)(q / (uint32_t)p.ny), p.y0 + (int)y, (int)z};
+}
+
 // the value of the lane beside this one (l ^ 1)
 __device__ __forceinline__ float lane_pair(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
@@ -155,22 +173,23 @@ __device__ __forceinline__ double lane_pair(double v) {
 
 // y_c[chi k][a][r] = sum_rows conj(P[a][chi][row][k]) x[chi half + j][site(loc)][r]
 // As real products: the test vectors are the A tiles, MT of them from
-// 16 MT blockIdx.z on, the 2 nr columns (re, im of each rhs side by side) the B
-// tiles, NT of them from rhs 8 NT blockIdx.y on.  Wave w of wpa sums the row
+// 16 MT at.z on, the 2 nr columns (re, im of each rhs side by side) the B
+// tiles, NT of them from rhs 8 NT at.y on.  Wave w of wpa sums the row
 // quadruples w, w + wpa, ..., four in a chain, the chains then one after the other
 // (a chain of a whole share was up to 1.8 times further from FP64 sums), and
 // the wpa partial tiles are added in order through LDS.
 template <class P, class PM, int MT, int NT>
 __global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restrict__ x, typename P::S* __restrict__ yc,
-                                                  const typename PM::S* __restrict__ Pm, TGeom t, int nrhs, int wpa) {
+                                                  const typename PM::S* __restrict__ Pm, TGeom t, int nrhs, int wpa,
+                                                  Tiles tiles) {
   using R = typename P::R;
   using MM = Mm<R>;
   using V4 = typename MM::V4;
   extern __shared__ __align__(16) char smem[];
-  const int64_t nblk = gridDim.x;
+  const TileAt at = tile_at(tiles);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
   const int sub = wave / wpa, w = wave - sub * wpa;  // block of P of this wave, its share of the rows
-  const int64_t ac = xcd_block(blockIdx.x, nblk) * (4 / wpa) + sub;
+  const int64_t ac = at.blk * (4 / wpa) + sub;
   const bool live = ac < 2 * t.c.V;
   const int64_t a = live ? ac >> 1 : 0;
   const int chi = live ? (int)(ac & 1) : 0;
@@ -193,13 +212,13 @@ __global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restric
   const typename P::S* xb[NT];
 #pragma unroll
   for (int m = 0; m < MT; m++) {
-    const int k = 16 * (MT * (int)blockIdx.z + m) + n;
+    const int k = 16 * (MT * at.z + m) + n;
     ka[m] = k < K ? k : K - 1;
   }
   const int part = n & 1;
 #pragma unroll
   for (int s = 0; s < NT; s++) {
-    const int r = 8 * (NT * (int)blockIdx.y + s) + (n >> 1);
+    const int r = 8 * (NT * at.y + s) + (n >> 1);
     xb[s] = x + (int64_t)chi * t.half * t.f.V * nrhs + (r < nrhs ? r : nrhs - 1);
   }
   const int quads = (rows + 3) >> 2;
@@ -276,13 +295,13 @@ __global__ __launch_bounds__(256) void k_restrict(const typename P::S* __restric
   if (!live) return;
 #pragma unroll
   for (int s = 0; s < NT; s++) {
-    const int r = 8 * (NT * (int)blockIdx.y + s) + (n >> 1);
+    const int r = 8 * (NT * at.y + s) + (n >> 1);
     if (r >= nrhs) continue;
 #pragma unroll
     for (int m = 0; m < MT; m++)
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        const int k = 16 * (MT * (int)blockIdx.z + m) + MM::row(kq, j);
+        const int k = 16 * (MT * at.z + m) + MM::row(kq, j);
         if (k < K)
           reinterpret_cast<R*>(yc)[2 * (((int64_t)(chi * K + k) * Vc + a) * nrhs + r) + part] = tot[m][s][j];
       }
@@ -303,12 +322,12 @@ __device__ __forceinline__ h4_t pick4(const uint32_t (&v)[4], bool hi) {
 template <int MT, int NT>
 __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__ x, float2* __restrict__ yc,
                                                     const uint32_t* __restrict__ Pm, TGeom t, int nrhs, int wpa,
-                                                    const double* __restrict__ xs, int xgs) {
+                                                    const double* __restrict__ xs, int xgs, Tiles tiles) {
   extern __shared__ __align__(16) char smem[];
-  const int64_t nblk = gridDim.x;
+  const TileAt at = tile_at(tiles);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
   const int sub = wave / wpa, w = wave - sub * wpa;
-  const int64_t ac = xcd_block(blockIdx.x, nblk) * (4 / wpa) + sub;
+  const int64_t ac = at.blk * (4 / wpa) + sub;
   const bool live = ac < 2 * t.c.V;
   const int64_t a = live ? ac >> 1 : 0;
   const int chi = live ? (int)(ac & 1) : 0;
@@ -326,7 +345,7 @@ __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__
   int ka[MT], rb[NT];
 #pragma unroll
   for (int m = 0; m < MT; m++) {
-    const int k = 8 * (MT * (int)blockIdx.z + m) + (n >> 1);
+    const int k = 8 * (MT * at.z + m) + (n >> 1);
     ka[m] = k < K ? k : K - 1;
   }
   const bool im = n & 1;
@@ -334,7 +353,7 @@ __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__
   const uint32_t* xb[NT];
 #pragma unroll
   for (int s = 0; s < NT; s++) {
-    const int r = 16 * (NT * (int)blockIdx.y + s) + n;
+    const int r = 16 * (NT * at.y + s) + n;
     rb[s] = r < nrhs ? r : nrhs - 1;
     xb[s] = x + grouped_index(chi * half * Vf, rb[s], nrhs, xgs, 2 * half * Vf);
   }
@@ -399,14 +418,14 @@ __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__
   if (!live) return;
 #pragma unroll
   for (int s = 0; s < NT; s++) {
-    const int r = 16 * (NT * (int)blockIdx.y + s) + n;
+    const int r = 16 * (NT * at.y + s) + n;
     if (r >= nrhs) continue;
     const float sc = (float)xs[r];
 #pragma unroll
     for (int m = 0; m < MT; m++)
 #pragma unroll
       for (int j = 0; j < 4; j += 2) {
-        const int k = 8 * (MT * (int)blockIdx.z + m) + ((4 * kq + j) >> 1);
+        const int k = 8 * (MT * at.z + m) + ((4 * kq + j) >> 1);
         if (k < K)
           yc[((int64_t)(chi * K + k) * Vc + a) * nrhs + r] = make_float2(sc * acc[m][s][j], sc * acc[m][s][j + 1]);
       }
@@ -418,7 +437,7 @@ __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__
 // groups of xgs right-hand sides)
 // As real products: rows of P are the A tiles, two tiles of 16 at a time per
 // wave, the 2 nr columns (re, im of each rhs side by side, nr rhs from
-// 8 NT blockIdx.y on) the B tiles, from an LDS copy of the aggregate's coarse
+// 8 NT at.y on) the B tiles, from an LDS copy of the aggregate's coarse
 // values.  VK consecutive test vectors per A load (4 VK divides N_tv where VK > 1).
 // ALL (four waves an aggregate): the entries of P of 32 test vectors (FP64: 16) are loaded
 // together, so that the lines of a row are read once before other waves replace
@@ -430,20 +449,20 @@ __global__ __launch_bounds__(256) void k_prolong(const typename P::S* __restrict
                                                  typename P::S* __restrict__ y, const typename PM::S* __restrict__ Pm,
                                                  TGeom t, int nrhs, int mode, int wpa,
                                                  const typename PX::S* __restrict__ xq, const double* __restrict__ xs,
-                                                 int xgs) {
+                                                 int xgs, Tiles tiles) {
   using R = typename P::R;
   using MM = Mm<R>;
   using V4 = typename MM::V4;
   constexpr int MT = 2, NC = 8 * NT;  // row tiles per step, rhs per workgroup
   extern __shared__ __align__(16) char smem[];
-  const int64_t nblk = gridDim.x;
+  const TileAt at = tile_at(tiles);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
   const int sub = wave / wpa, w = wave - sub * wpa;
-  const int64_t ac = xcd_block(blockIdx.x, nblk) * (4 / wpa) + sub;
+  const int64_t ac = at.blk * (4 / wpa) + sub;
   const bool live = ac < 2 * t.c.V;
   const int64_t a = live ? ac >> 1 : 0;
   const int chi = live ? (int)(ac & 1) : 0;
-  const int K = t.ntv, half = t.half, rows = t.rows, r0 = NC * (int)blockIdx.y;
+  const int K = t.ntv, half = t.half, rows = t.rows, r0 = NC * at.y;
   const int Kp = (K + 4 * VK - 1) / (4 * VK) * (4 * VK);
   const int64_t Vc = t.c.V, Vf = t.f.V;
   uint32_t* tab = reinterpret_cast<uint32_t*>(smem) + sub * row_words(t.rows);
@@ -611,79 +630,116 @@ double Transfer::bytes(mgm_prec p, int nrhs) const {
          (double)t.c.V * t.c.dof * nrhs * w;
 }
 
-// waves per aggregate and chirality: 2^4 aggregates of the fine level have 96
-// rows, six per wave quadruple and step (FP16 restriction, 12 test vectors, 12 rhs
-// on 16^4: 20 us with one wave, 26 with four)
-static int transfer_wpa(const TGeom& t) { return t.rows >= 256 ? 4 : 1; }
 static void check_transfer(const TGeom& t) {
   MGM_CHECK(t.ntv <= 128 && t.bvol <= 1024 && t.rows <= 4096, MGM_ERR_SHAPE,
             "transfers support at most 128 test vectors and 1024 sites per aggregate");
 }
 
-// Tiles of 8 rhs per workgroup: all up to four, else the split into fours or
-// threes with the fewest empty ones.  Four are halved where a wave has an
-// aggregate of its own (few rows, so that P is cheap to read twice): 12 test
-// vectors, 32 rhs on 16^4 in 2^4 aggregates, prolongation 75 us against 92.
-static int transfer_nt(int nrhs, int wpa) {
-  const int nt = (nrhs + 7) / 8, NT = nt <= 4 ? nt : (nt + 3) / 4 * 4 <= (nt + 2) / 3 * 3 ? 4 : 3;
-  return NT == 4 && wpa == 1 ? 2 : NT;
+// Waves per aggregate and chirality (one or four), and tiles of rhs per workgroup.  One
+// wave where the rows are few (2^4 aggregates of the fine level have 96, six steps of
+// four waves: FP16 restriction, 12 test vectors, 12 rhs on 16^4, 20 us with one, 26 with
+// four), in even groups of at most one_max tiles, if a CU gets cu_waves waves; else four
+// (8 test vectors on 4^4, FP64 restriction of 33 rhs 15.7 us with one, 7.4 with four; 40 test
+// vectors in 2^3 x 4 aggregates on 8^4, FP32 restriction of one 15.5 and 9.6), in even groups of
+// at most four_max tiles, or of fewer until every CU has a workgroup (24 test vectors, 16
+// aggregates 4^4, FP64 restriction of 33 rhs 75 us with three tiles, 32 with one).
+struct TransferSplit {
+  int wpa, nt;
+};
+static TransferSplit transfer_split(const Context* c, const TGeom& t, int tiles, int one_max, int four_max, int cu_waves) {
+  auto groups = [&](int nt) { return (tiles + nt - 1) / nt; };
+  auto even = [&](int most) { return groups(groups(most)); };
+  const int one = even(one_max);
+  if (t.rows < 256 && 2 * t.c.V * groups(one) >= (int64_t)cu_waves * c->cu_count) return {1, one};
+  int nt = even(four_max);
+  while (nt > 1 && 2 * t.c.V * groups(nt) < c->cu_count) nt--;
+  return {4, nt};
 }
-
-template <class P, class PM, int MT>
-static void launch_restrict_nt(Context* c, const TGeom& t, const typename P::S* x, typename P::S* yc,
-                               const typename PM::S* Pm, int nrhs) {
-  using V4 = typename Mm<typename P::R>::V4;
-  const int wpa = transfer_wpa(t), nt = (nrhs + 7) / 8, NT = transfer_nt(nrhs, wpa);
-  const int mz = (t.ntv + 16 * MT - 1) / (16 * MT);
-  const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((nt + NT - 1) / NT), (unsigned)mz), tb(256);
-  const size_t lds = sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) +
-                     (size_t)(4 / wpa) * (wpa - 1) * MT * NT * 64 * sizeof(V4);
-  switch (NT) {
-    case 1: hipLaunchKernelGGL((k_restrict<P, PM, MT, 1>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
-    case 2: hipLaunchKernelGGL((k_restrict<P, PM, MT, 2>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
-    case 3: hipLaunchKernelGGL((k_restrict<P, PM, MT, 3>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
-    default: hipLaunchKernelGGL((k_restrict<P, PM, MT, 4>), nb, tb, lds, c->stream, x, yc, Pm, t, nrhs, wpa); break;
+// one launch, or several of whole rhs groups where one would pass 2^31 threads
+template <class F>
+static void launch_tiles(int64_t blocks, int ny, int nz, F launch) {
+  const int most = (int)std::max<int64_t>(1, (1 << 23) / (blocks * nz));
+  for (int y0 = 0; y0 < ny; y0 += most) {
+    const Tiles p{std::min(most, ny - y0), nz, y0};
+    launch(dim3((unsigned)(blocks * p.ny * nz)), p);
+    MGM_LAUNCH_CHECK();
   }
-  MGM_LAUNCH_CHECK();
+}
+static int64_t transfer_blocks(const TGeom& t, int wpa) { return (2 * t.c.V * wpa + 3) / 4; }
+
+template <class P, class PM, int MT, int NT>
+static void launch_restrict_nt(Context* c, const TGeom& t, const typename P::S* x, typename P::S* yc,
+                               const typename PM::S* Pm, int nrhs, int wpa) {
+  const size_t lds = sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) +
+                     (size_t)(4 / wpa) * (wpa - 1) * MT * NT * 64 * sizeof(typename Mm<typename P::R>::V4);
+  launch_tiles(transfer_blocks(t, wpa), (nrhs + 8 * NT - 1) / (8 * NT), (t.ntv + 16 * MT - 1) / (16 * MT),
+               [&](dim3 nb, Tiles p) {
+                 hipLaunchKernelGGL((k_restrict<P, PM, MT, NT>), nb, dim3(256), lds, c->stream, x, yc, Pm, t, nrhs, wpa, p);
+               });
+}
+// Tiles of rhs.  FP64: up to three whole, more one by one, whose registers hold four
+// quadruples in flight (12 test vectors on 16^4 in 2^4 aggregates, 50 rhs, 335 us in twos, 199
+// one by one; 17 rhs 88 us whole, 96).  FP32: up to five whole (24 test vectors on 16^3 x 32 in 2^4
+// aggregates, 33 rhs, 282 us in threes, 230 in one), more in even groups of at most four;
+// with four waves an aggregate at most three.
+template <class P, class PM, int MT>
+static void launch_restrict_mt(Context* c, const TGeom& t, const typename P::S* x, typename P::S* yc,
+                               const typename PM::S* Pm, int nrhs) {
+  constexpr bool f64 = std::is_same<P, F64>::value;
+  const int tiles = (nrhs + 7) / 8, most = f64 && tiles > 3 ? 1 : 3;
+  const TransferSplit q = transfer_split(c, t, tiles, f64 ? most : tiles <= 5 ? 5 : 4, most, 4);
+  switch (q.nt) {
+    case 1: launch_restrict_nt<P, PM, MT, 1>(c, t, x, yc, Pm, nrhs, q.wpa); break;
+    case 2: launch_restrict_nt<P, PM, MT, 2>(c, t, x, yc, Pm, nrhs, q.wpa); break;
+    case 3: launch_restrict_nt<P, PM, MT, 3>(c, t, x, yc, Pm, nrhs, q.wpa); break;
+    case 4: if constexpr (!f64) launch_restrict_nt<P, PM, MT, 4>(c, t, x, yc, Pm, nrhs, q.wpa); break;
+    default: if constexpr (!f64) launch_restrict_nt<P, PM, MT, 5>(c, t, x, yc, Pm, nrhs, q.wpa); break;
+  }
 }
 template <class P, class PM>
 static void launch_restrict(Context* c, const TGeom& t, const typename P::S* x, typename P::S* yc,
                             const typename PM::S* Pm, int nrhs) {
   check_transfer(t);
   if (t.ntv <= 16)
-    launch_restrict_nt<P, PM, 1>(c, t, x, yc, Pm, nrhs);
+    launch_restrict_mt<P, PM, 1>(c, t, x, yc, Pm, nrhs);
   else
-    launch_restrict_nt<P, PM, 2>(c, t, x, yc, Pm, nrhs);
+    launch_restrict_mt<P, PM, 2>(c, t, x, yc, Pm, nrhs);
 }
 
+// Tiles of rhs: FP64 even groups of at most three (one wave an aggregate) or four; FP32
+// up to five whole (24 test vectors on 16^3 x 32 in 2^4 aggregates, 33 rhs, 292 us in threes, 272
+// in one), more in even groups of at most four.
 template <class P, class PM, class PX, int VK>
 static void launch_prolong_vk(Context* c, const TGeom& t, const typename P::S* xc, const typename P::S* x,
                               typename P::S* y, const typename PM::S* Pm, int nrhs, int mode,
                               const typename PX::S* xq, const double* xs, int xgs) {
-  const int ntile = (2 * nrhs + 15) / 16;
+  constexpr bool f64 = std::is_same<P, F64>::value;
+  const int tiles = (nrhs + 7) / 8;
   const size_t cb = sizeof(typename P::S);
   const int Kp = (t.ntv + 4 * VK - 1) / (4 * VK) * (4 * VK);
-  int wpa = transfer_wpa(t), NT = transfer_nt(nrhs, wpa);
+  TransferSplit q = transfer_split(c, t, tiles, f64 ? 3 : tiles <= 5 ? 5 : 4, 4, 8);
   // coarse values of more than 64 KiB: fewer rhs per workgroup, or one
   // aggregate and chirality (four waves) instead of four
   auto need = [&](int nt) {
-    return sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) + (size_t)(4 / wpa) * Kp * 8 * nt * cb;
+    return sizeof(uint32_t) * (4 / q.wpa) * row_words(t.rows) + (size_t)(4 / q.wpa) * Kp * 8 * nt * cb;
   };
-  while (NT > 2 && need(NT) > 65536) NT--;
-  if (need(NT) > 65536) wpa = 4;
-  while (NT > 1 && need(NT) > 65536) NT--;
-  const size_t lds = need(NT);
-  const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((ntile + NT - 1) / NT)), tb(256);
+  while (q.nt > 2 && need(q.nt) > 65536) q.nt--;
+  if (need(q.nt) > 65536) q.wpa = 4;
+  while (q.nt > 1 && need(q.nt) > 65536) q.nt--;
+  const size_t lds = need(q.nt);
   auto launch = [&](auto* k) {
-    hipLaunchKernelGGL(k, nb, tb, lds, c->stream, xc, x, y, Pm, t, nrhs, mode, wpa, xq, xs, xgs);
-    MGM_LAUNCH_CHECK();
+    launch_tiles(transfer_blocks(t, q.wpa), (tiles + q.nt - 1) / q.nt, 1, [&](dim3 nb, Tiles p) {
+      hipLaunchKernelGGL(k, nb, dim3(256), lds, c->stream, xc, x, y, Pm, t, nrhs, mode, q.wpa, xq, xs, xgs, p);
+    });
   };
-  const bool all = wpa == 4;
-  switch (NT) {
+  const bool all = q.wpa == 4;
+  switch (q.nt) {
     case 1: launch(all ? k_prolong<P, PM, PX, 1, VK, true> : k_prolong<P, PM, PX, 1, VK, false>); break;
     case 2: launch(all ? k_prolong<P, PM, PX, 2, VK, true> : k_prolong<P, PM, PX, 2, VK, false>); break;
     case 3: launch(all ? k_prolong<P, PM, PX, 3, VK, true> : k_prolong<P, PM, PX, 3, VK, false>); break;
-    default: launch(all ? k_prolong<P, PM, PX, 4, VK, true> : k_prolong<P, PM, PX, 4, VK, false>); break;
+    case 4: launch(all ? k_prolong<P, PM, PX, 4, VK, true> : k_prolong<P, PM, PX, 4, VK, false>); break;
+    default:
+      if constexpr (!f64) launch(k_prolong<P, PM, PX, 5, VK, false>);  // one wave an aggregate
   }
 }
 template <class P, class PM, class PX>
@@ -726,20 +782,21 @@ void Transfer::restrict16(const __half2* x16, const double* xs, float2* yc, int 
   MGM_CHECK(P16 != nullptr && xs != nullptr, MGM_ERR_INVALID_ARG, "FP16 transfer input needs P16 and scales");
   if (xgs <= 0) xgs = nrhs;
   MGM_CHECK(nrhs % xgs == 0, MGM_ERR_INVALID_ARG, "column groups must divide the rhs count");
-  const int wpa = transfer_wpa(t), ntile = (nrhs + 15) / 16, mt = (t.ntv + 7) / 8;
-  const int MT = mt <= 4 ? mt : (mt + 3) / 4 * 4 <= (mt + 2) / 3 * 3 ? 4 : 3;
-  const int NT = ntile <= 4 ? ntile : (ntile + 3) / 4 * 4 <= (ntile + 2) / 3 * 3 ? 4 : 3;
-  const dim3 nb((unsigned)((2 * t.c.V * wpa + 3) / 4), (unsigned)((ntile + NT - 1) / NT), (unsigned)((mt + MT - 1) / MT));
-  const size_t lds = sizeof(uint32_t) * (4 / wpa) * row_words(t.rows) +
-                     (size_t)(4 / wpa) * (wpa - 1) * MT * NT * 64 * sizeof(f4_t);
-#define MGM_R16(M, N)                                                                                              \
-  if (MT == M && NT == N)                                                                                          \
-    hipLaunchKernelGGL((k_restrict16<M, N>), nb, dim3(256), lds, ctx->stream, (const uint32_t*)x16, yc,            \
-                       (const uint32_t*)P16, t, nrhs, wpa, xs, xgs);
+  const int mt = (t.ntv + 7) / 8, MT = mt <= 4 ? mt : (mt + 3) / 4 * 4 <= (mt + 2) / 3 * 3 ? 4 : 3;
+  const TransferSplit q = transfer_split(ctx, t, (nrhs + 15) / 16, 4, 4, 4);
+  const size_t lds = sizeof(uint32_t) * (4 / q.wpa) * row_words(t.rows) +
+                     (size_t)(4 / q.wpa) * (q.wpa - 1) * MT * q.nt * 64 * sizeof(f4_t);
+  auto launch = [&](auto* k) {
+    launch_tiles(transfer_blocks(t, q.wpa), (nrhs + 16 * q.nt - 1) / (16 * q.nt), (mt + MT - 1) / MT, [&](dim3 nb, Tiles p) {
+      hipLaunchKernelGGL(k, nb, dim3(256), lds, ctx->stream, (const uint32_t*)x16, yc, (const uint32_t*)P16, t, nrhs,
+                         q.wpa, xs, xgs, p);
+    });
+  };
+#define MGM_R16(M, N) \
+  if (MT == M && q.nt == N) launch(k_restrict16<M, N>);
   MGM_R16(1, 1) MGM_R16(1, 2) MGM_R16(1, 3) MGM_R16(1, 4) MGM_R16(2, 1) MGM_R16(2, 2) MGM_R16(2, 3) MGM_R16(2, 4)
   MGM_R16(3, 1) MGM_R16(3, 2) MGM_R16(3, 3) MGM_R16(3, 4) MGM_R16(4, 1) MGM_R16(4, 2) MGM_R16(4, 3) MGM_R16(4, 4)
 #undef MGM_R16
-  MGM_LAUNCH_CHECK();
 }
 
 void Transfer::prolong16(const float2* xc, const __half2* x16, const double* xs, float2* y, int nrhs,
