@@ -414,7 +414,7 @@ __device__ __forceinline__ s4_t bf16x4(float a, float b, float c, float d) {
   return __builtin_bit_cast(s4_t, make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)));
 }
 
-// BF16: one tile per wave.  The default up to 64 dof (8192 sites, 48 dof, 100 rhs:
+// BF16: one tile per wave.  The default up to 64 dof, mostly (8192 sites, 48 dof, 100 rhs:
 // 782 -> 488 us, of which the nine neighbour reads from L2 set the pace; 20 rhs 248
 // -> 186; 512 sites, 64 dof, 80 rhs 72 -> 37; 256 sites, 16 dof, 25 rhs 9 -> 6).
 template <int MT, int KCH>
@@ -590,10 +590,31 @@ static std::vector<int> staged4_splits(const CoarseOp& A, int nrhs, size_t cb) {
 // fragments where the sites fill the chip (8 rhs, 48 dof, 8192 sites: 298 us against
 // 337 staged); with few sites the split over all row tiles shortens the
 // chain of a site (4 rhs, 64 dof, 512 sites: FP64 164 -> 88 us, FP32 90 -> 50).
-static int staged4_default(const CoarseOp& A, int ntr, int ns, const std::vector<int>& splits) {
+// Fewer sites than CUs: more than four tiles in one workgroup leave the others idle (100 rhs,
+// 48 dof, 16 sites: FP32 41 us against 58 staged, FP64 77 and 99), and three row tiles, which
+// do not split, gain nothing from sharing (1 rhs, 48 dof, 64 sites: FP32 41 and 45, FP64 74 and
+// 77; 20 rhs FP32 41 and 49).  One row tile in FP64: the fragments of a site are
+// few, and from 2048 sites on (1024 with more than four tiles) the chip is full without
+// (8 dof, 4096 sites: 17 rhs 32 and 41 us, 100 rhs 106 and 124).
+static int staged4_default(const CoarseOp& A, int ntr, int ns, const std::vector<int>& splits, bool f64) {
   if (splits.empty()) return 0;
+  const int MT = mgeo(A.d).MT;
+  if (A.g.V < A.ctx->cu_count && (ntr > 4 || (MT == 3 && ntr <= (f64 ? 1 : 2)))) return 0;
+  if (f64 && MT == 1 && A.g.V >= (ntr > 4 ? 1024 : 2048)) return 0;
   if (ntr == 1) return A.g.V < 1024 ? ns + (int)splits.size() - 1 : 0;
-  return ntr == 2 && mgeo(A.d).MT == 4 ? ns + 1 : ns;
+  return ntr == 2 && MT == 4 ? ns + 1 : ns;
+}
+// BF16: staged except for a single tile where the forms of one wave per tile are as well
+// without: four row tiles with fewer sites than CUs (56 dof, 64 sites, 4 rhs: 20 us, 23 staged),
+// two and four while all sites fit the chip at once (24 dof, 4096 sites, 1 rhs: 27 and
+// 33; 64 dof, 2048 sites, 16 rhs: 34 and 37), 8 dof on many sites (8192, 8 rhs: 21 and 22).
+static bool staged_bf16_default(const CoarseOp& A, int ntr) {
+  if (ntr > 1) return true;
+  const int64_t V = A.g.V;
+  const int MT = mgeo(A.d).MT;
+  if (MT == 4 && V < A.ctx->cu_count) return false;
+  if (MT % 2 == 0 && V >= 2048 && V * MT < 16384) return false;
+  return !(A.d <= 8 && V >= 8192);
 }
 template <class M>
 static void launch_staged4(const CoarseOp& A, const typename M::C2* x, typename M::C2* y, const typename M::C2* Ap,
@@ -640,7 +661,7 @@ void coarse_apply_mfma64(const CoarseOp& A, const double2* x, double2* y, int nr
                   }
                   MGM_LAUNCH_CHECK();
                 },
-                staged4_default(A, ntr, ns, splits));
+                staged4_default(A, ntr, ns, splits, true));
 }
 
 void coarse_apply_mfma32(const CoarseOp& A, const float2* x, float2* y, int nrhs) {
@@ -668,7 +689,7 @@ void coarse_apply_mfma32(const CoarseOp& A, const float2* x, float2* y, int nrhs
                   }
                   MGM_LAUNCH_CHECK();
                 },
-                staged4_default(A, ntr, ns, splits));
+                staged4_default(A, ntr, ns, splits, false));
 }
 
 __global__ void k_pack32(float2* __restrict__ out, const double2* __restrict__ packed64, int64_t n) {
@@ -763,7 +784,7 @@ void coarse_apply_mfma(const CoarseOp& A, const float2* x, float2* y, int nrhs) 
                   }
                   MGM_LAUNCH_CHECK();
                 },
-                staged ? (int)shapes.size() : 0);
+                staged && staged_bf16_default(A, ntr) ? (int)shapes.size() : 0);
 }
 
 }  // namespace mgm
