@@ -68,9 +68,11 @@ N_SITE_VARIANTS_DOT = 2  # site-parallel launch variants of the reducing dslash;
 TUNE_PREFIX = {"dslash_step": "dslash_step"}  # tune-table key prefix of each class with recorded counters
 
 
-def kernel_name(kclass, variants):
+def kernel_name(kclass, variants, forms=()):
+    """Kernel of a class by the launch variants and forms it ran with; forms:
+    rhs counts that ran another form than the listed variants."""
     if kclass == "dslash_step":
-        return KERNEL_NAMES[kclass]
+        return "k_dslash<F16, DOT, MR> (fused FP16 smoother step, site-parallel)" if forms else KERNEL_NAMES[kclass]
     if kclass == "dslash_f16" and variants and min(variants.values()) >= N_SITE_VARIANTS_DOT:
         return "k_dslash_march<F16, DOT> (fused MR-smoother dslash, plane-marching)"
     return KERNEL_NAMES[kclass]
@@ -170,6 +172,25 @@ def rhs_counts(kv):
     covers, larger first (one or two; 8 and 4 when it does not say)."""
     c = [int(v) for v in kv.get("rhs_counts", "8 4").split()]
     return max(c), min(c)
+
+
+def launch_choices(report, kind, prec, dims):
+    """(variants, forms) of a kernel from a tune report, per rhs count: the
+    number of the variant that launches take, and the counts among them that
+    take one of the other forms (box, site-parallel step), numbered behind the
+    listed variants."""
+    V = dims[0] * dims[1] * dims[2] * dims[3]
+    pref, fpref = "%s/%d/%d/" % (kind, prec, V), "%s_form@%dx%dx%dx%d/%d/%d/" % ((kind,) + tuple(dims) + (prec, V))
+    variants = {int(k[len(pref):]): v[0] for k, v in report.items() if k.startswith(pref)}
+    forms = set()
+    for k, (v, _) in report.items():
+        if k.startswith(fpref) and v > 0:
+            n = int(k[len(fpref):])
+            listed = report.get(pref + str(n), (0, []))[1]
+            if listed:  # a pinned variant goes before a measured form
+                variants[n] = len(listed) + v - 1
+                forms.add(n)
+    return variants, forms
 
 
 def measured_traffic(kclass, V, launches, total_bytes, variants=None):
@@ -405,7 +426,7 @@ def run(args):
         _run_gpu(args, cfg, U, t_gauge, cpu_pid, cpu_out, m, torch)
 
 
-def roofline(ds, V, q, achieved_gbs, avg_ms, bytes_launch, variants, traffic):
+def roofline(ds, V, q, achieved_gbs, avg_ms, bytes_launch, variants, traffic, forms=()):
     """Roofline of the dominant dslash against whichever roof is tighter for
     its algorithmic counts: FP32/FP64 vector FMA (unpacked) or HBM."""
     flops_launch = dslash_flops(ds, V, q["launches"], q["bytes"]) / max(q["launches"], 1)
@@ -417,7 +438,7 @@ def roofline(ds, V, q, achieved_gbs, avg_ms, bytes_launch, variants, traffic):
     main, other, bound = (alu, hbm, "alu") if t_alu > t_hbm else (hbm, alu, "hbm")
     out = {"bound": bound}
     out.update(main)
-    out.update({"traffic": traffic, "kernel": kernel_name(ds, variants), "launch_variants": variants,
+    out.update({"traffic": traffic, "kernel": kernel_name(ds, variants, forms), "launch_variants": variants,
                 "avg_launch_ms": avg_ms, "launches": q["launches"], "bytes_per_launch": bytes_launch,
                 "flop_per_launch": flops_launch, "other_roof": dict(other, bound="hbm" if bound == "alu" else "alu"),
                 "peak_note": "alu peak = unpacked vector FMA (packed FP32 is disabled in the build; "
@@ -487,8 +508,8 @@ def _run_gpu(args, cfg, U, t_gauge, cpu_pid, cpu_out, m, torch):
     q = prof[ds]
     rep = ctx.tune_report()
     # launch variants the dominant class ran with, per rhs count (pinned or tuned)
-    pref = "%s/%d/%d/" % (TUNE_PREFIX.get(ds, ""), m.api.PREC["f16"], op.V)
-    variants = {int(k[len(pref):]): v[0] for k, v in rep.items() if ds in TUNE_PREFIX and k.startswith(pref)}
+    variants, forms = (launch_choices(rep, TUNE_PREFIX[ds], m.api.PREC["f16"], op.dims) if ds in TUNE_PREFIX
+                       else ({}, set()))
     avg_ms = q["ms"] / max(q["launches"], 1)
     bytes_launch = q["bytes"] / max(q["launches"], 1)
     achieved = bytes_launch / (avg_ms * 1e-3) / 1e9 if q["launches"] else 0.0
@@ -504,7 +525,7 @@ def _run_gpu(args, cfg, U, t_gauge, cpu_pid, cpu_out, m, torch):
                    "inner_tol": sd.inner_tol},
         "roofline": roofline(ds, op.V, q, achieved, avg_ms, bytes_launch, variants,
                              measured_traffic(ds, op.V, q["launches"], q["bytes"], variants)
-                             if args.config == "c4" else None),
+                             if args.config == "c4" else None, forms),
         "hierarchy_workspace_gb": h.ws.numel() / 1e9,
         "setup_s": t_setup, "gauge_gen_s": t_gauge, "rhs_per_step": nrhs_step,
         "solver_iterations_per_step": results[-1]["stats"]["iterations"],
@@ -980,6 +1001,10 @@ def micro(args):
             rep = ctx.tune_report().get(key)
             if rep is not None:
                 line["variant"], line["variant_ms"] = rep[0], rep[1]
+            kind, rest = key.split("/", 1)
+            form = ctx.tune_report().get("%s_form@%dx%dx%dx%d/%s" % ((kind,) + op.dims + (rest,)))
+            if form is not None:
+                line["form"], line["form_ms"] = form
             print(json.dumps(line), flush=True)
             del x, y
 

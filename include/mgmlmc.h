@@ -85,24 +85,31 @@ mgm_status mgm_context_create(int device, void* hip_stream, mgm_context* out);
 /* Switches the stream used by later calls on this context. */
 mgm_status mgm_context_set_stream(mgm_context ctx, void* hip_stream);
 /* Launch-shape autotuner (project-written): when enabled, the first launch of
- * a tunable kernel (fine dslash: rhs per thread and block order of the
- * site-parallel kernel, then the tile, z-run and rhs group of the
- * plane-marching kernel; coarse stencils: 16-rhs tiles per workgroup) for a
- * given shape times every variant on that call's own arguments with HIP
- * events (best of three) and keeps the fastest for the rest of the context's
- * life.  Results do not depend on the variant beyond floating-point rounding
- * order.  Off by default (variant 0). */
+ * a tunable kernel for a given shape times every variant on that call's own
+ * arguments with HIP events (best of three) and keeps the fastest for the rest of
+ * the context's life.  Variants of the fine dslash: rhs per thread and site order of
+ * the site-parallel kernel, then the tile, z-run and rhs group of the
+ * plane-marching kernel (fused smoother step: those with FP32, then with packed FP16
+ * arithmetic), and as a form of its own the kernel in boxes of sites (FP64, FP32) or the
+ * site-parallel step (one and two rhs per thread); of the coarse stencils: 16-rhs
+ * tiles per workgroup, then the forms staged through LDS.  Results do not depend
+ * on the variant beyond floating-point rounding order.  Off by default: every
+ * launch then takes the variant that a rule on sizes and types picks. */
 mgm_status mgm_context_set_autotune(mgm_context ctx, int32_t enable);
-/* Text table of the tuned shapes ("key variant ms_v0 ms_v1 ..." per line),
+/* Text table of the tuned shapes ("key variant ms_v0 ms_v1 ..." per line, a
+ * time for every variant; none for a pinned one),
  * NUL-terminated, truncated to `bytes`; *needed receives the full length.  Keys
  * name the lattice by its volume; where the variants depend on the extents, a second
  * lattice of one volume has a line of its own, its extents behind the first word
- * ("dslash@XxYxZxT/..."). */
+ * ("dslash@XxYxZxT/...").  The choice between the listed variants and the other
+ * forms of a kernel has a line "dslash_form@XxYxZxT/...", whose variant 0 is the
+ * fastest listed one. */
 mgm_status mgm_context_tune_report(mgm_context ctx, char* buf, size_t bytes, size_t* needed);
 /* Pins launch variant `variant` (>= 0) for shape `key` (a key of the tune
  * report, e.g. from an earlier run), as if the autotuner had chosen it; later
  * launches of that shape use it whether or not tuning is enabled, on every
- * lattice of the volume unless the key names the extents.  A variant
+ * lattice of the volume unless the key names the extents.  A pinned variant goes
+ * before a measured form, a pinned form before both.  A variant
  * beyond the shape's count makes those launches fail with INVALID_ARG.
  * Errors: INVALID_ARG (NULL key, negative variant). */
 mgm_status mgm_context_tune_set(mgm_context ctx, const char* key, int32_t variant);

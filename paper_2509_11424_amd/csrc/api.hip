@@ -1,4 +1,5 @@
 // C ABI of the library: argument checks, status codes, object lifetimes.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -45,68 +46,77 @@ void Context::prof_end(int kclass, double bytes, hipEvent_t a) {
   if (prof.pending.size() > 4096) prof_flush();
 }
 
-// key of the same launch on one lattice: "kind@XxYxZxT/rest"
-static std::string on_lattice(const std::string& key, const std::string& lattice) {
+// "kind/rest" with `text` behind the kind
+static std::string behind_kind(const std::string& key, const std::string& text) {
   const size_t k = std::min(key.find('/'), key.size());
-  return key.substr(0, k) + "@" + lattice + key.substr(k);
+  return key.substr(0, k) + text + key.substr(k);
 }
-
+const Tuner::Entry* Tuner::at(const std::string& key) const {
+  auto it = table.find(key);
+  return it == table.end() ? nullptr : &it->second;
+}
 const Tuner::Entry* Tuner::find(const std::string& key, const std::string& lattice) const {
-  auto at = [&](const std::string& k) {
-    auto it = table.find(k);
-    return it == table.end() ? nullptr : &it->second;
-  };
   const Entry* all = at(key);
   if (all && !all->pinned() && all->lattice != lattice) all = nullptr;
-  const Entry* own = lattice.empty() ? nullptr : at(on_lattice(key, lattice));
+  const Entry* own = lattice.empty() ? nullptr : at(behind_kind(key, "@" + lattice));
   return own && (own->pinned() || !all || !all->pinned()) ? own : all;
 }
 
 int Context::choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt, int more,
                     const std::string& lattice) {
-  if (const Tuner::Entry* t = tune.find(key, lattice)) {
-    const int v = t->variant;
+  const std::string form_key = behind_kind(key, "_form@" + lattice);
+  const Tuner::Entry* e = tune.find(key, lattice);
+  const Tuner::Entry* f = lattice.empty() ? nullptr : tune.at(form_key);
+  if (f && !f->pinned() && e && e->pinned()) f = nullptr;
+  int v = f && dflt >= nvar ? 0 : dflt;
+  if (f && f->variant > 0) {
+    MGM_CHECK(f->variant <= more, MGM_ERR_INVALID_ARG,
+              "pinned launch form " + std::to_string(f->variant) + " out of range for " + form_key);
+    v = nvar + f->variant - 1;
+  } else if (e) {
+    v = e->variant;
     MGM_CHECK(v < nvar + more, MGM_ERR_INVALID_ARG,
               "pinned launch variant " + std::to_string(v) + " out of range for " + key);
-    run(v);
-    return v;
-  }
-  if (!tune.enabled || capturing || nvar + more <= 1) {
-    run(dflt);
-    return dflt;
-  }
-  const bool prof_was_on = prof.on;
-  prof.on = false;  // tuning launches stay out of the kernel-class statistics
-  Tuner::Entry e;
-  e.lattice = lattice;
-  e.ms.assign(nvar + more, 0.0f);
-  hipEvent_t a = take_event(), b = take_event();
-  for (int v = 0; v < nvar + more; v++) {
-    run(v);  // warm-up
-    float best = 3.0e38f;
-    for (int rep = 0; rep < 3; rep++) {
-      MGM_HIP(hipEventRecord(a, stream));
-      run(v);
-      MGM_HIP(hipEventRecord(b, stream));
-      MGM_HIP(hipEventSynchronize(b));
-      float ms = 0;
-      MGM_HIP(hipEventElapsedTime(&ms, a, b));
-      best = ms < best ? ms : best;
+  } else if (tune.enabled && !capturing && nvar + more > 1) {
+    const bool prof_was_on = prof.on;
+    prof.on = false;  // tuning launches stay out of the kernel-class statistics
+    hipEvent_t a = take_event(), b = take_event();
+    auto time_of = [&](int u) {
+      run(u);  // warm-up
+      float best = 3.0e38f;
+      for (int rep = 0; rep < 3; rep++) {
+        MGM_HIP(hipEventRecord(a, stream));
+        run(u);
+        MGM_HIP(hipEventRecord(b, stream));
+        MGM_HIP(hipEventSynchronize(b));
+        float ms = 0;
+        MGM_HIP(hipEventElapsedTime(&ms, a, b));
+        best = ms < best ? ms : best;
+      }
+      return best;
+    };
+    auto fastest = [](const Tuner::Entry& t) { return (int)(std::min_element(t.ms.begin(), t.ms.end()) - t.ms.begin()); };
+    Tuner::Entry t;
+    t.lattice = lattice;
+    for (int u = 0; u < nvar; u++) t.ms.push_back(time_of(u));
+    v = t.variant = fastest(t);
+    if (more > 0 && !f) {
+      Tuner::Entry forms;
+      forms.lattice = lattice;
+      forms.ms.push_back(t.ms[v]);
+      for (int u = nvar; u < nvar + more; u++) forms.ms.push_back(time_of(u));
+      forms.variant = fastest(forms);
+      if (forms.variant > 0) v = nvar + forms.variant - 1;
+      tune.table[form_key] = forms;
     }
-    e.ms[v] = best;
+    // the first lattice of a volume has the plain key
+    tune.table[tune.table.count(key) ? behind_kind(key, "@" + lattice) : key] = t;
+    prof.pool.push_back(a);
+    prof.pool.push_back(b);
+    prof.on = prof_was_on;
   }
-  int bv = 0;
-  for (int v = 1; v < nvar + more; v++)
-    if (e.ms[v] < e.ms[bv]) bv = v;
-  e.variant = bv;
-  e.ms.resize(nvar);  // the report lists the first nvar
-  // the first lattice of a volume has the plain key
-  tune.table[tune.table.count(key) ? on_lattice(key, lattice) : key] = e;
-  prof.pool.push_back(a);
-  prof.pool.push_back(b);
-  prof.on = prof_was_on;
-  run(bv);  // the call's result comes from the chosen variant
-  return bv;
+  run(v);  // the call's result comes from the chosen variant
+  return v;
 }
 
 void Context::prof_flush() {

@@ -271,8 +271,9 @@ struct Profiler {
 
 // Launch-shape autotuner: the first call of a kernel for a shape key times
 // every variant on the call's own arguments (HIP events, best of three) and
-// keeps the fastest; later calls reuse it.  Off by default (variant 0), and
-// never active while a stream is being captured into a graph.
+// keeps the fastest; later calls reuse it.  Off by default (each launch then
+// takes the default of its rule), and never active while a stream is being
+// captured into a graph.
 struct Tuner {
   bool enabled = false;
   struct Entry {
@@ -288,6 +289,7 @@ struct Tuner {
   // an entry of its own.  A pinned entry holds for every lattice and goes before a
   // measured one.
   const Entry* find(const std::string& key, const std::string& lattice) const;
+  const Entry* at(const std::string& key) const;
 };
 
 struct Context {
@@ -307,11 +309,12 @@ struct Context {
   void prof_end(int kclass, double bytes, hipEvent_t a);
   void prof_flush();
   void sync() { MGM_HIP(hipStreamSynchronize(stream)); }
-  // variant of `key` among nvar; run(v) launches variant v on the stream;
-  // `dflt` is the variant used while the autotuner is off.  `more` variants
-  // follow the nvar listed ones: they are tuned and pinned like them, but the
-  // times of the report are those of the listed ones, whose numbers saved
-  // tables hold.  `lattice`: the extents, where the variants depend on them
+  // Variant of `key` among nvar; run(v) launches variant v on the stream; `dflt`
+  // is the variant used while the autotuner is off.  `lattice`: the extents, where the
+  // variants depend on them.  `more` other forms follow the nvar variants: they are
+  // chosen under an entry of their own ("kind_form@lattice/..."), whose variant 0 stands for
+  // those nvar, so that the numbers and times of the older variants keep their
+  // places in tables and reports.  A pinned variant of `key` goes before a measured form.
   int choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt = 0, int more = 0,
              const std::string& lattice = "");
 };

@@ -124,3 +124,16 @@ def test_run_batches():
     assert bench.run_batches(c4, "f64", True, [4, 8, 8]) == [4, 8, 8]
     c3 = bench.CONFIGS["c3"]
     assert bench.run_batches(c3, "f64", True) == c3["batch"]
+
+
+def test_launch_choices_name_the_form_that_ran():
+    """A measured form behind the listed variants; a pinned variant (no times) goes before it."""
+    import bench
+    dims = (32, 32, 32, 64)
+    key, form = "dslash_step/2/%d/" % (32 ** 3 * 64), "dslash_step_form@32x32x32x64/2/%d/" % (32 ** 3 * 64)
+    rep = {key + "4": (25, []), form + "4": (1, [0.3, 0.2]), key + "8": (3, [0.1] * 10), form + "8": (2, [0.1, 0.2, 0.05]),
+           key + "12": (7, [0.1] * 8), form + "12": (0, [0.1, 0.2, 0.3]), "dslash_step@16x64x32x64/2/2097152/4": (1, [1.0, 2.0])}
+    variants, forms = bench.launch_choices(rep, "dslash_step", 2, dims)
+    assert variants == {4: 25, 8: 11, 12: 7} and forms == {8}
+    assert bench.kernel_name("dslash_step", variants, forms).startswith("k_dslash<F16, DOT, MR>")
+    assert bench.kernel_name("dslash_step", variants).startswith("k_dslash_march")
