@@ -95,7 +95,9 @@ int Context::choose(const std::string& key, int nvar, const std::function<void(i
       }
       return best;
     };
-    auto fastest = [](const Tuner::Entry& t) { return (int)(std::min_element(t.ms.begin(), t.ms.end()) - t.ms.begin()); };
+    auto fastest = [](const Tuner::Entry& t) {
+      return (int)(std::min_element(t.ms.begin(), t.ms.end()) - t.ms.begin());
+    };
     Tuner::Entry t;
     t.lattice = lattice;
     for (int u = 0; u < nvar; u++) t.ms.push_back(time_of(u));

@@ -5,6 +5,7 @@
 #include "blas.h"
 #include "group.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace mgm {
@@ -50,7 +51,7 @@ __device__ __forceinline__ void stw(void* p, int64_t i, const cx<double> (&v)[W]
 // arrays are aligned.  One element a thread read 256 bytes a wave in FP16.
 template <class PA, class PB>
 static int pack_width(int nrhs, int ga, int gb, const void* a, const void* b, const void* c) {
-  constexpr size_t narrow = sizeof(typename PA::S) < sizeof(typename PB::S) ? sizeof(typename PA::S) : sizeof(typename PB::S);
+  constexpr size_t narrow = std::min(sizeof(typename PA::S), sizeof(typename PB::S));
   int w = (int)(16 / narrow);
   if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) % 16) return 1;
   while (w > 1 && (nrhs % w || ga % w || gb % w)) w /= 2;
@@ -59,7 +60,7 @@ static int pack_width(int nrhs, int ga, int gb, const void* a, const void* b, co
 // launch(std::integral_constant<int, W>) for the W above (at most 16 / the narrower)
 template <class PA, class PB, class F>
 static void with_width(int w, F launch) {
-  constexpr size_t narrow = sizeof(typename PA::S) < sizeof(typename PB::S) ? sizeof(typename PA::S) : sizeof(typename PB::S);
+  constexpr size_t narrow = std::min(sizeof(typename PA::S), sizeof(typename PB::S));
   if constexpr (narrow <= 4)
     if (w == 4) return launch(std::integral_constant<int, 4>());
   if constexpr (narrow <= 8)
@@ -386,7 +387,8 @@ void b_mr_update(Context* c, const double2* qr, const double* qq, Vec rho, Vec q
             "mr update: shape mismatch");
   const void* src = rho_in ? rho_in->p : rho.p;
   DISPATCH_PREC(rho.prec, P,
-      with_width<P, P>((uintptr_t)src % 16 ? 1 : pack_width<P, P>(rho.nrhs, rho.nrhs, rho.nrhs, rho.p, q.p, y.p), [&](auto w) {
+      const int most = pack_width<P, P>(rho.nrhs, rho.nrhs, rho.nrhs, rho.p, q.p, y.p);
+      with_width<P, P>((uintptr_t)src % 16 ? 1 : most, [&](auto w) {
         hipLaunchKernelGGL((k_mr_update<P, decltype(w)::value>), dim3(ew_blocks(n / decltype(w)::value)), dim3(256), 0,
                            c->stream, qr, qq, src, rho.p, q.p, y.p, n, rho.nrhs, y_zero ? 1 : 0);
       }));
@@ -514,7 +516,8 @@ __global__ __launch_bounds__(256) void k_finalize_r(const double2* partial, int 
 }
 static void finalize_c(Context* c, const double2* partial, int nblk, int cnt, double2* out, int64_t out_off) {
   if (finalize_ob(cnt) == 4)
-    hipLaunchKernelGGL(k_finalize_c<4>, dim3((cnt + 3) / 4), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out, out_off);
+    hipLaunchKernelGGL(k_finalize_c<4>, dim3((cnt + 3) / 4), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out,
+                       out_off);
   else
     hipLaunchKernelGGL(k_finalize_c<1>, dim3(cnt), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out, out_off);
 }
@@ -525,7 +528,8 @@ static void finalize_r(Context* c, const double2* partial, int nblk, int cnt, do
     hipLaunchKernelGGL(k_finalize_r<1>, dim3(cnt), dim3(256), 0, c->stream, partial, nblk, cnt, cnt, out);
 }
 // q^H rho (slot 0) and |q|^2 (slot 1) -> separate outputs (grid = 2 * nrhs)
-__global__ __launch_bounds__(256) void k_finalize_dn(const double2* partial, int nblk, int nrhs, double2* qr, double* qq) {
+__global__ __launch_bounds__(256) void k_finalize_dn(const double2* partial, int nblk, int nrhs, double2* qr,
+                                                     double* qq) {
   const int i = blockIdx.x;
   const double2 v = sum_partials<1>(partial, nblk, 2 * nrhs, i, 2 * nrhs);
   if (threadIdx.x == 0) {

@@ -369,8 +369,9 @@ constexpr int kTileThreads = 768;
 
 // per-column block sums of a tile, through LDS
 template <int RB>
-__device__ __forceinline__ void tile_dot_store(const cx<double> (&dqr)[RB], const double (&dqq)[RB], int nrhs, int sites,
-                                               int64_t nblocks, unsigned char* smem, double2* __restrict__ dpart) {
+__device__ __forceinline__ void tile_dot_store(const cx<double> (&dqr)[RB], const double (&dqq)[RB], int nrhs,
+                                               int sites, int64_t nblocks, unsigned char* smem,
+                                               double2* __restrict__ dpart) {
   const int t = threadIdx.x, n = sites * nrhs;
   double* sr = reinterpret_cast<double*>(smem);  // [3][n]
   __syncthreads();
@@ -405,11 +406,12 @@ __device__ __forceinline__ void tile_dot_store(const cx<double> (&dqr)[RB], cons
   }
 }
 
+// box of sites that a block owns
 struct Tile {
   int b[4];   // extents
   int sites;  // their product
 };
-// O: the type of a byte offset into a dof plane, 32 bits where a plane fits.
+
 // Site-parallel dslash: one thread computes RB consecutive right-hand sides
 // of one site, so the links, clover entries and index arithmetic are shared by
 // the columns (16-byte FP32, 8-byte FP16 spinor loads at RB = 2).  Bound by the
@@ -427,10 +429,11 @@ struct Tile {
 // O: the type of a byte offset into a dof plane, 32 bits where a plane fits.
 // TILE (FP64, FP32): a block owns all rhs of a box of sites and stages their spinors
 // in LDS, so hops inside the box (4 of 8 in a box of 4 x 2 x 2 x 4) and the centre
-// do not read L1 again.  The box is rarely larger than 32 sites: blocks of three or four
-// waves fill a CU's wave slots and do not wait for each other.  FP64 at 12 rhs on
-// 16^4 161 us to 143, at 4 rhs 66 to 48; FP32 at 12 rhs on 24^3 x 48 699 to 614 (38 million L1 lines instead of 66), then bound by reads past
-// L2: the boxes an XCD has in flight exceed its 4 MB, 25 million lines come from
+// do not read L1 again.  A block has threads x RB / nrhs sites: 103 to 256 threads
+// (several blocks a CU, which do not wait for each other), or in FP64 one block of 577 to
+// 768 a CU (tile_plan).  FP64 at 12 rhs on 16^4 161 us to 143, at 4 rhs 66 to 48; FP32 at 12
+// rhs on 24^3 x 48 699 to 614 (38 million L1 lines instead of 66), then bound by reads
+// past L2: the boxes an XCD has in flight exceed its 4 MB, 25 million lines come from
 // beyond, 9 million would do.
 // Same sums in the same order as the untiled form.
 template <class P, bool DOT, bool MR, int RB, class O, bool TILE>
@@ -536,7 +539,8 @@ __global__ __launch_bounds__(TILE ? kTileThreads : 256) void k_dslash(typename P
       // neighbours inside the tile from LDS, the others from memory
       const int lm = mu == 0 ? lc[0] : mu == 1 ? lc[1] : mu == 2 ? lc[2] : lc[3];
       const int bm = mu == 0 ? tile.b[0] : mu == 1 ? tile.b[1] : mu == 2 ? tile.b[2] : tile.b[3];
-      const int dm = (mu == 0 ? 1 : mu == 1 ? tile.b[0] : mu == 2 ? tile.b[0] * tile.b[1] : tile.b[0] * tile.b[1] * tile.b[2]) * nrhs;
+      const int xy = tile.b[0] * tile.b[1];
+      const int dm = (mu == 0 ? 1 : mu == 1 ? tile.b[0] : mu == 2 ? xy : xy * tile.b[2]) * nrhs;
       const bool edge = fwd ? lm == bm - 1 : lm == 0;
       const int l2 = edge ? le + (bm == ex ? (fwd ? -(bm - 1) * dm : (bm - 1) * dm) : 0) : fwd ? le + dm : le - dm;
 #pragma unroll
@@ -838,7 +842,8 @@ __device__ __forceinline__ void buf_link_raw(Rsrc ru, uint32_t plane_b, int mu, 
   constexpr int LG = FieldGroup<P>::LG;
 #pragma unroll
   for (int c = 0; c < 8 / LG; c++) {
-    const auto v = buf_words<LG * sizeof(S)>(ru, ls * (uint32_t)(LG * sizeof(S)), (uint32_t)(mu * 8 + c * LG) * plane_b);
+    const auto v =
+        buf_words<LG * sizeof(S)>(ru, ls * (uint32_t)(LG * sizeof(S)), (uint32_t)(mu * 8 + c * LG) * plane_b);
     static_assert(sizeof(v) == LG * sizeof(S), "group size");
     __builtin_memcpy(&w[c * LG], &v, sizeof(v));
   }
@@ -1423,10 +1428,10 @@ struct MrArgs {
 // Taken where the first is below 6 of 9 spinors (against the untiled form, 16^4: FP64 2.9 at
 // 1 rhs 26.6 us to 20.8, 4.0 at 4 rhs 66 to 48, 5.0 at 12 rhs 161 to 143, 6.0 at 32 rhs 384 to 392;
 // FP32 4.5 at 12 rhs 78 to 65, 7.7 at 25 rhs 151 to 165), past 2 GB below 4.6 (32^3 x 64: FP64
-// 5.0 at 12 rhs 5.04 ms to 5.3, 4.0 at 4 rhs 1.96 to 1.67, FP32 4.5 at 12 rhs 2.26 to 2.16), every CU gets a block and
-// the fullest at most 5/4 of the mean (FP32 at 4 rhs on 12 x 10 x 14 x 18, 336 blocks: 24.6 us to
-// 26.1), and a plane fits 32-bit offsets.  In FP32 every CU gets two blocks' worth of threads
-// (1 rhs on 16^4 12.6 us to 14.0).  Not in FP16, whose spinors leave more of the
+// 5.0 at 12 rhs 5.04 ms to 5.3, 4.0 at 4 rhs 1.96 to 1.67, FP32 4.5 at 12 rhs 2.26 to 2.16),
+// every CU gets a block and the fullest at most 5/4 of the mean (FP32 at 4 rhs on 12 x 10 x 14 x
+// 18, 336 blocks: 24.6 us to 26.1), and a plane fits 32-bit offsets.  In FP32 every CU gets
+// two blocks' worth of threads (1 rhs on 16^4 12.6 us to 14.0).  Not in FP16, whose spinors leave more of the
 // time to arithmetic (12 rhs on 16^4: 59 us to 60 at best, 50 rhs 188 to 253).
 struct TilePlan {
   Tile t{};
@@ -1461,7 +1466,9 @@ static bool tile_plan(const FineOp& op, mgm_prec p, int nrhs, bool dot, TilePlan
           const int bx[4] = {div[0][a], div[1][b], div[2][c], div[3][d]};
           const int sites = s3 * bx[3], th = sites * nq;
           if (th < lo || 5 * th < 4 * ((th + 63) / 64 * 64)) continue;
-          if (dot && sites * nrhs < 256) continue;  // bounds the partial sums
+          // the partial sums have room for the untiled form's blocks of 256 elements: a
+          // limit of memory, smaller boxes have not been timed with dots
+          if (dot && sites * nrhs < 256) continue;
           const int64_t cus = op.ctx->cu_count, nb = g.V / sites;
           if (nb < cus || 4 * ((nb + cus - 1) / cus * cus) > 5 * nb) continue;
           double reads = 1;
@@ -1591,7 +1598,9 @@ static double march_us(const FineOp& op, mgm_prec p, int nrhs, const MarchShape&
   const int64_t cus = op.ctx->cu_count;
   const int64_t res = std::max<int64_t>(
       1, std::min<int64_t>(1024 / th, (int64_t)(op.ctx->max_lds / march_lds(g, p, m, dot))));
-  auto plane = [&](int64_t blocks_per_cu) { return blocks_per_cu == 0 ? 0.0 : 6.5 + 11.5e-3 * (double)(blocks_per_cu * th); };
+  auto plane = [&](int64_t blocks_per_cu) {
+    return blocks_per_cu == 0 ? 0.0 : 6.5 + 11.5e-3 * (double)(blocks_per_cu * th);
+  };
   const int64_t full = blocks / (cus * res), tail = (blocks - full * cus * res + cus - 1) / cus;
   const double ratio = (double)nrhs / m.nbr;
   const double line = (m.nbr == 1 ? 1.4 : m.nbr == 2 ? 1.15 : 1.0) * (1.0 + 0.015 * ratio * ratio);
@@ -1689,7 +1698,8 @@ static std::string lattice_of(const Geom& g) {
 // then every plane-marching shape that applies.  Untuned, FP16 takes the form
 // with the smallest estimated time (the first marching shape that applies left
 // 224 of 256 CUs idle on 16^4: 146 us against 19 at 4 rhs), FP32 and FP64
-// the tile form (the last variant) where there is a plan, else variant 0.  Returns the block count of the variant that ran.
+// the tile form (chosen beside the variants) where there is a plan, else variant 0.
+// Returns the block count of the variant that ran.
 template <bool DOT>
 static int64_t launch_dslash(const FineOp& op, mgm_prec p, const void* x, void* y, int nrhs, double2* dpart) {
   const int rb0 = rb_of(p, nrhs, DOT);

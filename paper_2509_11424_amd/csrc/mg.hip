@@ -99,7 +99,8 @@ void mg_agg_map(Context* c, const TGeom& t, int64_t* out) {
 // the tiles of one aggregate (right-hand sides, test vectors) follow each other there,
 // as they share P and the lines at the ends of their column ranges: FP32
 // prolongation of 33 rhs on 16^3 x 32 in 2^4 aggregates, 24 test vectors, 404 us with the
-// tiles in separate passes over the lattice, 330 side by side.  Aggregates 4^4, 24 test vectors, 20 rhs on 16^3 x 32, start
+// tiles in separate passes over the lattice, 330 side by side.  Aggregates 4^4, 24 test
+// vectors, 20 rhs on 16^3 x 32, first form
 // (scalar FMAs on LDS tiles) -> now: restriction FP64 329 -> 264 us, FP32 177 ->
 // 150, FP16 200 -> 51 (277 MB: at the rate of a copy); prolongation FP64 394 -> 269,
 // FP32 203 -> 153, FP16 added 289 -> 160 (530 MB, 104 us at that rate).
@@ -646,7 +647,8 @@ static void check_transfer(const TGeom& t) {
 struct TransferSplit {
   int wpa, nt;
 };
-static TransferSplit transfer_split(const Context* c, const TGeom& t, int tiles, int one_max, int four_max, int cu_waves) {
+static TransferSplit transfer_split(const Context* c, const TGeom& t, int tiles, int one_max, int four_max,
+                                    int cu_waves) {
   auto groups = [&](int nt) { return (tiles + nt - 1) / nt; };
   auto even = [&](int most) { return groups(groups(most)); };
   const int one = even(one_max);
@@ -674,7 +676,8 @@ static void launch_restrict_nt(Context* c, const TGeom& t, const typename P::S* 
                      (size_t)(4 / wpa) * (wpa - 1) * MT * NT * 64 * sizeof(typename Mm<typename P::R>::V4);
   launch_tiles(transfer_blocks(t, wpa), (nrhs + 8 * NT - 1) / (8 * NT), (t.ntv + 16 * MT - 1) / (16 * MT),
                [&](dim3 nb, Tiles p) {
-                 hipLaunchKernelGGL((k_restrict<P, PM, MT, NT>), nb, dim3(256), lds, c->stream, x, yc, Pm, t, nrhs, wpa, p);
+                 hipLaunchKernelGGL((k_restrict<P, PM, MT, NT>), nb, dim3(256), lds, c->stream, x, yc, Pm, t, nrhs,
+                                    wpa, p);
                });
 }
 // Tiles of rhs.  FP64: up to three whole, more one by one, whose registers hold four
@@ -787,10 +790,11 @@ void Transfer::restrict16(const __half2* x16, const double* xs, float2* yc, int 
   const size_t lds = sizeof(uint32_t) * (4 / q.wpa) * row_words(t.rows) +
                      (size_t)(4 / q.wpa) * (q.wpa - 1) * MT * q.nt * 64 * sizeof(f4_t);
   auto launch = [&](auto* k) {
-    launch_tiles(transfer_blocks(t, q.wpa), (nrhs + 16 * q.nt - 1) / (16 * q.nt), (mt + MT - 1) / MT, [&](dim3 nb, Tiles p) {
-      hipLaunchKernelGGL(k, nb, dim3(256), lds, ctx->stream, (const uint32_t*)x16, yc, (const uint32_t*)P16, t, nrhs,
-                         q.wpa, xs, xgs, p);
-    });
+    launch_tiles(transfer_blocks(t, q.wpa), (nrhs + 16 * q.nt - 1) / (16 * q.nt), (mt + MT - 1) / MT,
+                 [&](dim3 nb, Tiles p) {
+                   hipLaunchKernelGGL(k, nb, dim3(256), lds, ctx->stream, (const uint32_t*)x16, yc,
+                                      (const uint32_t*)P16, t, nrhs, q.wpa, xs, xgs, p);
+                 });
   };
 #define MGM_R16(M, N) \
   if (MT == M && q.nt == N) launch(k_restrict16<M, N>);
