@@ -1769,6 +1769,13 @@ bool FineOp::step_fusable(mgm_prec p, int nrhs) const {
   return false;
 }
 
+static std::string step_key(const FineOp& op, mgm_prec p, int nrhs) {
+  return "dslash_step/" + std::to_string((int)p) + "/" + std::to_string(op.g.V) + "/" + std::to_string(nrhs);
+}
+bool FineOp::step_chosen(int nrhs) const {
+  return ctx->tune.find(step_key(*this, MGM_PREC_F16, nrhs), lattice_of(g)) != nullptr;
+}
+
 double FineOp::step_bytes(mgm_prec p, int nrhs) const {
   // the dslash (r in, r' out in place of q), plus x read and written
   return bytes(p, nrhs) + 2.0 * 12.0 * (double)g.V * nrhs * (double)prec_bytes(p);
@@ -1783,7 +1790,7 @@ int64_t FineOp::apply_step(mgm_prec p, const void* r, void* r_next, void* x, con
   mr.x = x;
   mr.qr = qr;
   mr.qq = qq;
-  const std::string key = "dslash_step/" + std::to_string((int)p) + "/" + std::to_string(g.V) + "/" + std::to_string(nrhs);
+  const std::string key = step_key(*this, p, nrhs);
   ProfScope ps(ctx, KC_DSLASH_STEP, step_bytes(p, nrhs));
   int64_t nb = 0;
   // variants: every shape with FP32 arithmetic on converted values, then

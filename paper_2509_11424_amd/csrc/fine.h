@@ -49,6 +49,8 @@ struct FineOp {
   double step_bytes(mgm_prec p, int nrhs) const;
   // estimated microseconds of one FP16 smoother step in its default form
   double step_us(int nrhs) const;
+  // whether a launch variant of the step is tuned or pinned for this rhs count
+  bool step_chosen(int nrhs) const;
 };
 
 }  // namespace mgm

@@ -110,18 +110,20 @@ static bool smooth_f16(Hier& H, int l, mgm_prec p, const SolveCfg& cfg) {
 // groups on 32^3 x 64 (20 rhs: 5 steps of 0.68 ms against 4.5 ms) and none on
 // 16^4 (12 rhs: 0.10 ms against 3 of 0.035 ms).  The estimates are those of the
 // untuned forms: while the autotuner is on, groups are formed wherever they
-// can be, as it then measures the marching shapes of each.  Returns the group
-// size (nrhs: no groups).
+// can be, as it then measures the marching shapes of each, and afterwards, or with
+// a saved table, where their step has a tuned or pinned variant.  Returns the
+// group size (nrhs: no groups).
 static bool smooth_fusable(Hier& H, int nrhs, const SolveCfg& cfg) {
   return cfg.smooth >= 2 && H.ws16[0].qr2 != nullptr && H.fine->step_fusable(MGM_PREC_F16, nrhs);
 }
 static int smooth_group(Hier& H, int nrhs, const SolveCfg& cfg) {
   if (nrhs <= 8) return nrhs;
-  if (H.ctx->tune.enabled) {
-    for (int gs : {8, 4})
-      if (nrhs % gs == 0 && smooth_fusable(H, gs, cfg)) return gs;
-    return nrhs;
-  }
+  for (int gs : {8, 4})
+    if (nrhs % gs == 0 && smooth_fusable(H, gs, cfg)) {
+      if (H.ctx->tune.enabled || H.fine->step_chosen(gs)) return gs;
+      break;
+    }
+  if (H.ctx->tune.enabled) return nrhs;
   int best = nrhs;
   double t = smooth_fusable(H, nrhs, cfg) ? H.fine->step_us(nrhs) + 8.0 : 1e30;
   for (int gs : {8, 4}) {
