@@ -590,31 +590,30 @@ static std::vector<int> staged4_splits(const CoarseOp& A, int nrhs, size_t cb) {
 // fragments where the sites fill the chip (8 rhs, 48 dof, 8192 sites: 298 us against
 // 337 staged); with few sites the split over all row tiles shortens the
 // chain of a site (4 rhs, 64 dof, 512 sites: FP64 164 -> 88 us, FP32 90 -> 50).
-// Fewer sites than CUs: more than four tiles in one workgroup leave the others idle (100 rhs,
-// 48 dof, 16 sites: FP32 41 us against 58 staged, FP64 77 and 99), and three row tiles, which
-// do not split, gain nothing from sharing (1 rhs, 48 dof, 64 sites: FP32 41 and 45, FP64 74 and
-// 77; 20 rhs FP32 41 and 49).  One row tile in FP64: the fragments of a site are
-// few, and from 2048 sites on (1024 with more than four tiles) the chip is full without
-// (8 dof, 4096 sites: 17 rhs 32 and 41 us, 100 rhs 106 and 124).
+// Times below are repeated launches / a launch after other work, whose fragments come from
+// HBM.  More than four tiles in one workgroup leave CUs idle where the sites are half as many
+// or fewer: four row tiles are split (100 rhs, 64 dof, 64 sites: FP64 138 / 167 us with one
+// wave per tile, 162 / 177 staged, 109 / 114 split, FP32 82 / 116, 95 / 105, 70 / 75), three
+// do not split and stay with one wave (48 dof: FP64 88 / 112 and 107 / 122; FP32 on 64 sites
+// 42 / 81 and 59 / 68, on 128 58 / 83 and 61 / 69).  One row tile in FP64: the fragments of a
+// site are few, and from 2048 sites on (1024 with more than four tiles) the chip is
+// full without (16 dof, 20 rhs, 4096 sites: 57 / 83 us, 72 / 94 staged).
 static int staged4_default(const CoarseOp& A, int ntr, int ns, const std::vector<int>& splits, bool f64) {
   if (splits.empty()) return 0;
   const int MT = mgeo(A.d).MT;
-  if (A.g.V < A.ctx->cu_count && (ntr > 4 || (MT == 3 && ntr <= (f64 ? 1 : 2)))) return 0;
-  if (f64 && MT == 1 && A.g.V >= (ntr > 4 ? 1024 : 2048)) return 0;
-  if (ntr == 1) return A.g.V < 1024 ? ns + (int)splits.size() - 1 : 0;
+  const int64_t V = A.g.V, cus = A.ctx->cu_count;
+  if (ntr > 4 && MT == 4 && 2 * V <= cus) return ns + (int)splits.size() - 1;
+  if (ntr > 4 && MT == 3 && (f64 ? 2 : 4) * V <= cus) return 0;
+  if (f64 && MT == 1 && V >= (ntr > 4 ? 1024 : 2048)) return 0;
+  if (ntr == 1) return V < 1024 ? ns + (int)splits.size() - 1 : 0;
   return ntr == 2 && MT == 4 ? ns + 1 : ns;
 }
-// BF16: staged except for a single tile where the forms of one wave per tile are as well
-// without: four row tiles with fewer sites than CUs (56 dof, 64 sites, 4 rhs: 20 us, 23 staged),
-// two and four while all sites fit the chip at once (24 dof, 4096 sites, 1 rhs: 27 and
-// 33; 64 dof, 2048 sites, 16 rhs: 34 and 37), 8 dof on many sites (8192, 8 rhs: 21 and 22).
+// BF16: staged except for a single tile of an even number of row tiles where all sites fit
+// the chip at once, about 2048 (24 dof, 4 rhs: 19 / 36 us with one wave per tile, 21 / 37
+// staged; 64 dof, 8 rhs 66 / 120 and 67 / 125; on 4096 sites 24 dof, 12 rhs 43 / 75 and
+// 36 / 69; 64 dof, 4 rhs on 64 sites 20 / 36 and 22 / 25).
 static bool staged_bf16_default(const CoarseOp& A, int ntr) {
-  if (ntr > 1) return true;
-  const int64_t V = A.g.V;
-  const int MT = mgeo(A.d).MT;
-  if (MT == 4 && V < A.ctx->cu_count) return false;
-  if (MT % 2 == 0 && V >= 2048 && V * MT < 16384) return false;
-  return !(A.d <= 8 && V >= 8192);
+  return ntr > 1 || mgeo(A.d).MT % 2 != 0 || A.g.V < 2048 || A.g.V >= 4096;
 }
 template <class M>
 static void launch_staged4(const CoarseOp& A, const typename M::C2* x, typename M::C2* y, const typename M::C2* Ap,
