@@ -100,10 +100,10 @@ void mg_agg_map(Context* c, const TGeom& t, int64_t* out) {
 // as they share P and the lines at the ends of their column ranges: FP32
 // prolongation of 33 rhs on 16^3 x 32 in 2^4 aggregates, 24 test vectors, 404 us with the
 // tiles in separate passes over the lattice, 330 side by side.  Aggregates 4^4, 24 test
-// vectors, 20 rhs on 16^3 x 32, first form
-// (scalar FMAs on LDS tiles) -> now: restriction FP64 329 -> 264 us, FP32 177 ->
-// 150, FP16 200 -> 51 (277 MB: at the rate of a copy); prolongation FP64 394 -> 269,
-// FP32 203 -> 153, FP16 added 289 -> 160 (530 MB, 104 us at that rate).
+// vectors, 20 rhs on 16^3 x 32, first form (scalar FMAs on LDS tiles) -> now:
+// restriction FP64 324 -> 259 us, FP32 176 -> 142, FP16 200 -> 50 (277 MB: at the
+// rate of a copy); prolongation FP64 393 -> 251, FP32 203 -> 123, FP16 added
+// 290 -> 155 (530 MB, 104 us at that rate).
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef double d4_t __attribute__((ext_vector_type(4)));
@@ -440,11 +440,12 @@ __global__ __launch_bounds__(256) void k_restrict16(const uint32_t* __restrict__
 // wave, the 2 nr columns (re, im of each rhs side by side, nr rhs from
 // 8 NT at.y on) the B tiles, from an LDS copy of the aggregate's coarse
 // values.  VK consecutive test vectors per A load (4 VK divides N_tv where VK > 1).
-// ALL (four waves an aggregate): the entries of P of 32 test vectors (FP64: 16) are loaded
-// together, so that the lines of a row are read once before other waves replace
-// them in L1 (FP16 added, 20 rhs on 24^3 x 48 in 4^4 aggregates, 24 test vectors, 742 us to 688);
-// else in steps, with fewer registers (FP32, 32 rhs on 16^4 in 2^4 aggregates, 12 test vectors,
-// 75 us in steps, 82 with all).
+// ALL: the entries of P of 32 test vectors (FP64: 16) are loaded together, so that the lines
+// of a row are read once before other waves replace them in L1, and their latency is paid
+// once (FP16 added, 24 test vectors: 20 rhs on 24^3 x 48 in 4^4 aggregates 742 us to 688, 12 rhs on
+// 16^3 x 32 in 2^4 133 to 119, with cold caches 164 to 144); else in steps, with fewer registers: one
+// wave an aggregate with four tiles of rhs and more, FP64 three (FP32, 32 rhs on 16^4, 12 test
+// vectors, 55 us in steps, 85 with all; FP64 50 rhs 260, 282 with all).
 template <class P, class PM, class PX, int NT, int VK, bool ALL>
 __global__ __launch_bounds__(256) void k_prolong(const typename P::S* __restrict__ xc, const typename P::S* __restrict__ x,
                                                  typename P::S* __restrict__ y, const typename PM::S* __restrict__ Pm,
@@ -737,10 +738,10 @@ static void launch_prolong_vk(Context* c, const TGeom& t, const typename P::S* x
   };
   const bool all = q.wpa == 4;
   switch (q.nt) {
-    case 1: launch(all ? k_prolong<P, PM, PX, 1, VK, true> : k_prolong<P, PM, PX, 1, VK, false>); break;
-    case 2: launch(all ? k_prolong<P, PM, PX, 2, VK, true> : k_prolong<P, PM, PX, 2, VK, false>); break;
-    case 3: launch(all ? k_prolong<P, PM, PX, 3, VK, true> : k_prolong<P, PM, PX, 3, VK, false>); break;
-    case 4: launch(all ? k_prolong<P, PM, PX, 4, VK, true> : k_prolong<P, PM, PX, 4, VK, false>); break;
+    case 1: launch(k_prolong<P, PM, PX, 1, VK, true>); break;
+    case 2: launch(k_prolong<P, PM, PX, 2, VK, true>); break;
+    case 3: launch(all || !f64 ? k_prolong<P, PM, PX, 3, VK, true> : k_prolong<P, PM, PX, 3, VK, false>); break;
+    case 4: launch(all || f64 ? k_prolong<P, PM, PX, 4, VK, true> : k_prolong<P, PM, PX, 4, VK, false>); break;
     default:
       if constexpr (!f64) launch(k_prolong<P, PM, PX, 5, VK, false>);  // one wave an aggregate
   }
