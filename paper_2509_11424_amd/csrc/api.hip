@@ -64,6 +64,11 @@ const Tuner::Entry* Tuner::find(const std::string& key, const std::string& latti
 
 int Context::choose(const std::string& key, int nvar, const std::function<void(int)>& run, int dflt, int more,
                     const std::string& lattice) {
+  const bool tunes = tune.enabled && !capturing && nvar + more > 1;
+  if (tune.table.empty() && !tunes) {
+    run(dflt);
+    return dflt;
+  }
   const std::string form_key = behind_kind(key, "_form@" + lattice);
   const Tuner::Entry* e = tune.find(key, lattice);
   const Tuner::Entry* f = lattice.empty() ? nullptr : tune.at(form_key);
@@ -77,7 +82,7 @@ int Context::choose(const std::string& key, int nvar, const std::function<void(i
     v = e->variant;
     MGM_CHECK(v < nvar + more, MGM_ERR_INVALID_ARG,
               "pinned launch variant " + std::to_string(v) + " out of range for " + key);
-  } else if (tune.enabled && !capturing && nvar + more > 1) {
+  } else if (tunes) {
     const bool prof_was_on = prof.on;
     prof.on = false;  // tuning launches stay out of the kernel-class statistics
     hipEvent_t a = take_event(), b = take_event();
